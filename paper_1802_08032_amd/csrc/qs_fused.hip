@@ -38,11 +38,14 @@ namespace {
 constexpr int kTBMax = 10;
 constexpr int kRBMax = 5;
 
+// One register layout of a pass, 32 words: every wave loads it as one word
+// per lane and reads the words back with v_readlane.
 struct FPhase {
     uint32_t wthr[kTBMax], wreg[kRBMax];  // LDS images of the layout being left
     uint32_t rthr[kTBMax], rreg[kRBMax];  // LDS images of the layout entered
-    int op_begin, op_end;
+    uint32_t op_begin, op_end;
 };
+static_assert(sizeof(FPhase) == 32 * sizeof(uint32_t), "a phase is one word for each of 32 lanes");
 
 struct FPass {
     int nphases;
@@ -50,155 +53,249 @@ struct FPass {
     uint64_t ld_thr[kTBMax], ld_reg[kRBMax];  // HBM offsets of the load layout
     uint64_t st_thr[kTBMax], st_reg[kRBMax];  // HBM offsets of the store layout
     BitInsert outside;                        // inserts zeros at the tile's qubits
-    FPhase ph[kPhMax];
-    FPhase fin;
+    FPhase ph[kPhMax + 1];                    // the phases, then (final_transpose) the store layout
 };
 
+// Host form of an op.
 struct FOp {
-    int kind;        // specialised op code (see apply_op)
+    int kind;        // op code, below
     int rb;          // target register bit (dense / not / core)
     uint32_t rmask;  // register bits that must be 1
     uint32_t tmask;  // thread-index bits that must be 1
     uint64_t gmask;  // global qubits outside the tile that must be 1
     double m[8];     // dense matrix, phase factor in m[0], m[1], or core coefficient k in m[0], m[1]
     uint32_t aux;    // 4x4 ops: entry of the 4x4 matrix table
-    uint32_t pad;
+    bool cx;         // kNot with a register control: the phase of both bits follows
+    bool lane;       // kPhase: a phase of lanes in the planned layout (phase_case)
 };
 
-// In-register op application.  Conditions that are the same for the whole
-// workgroup (controls outside the tile, register-bit controls) become scalar
-// selects; only thread-bit controls need per-lane selects.  Every variant is
-// straight-line code over compile-time register indices.
-
+// Device form: one or more FOps that a wave runs under one dispatch, in the
+// order cores, NOT, phase, signs (bundle() below).
+//   code  class bits | tmask << 16
+//   sub   one bit of the class's list (NOT, 4x4, other)
+//   multi bits 0..4 in-place cores on register bits 0..4, 5..9 exchanged cores, 10..14 rmask,
+//         15..19 signs of single bits, 20..29 signs of pairs
+//   ph    the phase's register bits: 0..4 single bits, 5..14 pairs, kPhAny rmask, kPhAll none
+//   m     the core coefficient of register bit b at 2 b; at 10 a phase factor; the matrix of kOther
+//         at 0; the table entry of a 4x4 in the bits of m[10]
 template <typename T>
-__device__ __forceinline__ void load_mat(T (&m)[8], const FOp& op)
+struct alignas(16) FRec {
+    uint32_t code, sub, multi, ph;
+    uint64_t gmask;
+    T m[12];
+};
+
+// Op kinds: class << 5 | sub.  Register-bit pairs (b1 < b2) are numbered in
+// lexical order.
+//   kCoreA, sub rb     unit-diagonal core, amplitudes in place: (a, b) <- (a + k b, b - conj(k) a)
+//   kCoreB, sub rb     core with the pair exchanged: (a, b) <- (k a + b, a - conj(k) b)
+//   kNot, sub 6 rb + c NOT on rb where register bit c is 1 (c = 5: everywhere)
+//   kNotM, sub rb      NOT with any register and thread-bit controls
+//   kPhase, sub        phase m[0] + i m[1]: sub 0 no register bit, 1 + b where bit b is 1,
+//                      6 + pair where both are 1, 16 any rmask; thread-bit controls in tmask
+//   kSign, sub         the phase -1, subs as kPhase
+//   kDense4, sub pair  4x4 on register bits, matrix in the 4x4 table
+//   kOther, sub rb     dense 2x2 with any controls; sub 8 + rb: a diagonal one;
+//                      sub 16: nothing (a gate whose effect is deferred)
+// A kNot with `cx` has c < 5 and is followed by the phase m[0] + i m[1] where
+// both bits of rmask are 1.
+enum : int {
+    kCoreA = 0, kCoreB = 32, kNot = 64, kNotM = 96, kPhase = 128, kSign = 160, kDense4 = 192, kOther = 224,
+    kDiag = kOther + 8, kNop = kOther + 16
+};
+// Class bits of the device code.
+enum : uint32_t {
+    kcCore = 1, kcNot = 2, kcPhase = 4, kcSign = 8, kcRare = 16, kcNotM = 32, kcDense4 = 64, kcOther = 128, kcLane = 256
+};
+
+constexpr uint32_t kPhAny = 1u << 15, kPhAll = 1u << 16;
+
+constexpr int kPairB1[10] = {0, 0, 0, 0, 1, 1, 1, 2, 2, 3};
+constexpr int kPairB2[10] = {1, 2, 3, 4, 2, 3, 4, 3, 4, 4};
+
+inline int pair_of(int b1, int b2)
 {
-#pragma unroll
-    for (int k = 0; k < 8; ++k) m[k] = (T)op.m[k];
+    if (b1 > b2) std::swap(b1, b2);
+    int p = 0;
+    while (!(kPairB1[p] == b1 && kPairB2[p] == b2)) ++p;
+    return p;
 }
 
-// Identity element k of a row-major interleaved 2x2 matrix.
-template <typename T>
-__device__ __forceinline__ T ident(int k) { return (k == 0 || k == 6) ? T(1) : T(0); }
+__device__ __forceinline__ uint32_t lane_get(uint32_t v, int l) { return (uint32_t)__builtin_amdgcn_readlane((int)v, l); }
+__device__ __forceinline__ float lane_get(float v, int l)
+{
+    return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), l));
+}
+__device__ __forceinline__ double lane_get(double v, int l)
+{
+    const long long b = __double_as_longlong(v);
+    const uint32_t lo = lane_get((uint32_t)b, l), hi = lane_get((uint32_t)((unsigned long long)b >> 32), l);
+    return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
+}
 
-// Dense 2x2 on register bit RBIT.  MASKED: only pairs whose register index
-// has every bit of rmask set (identity matrix elsewhere, chosen per pair).
-template <typename T, int RB, int RBIT, bool MASKED>
-__device__ __forceinline__ void dense_rb(typename C2<T>::type (&v)[1 << RB], const T (&m)[8], uint32_t rmask)
+__device__ __forceinline__ float flip_sign(float v, uint32_t s) { return __uint_as_float(__float_as_uint(v) ^ s); }
+__device__ __forceinline__ double flip_sign(double v, uint32_t s)
+{
+    return __longlong_as_double(__double_as_longlong(v) ^ (long long)((unsigned long long)s << 32));
+}
+
+// Up to 64 op records of a phase, one per lane.
+template <typename T, int RB>
+struct OpLanes {
+    uint32_t code, sub, multi, ph;
+    uint64_t gmask;
+    T m[2 * RB], f0, f1;
+};
+
+template <typename T, int RB>
+__device__ __forceinline__ OpLanes<T, RB> load_ops(const FRec<T>* __restrict__ recs, uint32_t begin, uint32_t end,
+                                                   uint32_t lane)
+{
+    OpLanes<T, RB> o;
+    const uint32_t i = begin + lane;
+    const FRec<T>* R = recs + (i < end ? i : begin);
+    o.code = R->code;
+    o.sub = R->sub;
+    o.multi = R->multi;
+    o.ph = R->ph;
+    o.gmask = R->gmask;
+#pragma unroll
+    for (int k = 0; k < 2 * RB; ++k) o.m[k] = R->m[k];
+    o.f0 = R->m[10];
+    o.f1 = R->m[11];
+    return o;
+}
+
+// --- in-register ops: straight-line code over compile-time register indices ---
+
+// Dense 2x2 on register bit RBIT for the pairs whose register index has every
+// bit of rmask set (uniform branches) on the lanes that `sel` selects.
+template <typename T, int RB, int RBIT>
+__device__ __forceinline__ void dense_case(typename C2<T>::type (&v)[1 << RB], const T (&mm)[8], uint32_t rmask,
+                                           bool sel)
 {
     using V = typename C2<T>::type;
+    T m[8];
+#pragma unroll
+    for (int k = 0; k < 8; ++k) m[k] = sel ? mm[k] : (k == 0 || k == 6) ? T(1) : T(0);
 #pragma unroll
     for (int r0 = 0; r0 < (1 << RB); ++r0) {
         if (r0 & (1 << RBIT)) continue;
-        if constexpr (MASKED) {
-            // the register-control test is the same for every lane: a scalar
-            // branch skips the pairs it excludes
-            if (((uint32_t)r0 & rmask) == rmask) apply2<T, V>(m, v[r0], v[r0 | (1 << RBIT)]);
-        } else {
-            apply2<T, V>(m, v[r0], v[r0 | (1 << RBIT)]);
-        }
+        if (((uint32_t)r0 & rmask) == rmask) apply2<T, V>(m, v[r0], v[r0 | (1 << RBIT)]);
     }
 }
 
-// NOT on register bit RBIT: swap each pair where `sel` (per lane) and, when
-// MASKED, the pair's register controls hold.  LANE = false: sel is true.
-template <typename T, int RB, int RBIT, bool MASKED, bool LANE>
-__device__ __forceinline__ void not_rb(typename C2<T>::type (&v)[1 << RB], uint32_t rmask, bool sel)
+template <typename T, int RB, int RBIT>
+__device__ __forceinline__ void diag_case(typename C2<T>::type (&v)[1 << RB], const T (&mm)[8], uint32_t rmask,
+                                          bool sel)
+{
+    using V = typename C2<T>::type;
+    const T d0r = sel ? mm[0] : T(1), d0i = sel ? mm[1] : T(0), d1r = sel ? mm[6] : T(1), d1i = sel ? mm[7] : T(0);
+#pragma unroll
+    for (int r0 = 0; r0 < (1 << RB); ++r0) {
+        if (r0 & (1 << RBIT)) continue;
+        if (((uint32_t)r0 & rmask) != rmask) continue;
+        v[r0] = cmul<T, V>(d0r, d0i, v[r0]);
+        v[r0 | (1 << RBIT)] = cmul<T, V>(d1r, d1i, v[r0 | (1 << RBIT)]);
+    }
+}
+
+// NOT on RBIT where register bit C is 1 (C == 5: everywhere): moves only.
+template <typename T, int RB, int RBIT, int C>
+__device__ __forceinline__ void not_case(typename C2<T>::type (&v)[1 << RB])
+{
+#pragma unroll
+    for (int r0 = 0; r0 < (1 << RB); ++r0) {
+        if (r0 & (1 << RBIT)) continue;
+        if (C < 5 && !((r0 >> C) & 1)) continue;
+        const int r1 = r0 | (1 << RBIT);
+        const T ax = v[r0].x, ay = v[r0].y, bx = v[r1].x, by = v[r1].y;
+        v[r0].x = bx;
+        v[r0].y = by;
+        v[r1].x = ax;
+        v[r1].y = ay;
+    }
+}
+
+template <typename T, int RB, int RBIT>
+__device__ __forceinline__ void notm_case(typename C2<T>::type (&v)[1 << RB], uint32_t rmask, bool sel)
 {
     using V = typename C2<T>::type;
 #pragma unroll
     for (int r0 = 0; r0 < (1 << RB); ++r0) {
         if (r0 & (1 << RBIT)) continue;
         const int r1 = r0 | (1 << RBIT);
-        if constexpr (MASKED) {  // uniform over the wave: skip excluded pairs by a branch
-            if (((uint32_t)r0 & rmask) != rmask) continue;
-        }
-        const bool c = LANE ? sel : true;
-        if constexpr (!LANE) {
-            const V t = v[r0];
-            v[r0] = v[r1];
-            v[r1] = t;
-        } else {
-            const V a = v[r0], b = v[r1];
-            v[r0].x = c ? b.x : a.x;
-            v[r0].y = c ? b.y : a.y;
-            v[r1].x = c ? a.x : b.x;
-            v[r1].y = c ? a.y : b.y;
-        }
+        if (((uint32_t)r0 & rmask) != rmask) continue;  // uniform over the wave
+        const V a = v[r0], b = v[r1];
+        v[r0].x = sel ? b.x : a.x;
+        v[r0].y = sel ? b.y : a.y;
+        v[r1].x = sel ? a.x : b.x;
+        v[r1].y = sel ? a.y : b.y;
     }
 }
 
-// Diagonal phase: multiply the registers whose index has every bit of rmask
-// set by (fr, fi) (already 1 on lanes that fail their thread-bit controls).
-template <typename T, int RB>
-__device__ __forceinline__ void phase_op(typename C2<T>::type (&v)[1 << RB], T fr, T fi, uint32_t rmask)
+// Multiply the registers whose index has every bit of MASK set by (fr, fi).
+// The two products of the imaginary part round differently with their order;
+// LANE has the one that phases of lanes use.  Each kind keeps its order, so
+// that the sums of a complex64 batch do not change with its layout.
+template <typename T, int RB, uint32_t MASK, bool LANE = false>
+__device__ __forceinline__ void phase_case(typename C2<T>::type (&v)[1 << RB], T fr, T fi, uint32_t rmask = 0)
 {
-    using V = typename C2<T>::type;
 #pragma unroll
     for (int r = 0; r < (1 << RB); ++r)
-        if (((uint32_t)r & rmask) == rmask) v[r] = cmul<T, V>(fr, fi, v[r]);  // uniform branch
+        if (((uint32_t)r & MASK) == MASK && ((uint32_t)r & rmask) == rmask) {
+            const T x = v[r].x, y = v[r].y;
+            v[r].x = fma(fr, x, -(fi * y));
+            v[r].y = LANE ? fma(fi, x, fr * y) : fma(fr, y, fi * x);
+        }
 }
 
-// Op codes: the host specialises every op so that the device dispatches with
-// one switch and each case is straight-line code.
-//   code = 4 * rb + variant        dense gate (variant: bit 0 register controls,
-//                                  bit 1 thread-bit controls)
-//   code = 32 + 4 * rb + variant   NOT
-//   code = 64 + lane               phase (lane: thread-bit controls present)
-//   code = 96 + 4 * rb + variant   diagonal dense gate (u01 = u10 = 0)
-//   code = 128 + 4 * rb            unit-diagonal core, amplitudes in place:
-//                                  (a, b) <- (a + k b, b - conj(k) a)
-//   code = 160 + 4 * rb            core with the pair exchanged:
-//                                  (a, b) <- (k a + b, a - conj(k) b)
-//   code = 192 + pair              4x4 on register bits (b1 < b2), pair index
-//                                  of (b1, b2), matrix in the 4x4 table
-//   code = 255                     nothing (a gate whose effect is deferred)
-enum : int { kDense = 0, kNot = 32, kPhase = 64, kDiag = 96, kCoreA = 128, kCoreB = 160, kDense4 = 192, kNop = 255 };
-
-// Register-bit pairs of the 4x4 ops, indexed by (b1 < b2) in lexical order.
-constexpr int kPairB1[10] = {0, 0, 0, 0, 1, 1, 1, 2, 2, 3};
-constexpr int kPairB2[10] = {1, 2, 3, 4, 2, 3, 4, 3, 4, 4};
-
-template <typename T, int RB, int RBIT, bool EXCH>
-__device__ __forceinline__ void core_case(typename C2<T>::type (&v)[1 << RB], const FOp& op)
+template <typename T, int RB, uint32_t MASK>
+__device__ __forceinline__ void sign_case(typename C2<T>::type (&v)[1 << RB], uint32_t s)
 {
-    using V = typename C2<T>::type;
-    const T kr = (T)op.m[0], ki = (T)op.m[1];
+#pragma unroll
+    for (int r = 0; r < (1 << RB); ++r)
+        if (((uint32_t)r & MASK) == MASK) {
+            v[r].x = flip_sign(v[r].x, s);
+            v[r].y = flip_sign(v[r].y, s);
+        }
+}
+
+// In-place form: the new b takes a fresh register, the new a is accumulated
+// where a was (for EXCH, where b was).
+template <typename T, int RB, int RBIT, bool EXCH>
+__device__ __forceinline__ void core_case(typename C2<T>::type (&v)[1 << RB], T kr, T ki)
+{
 #pragma unroll
     for (int r0 = 0; r0 < (1 << RB); ++r0) {
         if (r0 & (1 << RBIT)) continue;
-        const V a = v[r0], b = v[r0 | (1 << RBIT)];
-        V na, nb;
-        if constexpr (!EXCH) {  // a + k b, b - conj(k) a
-            na.x = kr * b.x + a.x;
-            na.x = -ki * b.y + na.x;
-            na.y = kr * b.y + a.y;
-            na.y = ki * b.x + na.y;
-            nb.x = -kr * a.x + b.x;
-            nb.x = -ki * a.y + nb.x;
-            nb.y = -kr * a.y + b.y;
-            nb.y = ki * a.x + nb.y;
-        } else {  // k a + b, a - conj(k) b
-            na.x = kr * a.x + b.x;
-            na.x = -ki * a.y + na.x;
-            na.y = kr * a.y + b.y;
-            na.y = ki * a.x + na.y;
-            nb.x = -kr * b.x + a.x;
-            nb.x = -ki * b.y + nb.x;
-            nb.y = -kr * b.y + a.y;
-            nb.y = ki * b.x + nb.y;
-        }
-        v[r0] = na;
-        v[r0 | (1 << RBIT)] = nb;
+        // with the pair exchanged, (k a + b, a - conj(k) b) is the plain core of (b, a)
+        const int ra = EXCH ? r0 | (1 << RBIT) : r0, rb = EXCH ? r0 : r0 | (1 << RBIT);
+        T ax = v[ra].x, ay = v[ra].y, bx = v[rb].x, by = v[rb].y;
+        T nx = -kr * ax + bx;
+        T ny = -kr * ay + by;
+        nx = -ki * ay + nx;
+        ny = ki * ax + ny;
+        ax = kr * bx + ax;
+        ay = kr * by + ay;
+        ax = -ki * by + ax;
+        ay = ki * bx + ay;
+        v[r0].x = ax;
+        v[r0].y = ay;
+        v[r0 | (1 << RBIT)].x = nx;
+        v[r0 | (1 << RBIT)].y = ny;
     }
 }
 
-// 4x4 complex matrix m (row-major, index bit(B1) + 2 bit(B2)) on every
-// register quad.
+// 4x4 complex matrix on every register quad, index bit(B1) + 2 bit(B2); lane
+// e of `mv` holds value e of the row-major interleaved matrix.
 template <typename T, int RB, int B1, int B2>
-__device__ __forceinline__ void dense4_case(typename C2<T>::type (&v)[1 << RB], const T* __restrict__ m)
+__device__ __forceinline__ void dense4_case(typename C2<T>::type (&v)[1 << RB], T mv)
 {
     using V = typename C2<T>::type;
+    T m[32];
+#pragma unroll
+    for (int k = 0; k < 32; ++k) m[k] = lane_get(mv, k);
 #pragma unroll
     for (int r0 = 0; r0 < (1 << RB); ++r0) {
         if ((r0 >> B1) & 1 || (r0 >> B2) & 1) continue;
@@ -225,99 +322,114 @@ __device__ __forceinline__ void dense4_case(typename C2<T>::type (&v)[1 << RB], 
     }
 }
 
-template <typename T, int RB, int RBIT, int VAR>
-__device__ __forceinline__ void dense_case(typename C2<T>::type (&v)[1 << RB], const FOp& op, uint32_t tid)
-{
-    T m[8];
-    load_mat<T>(m, op);
-    if constexpr (VAR & 2) {
-        const bool sel = (tid & op.tmask) == op.tmask;
-#pragma unroll
-        for (int k = 0; k < 8; ++k) m[k] = sel ? m[k] : ident<T>(k);
-    }
-    dense_rb<T, RB, RBIT, (VAR & 1) != 0>(v, m, op.rmask);
-}
+__device__ __forceinline__ uint32_t table_entry(float m) { return __float_as_uint(m); }
+__device__ __forceinline__ uint32_t table_entry(double m) { return (uint32_t)__double_as_longlong(m); }
 
-// Diagonal 2x2 on register bit RBIT: each amplitude of a pair is multiplied
-// by its diagonal entry (half the work of a dense product).
-template <typename T, int RB, int RBIT, int VAR>
-__device__ __forceinline__ void diag_case(typename C2<T>::type (&v)[1 << RB], const FOp& op, uint32_t tid)
-{
-    using V = typename C2<T>::type;
-    T d0r = (T)op.m[0], d0i = (T)op.m[1], d1r = (T)op.m[6], d1i = (T)op.m[7];
-    if constexpr (VAR & 2) {
-        const bool sel = (tid & op.tmask) == op.tmask;
-        d0r = sel ? d0r : T(1);
-        d0i = sel ? d0i : T(0);
-        d1r = sel ? d1r : T(1);
-        d1i = sel ? d1i : T(0);
-    }
-#pragma unroll
-    for (int r0 = 0; r0 < (1 << RB); ++r0) {
-        if (r0 & (1 << RBIT)) continue;
-        if constexpr (VAR & 1) {  // register controls: uniform over the wave
-            if (((uint32_t)r0 & op.rmask) != op.rmask) continue;
-        }
-        v[r0] = cmul<T, V>(d0r, d0i, v[r0]);
-        v[r0 | (1 << RBIT)] = cmul<T, V>(d1r, d1i, v[r0 | (1 << RBIT)]);
-    }
-}
-
-template <typename T, int RB, int RBIT, int VAR>
-__device__ __forceinline__ void not_case(typename C2<T>::type (&v)[1 << RB], const FOp& op, uint32_t tid)
-{
-    const bool sel = (tid & op.tmask) == op.tmask;
-    not_rb<T, RB, RBIT, (VAR & 1) != 0, (VAR & 2) != 0>(v, op.rmask, sel);
-}
-
-template <typename T, int RB, bool LANE>
-__device__ __forceinline__ void phase_case(typename C2<T>::type (&v)[1 << RB], const FOp& op, uint32_t tid)
-{
-    T fr = (T)op.m[0], fi = (T)op.m[1];
-    if constexpr (LANE) {
-        const bool sel = (tid & op.tmask) == op.tmask;
-        fr = sel ? fr : T(1);
-        fi = sel ? fi : T(0);
-    }
-    phase_op<T, RB>(v, fr, fi, op.rmask);
-}
+// One record.  Its classes and subs are single bits, tested one after the
+// other without else branches, each on a value the compiler cannot relate to
+// the last test: such a chain keeps the amplitudes in the same registers
+// throughout, while a switch over the ops becomes a net of branches that
+// copies all of them (2,200 moves in the kernel, about 800 cycles per op).
+#define QS_IF(word, mask) \
+    asm volatile("" : "+s"(word)); \
+    if (__builtin_expect(((word) & (mask)) != 0, 0))
 
 template <typename T, int RB>
-__device__ __forceinline__ void apply_op(typename C2<T>::type (&v)[1 << RB], const FOp& op, uint32_t tid,
-                                         const T* __restrict__ m4tab)
+__device__ __forceinline__ void apply_op(typename C2<T>::type (&v)[1 << RB], const OpLanes<T, RB>& o, int i, uint32_t code,
+                                         T m4, const FRec<T>* __restrict__ rec, uint32_t tid)
 {
-    switch (op.kind) {
-#define QS_DENSE(RBIT)                                                                   \
-    case kDense + 4 * RBIT + 0: if constexpr (RB > RBIT) dense_case<T, RB, RBIT, 0>(v, op, tid); break; \
-    case kDense + 4 * RBIT + 1: if constexpr (RB > RBIT) dense_case<T, RB, RBIT, 1>(v, op, tid); break; \
-    case kDense + 4 * RBIT + 2: if constexpr (RB > RBIT) dense_case<T, RB, RBIT, 2>(v, op, tid); break; \
-    case kDense + 4 * RBIT + 3: if constexpr (RB > RBIT) dense_case<T, RB, RBIT, 3>(v, op, tid); break; \
-    case kNot + 4 * RBIT + 0: if constexpr (RB > RBIT) not_case<T, RB, RBIT, 0>(v, op, tid); break;     \
-    case kNot + 4 * RBIT + 1: if constexpr (RB > RBIT) not_case<T, RB, RBIT, 1>(v, op, tid); break;     \
-    case kNot + 4 * RBIT + 2: if constexpr (RB > RBIT) not_case<T, RB, RBIT, 2>(v, op, tid); break;     \
-    case kNot + 4 * RBIT + 3: if constexpr (RB > RBIT) not_case<T, RB, RBIT, 3>(v, op, tid); break;     \
-    case kDiag + 4 * RBIT + 0: if constexpr (RB > RBIT) diag_case<T, RB, RBIT, 0>(v, op, tid); break;   \
-    case kDiag + 4 * RBIT + 1: if constexpr (RB > RBIT) diag_case<T, RB, RBIT, 1>(v, op, tid); break;   \
-    case kDiag + 4 * RBIT + 2: if constexpr (RB > RBIT) diag_case<T, RB, RBIT, 2>(v, op, tid); break;   \
-    case kDiag + 4 * RBIT + 3: if constexpr (RB > RBIT) diag_case<T, RB, RBIT, 3>(v, op, tid); break;
-    QS_DENSE(0) QS_DENSE(1) QS_DENSE(2) QS_DENSE(3) QS_DENSE(4)
-#undef QS_DENSE
-#define QS_CORE(RBIT)                                                                                    \
-    case kCoreA + 4 * RBIT: if constexpr (RB > RBIT) core_case<T, RB, RBIT, false>(v, op); break;        \
-    case kCoreB + 4 * RBIT: if constexpr (RB > RBIT) core_case<T, RB, RBIT, true>(v, op); break;
-    QS_CORE(0) QS_CORE(1) QS_CORE(2) QS_CORE(3) QS_CORE(4)
-#undef QS_CORE
-#define QS_D4(P)                                                                                         \
-    case kDense4 + P:                                                                                    \
-        if constexpr (RB > kPairB2[P]) dense4_case<T, RB, kPairB1[P], kPairB2[P]>(v, m4tab + 32 * op.aux); \
-        break;
-    QS_D4(0) QS_D4(1) QS_D4(2) QS_D4(3) QS_D4(4) QS_D4(5) QS_D4(6) QS_D4(7) QS_D4(8) QS_D4(9)
+    uint32_t multi = lane_get(o.multi, i), sub = lane_get(o.sub, i);
+    QS_IF(code, kcCore) {
+#define QS_C(B)                                                                                                      \
+    if constexpr (RB > B) {                                                                                          \
+        QS_IF(multi, 1u << B) core_case<T, RB, B, false>(v, lane_get(o.m[2 * B], i), lane_get(o.m[2 * B + 1], i));   \
+        QS_IF(multi, 32u << B) core_case<T, RB, B, true>(v, lane_get(o.m[2 * B], i), lane_get(o.m[2 * B + 1], i));   \
+    }
+        QS_C(0) QS_C(1) QS_C(2) QS_C(3) QS_C(4)
+#undef QS_C
+    }
+    QS_IF(code, kcNot) {
+#define QS_N(B, C) \
+    if constexpr ((C == 5 || RB > C) && B != C) { QS_IF(sub, 1u << (6 * B + C)) not_case<T, RB, B, C>(v); }
+#define QS_NB(B)                                                                 \
+    if constexpr (RB > B) {                                                      \
+        QS_IF(sub, 63u << (6 * B)) {                                             \
+            QS_N(B, 0) QS_N(B, 1) QS_N(B, 2) QS_N(B, 3) QS_N(B, 4) QS_N(B, 5)    \
+        }                                                                        \
+    }
+        QS_NB(0) QS_NB(1) QS_NB(2) QS_NB(3) QS_NB(4)
+#undef QS_NB
+#undef QS_N
+    }
+    QS_IF(code, kcPhase) {
+        const uint32_t tmask = code >> 16, rmask = (multi >> 10) & 31u;
+        const bool sel = (tid & tmask) == tmask;
+        const T m0 = lane_get(o.f0, i), m1 = lane_get(o.f1, i);
+        const T fr = sel ? m0 : T(1), fi = sel ? m1 : T(0);
+        uint32_t ph = lane_get(o.ph, i);
+        QS_IF(ph, 31u) {
+#define QS_P(B) if constexpr (RB > B) { QS_IF(ph, 1u << B) phase_case<T, RB, 1u << B>(v, fr, fi); }
+            QS_P(0) QS_P(1) QS_P(2) QS_P(3) QS_P(4)
+#undef QS_P
+        }
+        QS_IF(ph, 1023u << 5) {
+#define QS_P(P)                                                                                    \
+    if constexpr (RB > kPairB2[P]) {                                                               \
+        QS_IF(ph, 32u << P) phase_case<T, RB, (1u << kPairB1[P]) | (1u << kPairB2[P])>(v, fr, fi); \
+    }
+            QS_P(0) QS_P(1) QS_P(2) QS_P(3) QS_P(4) QS_P(5) QS_P(6) QS_P(7) QS_P(8) QS_P(9)
+#undef QS_P
+        }
+        QS_IF(ph, kPhAll) phase_case<T, RB, 0>(v, fr, fi);
+        QS_IF(ph, kPhAny) phase_case<T, RB, 0, true>(v, fr, fi, rmask);  // uniform branches
+    }
+    QS_IF(code, kcSign) {
+        const uint32_t tmask = code >> 16;
+        const uint32_t s = (tid & tmask) == tmask ? 0x80000000u : 0u;
+        QS_IF(multi, 31u << 15) {
+#define QS_P(B) if constexpr (RB > B) { QS_IF(multi, (1u << 15) << B) sign_case<T, RB, 1u << B>(v, s); }
+            QS_P(0) QS_P(1) QS_P(2) QS_P(3) QS_P(4)
+#undef QS_P
+        }
+        QS_IF(multi, 1023u << 20) {
+#define QS_P(P)                                                                                        \
+    if constexpr (RB > kPairB2[P]) {                                                                   \
+        QS_IF(multi, (1u << 20) << P) sign_case<T, RB, (1u << kPairB1[P]) | (1u << kPairB2[P])>(v, s); \
+    }
+            QS_P(0) QS_P(1) QS_P(2) QS_P(3) QS_P(4) QS_P(5) QS_P(6) QS_P(7) QS_P(8) QS_P(9)
+#undef QS_P
+        }
+    }
+    QS_IF(code, kcRare) {
+        const uint32_t rmask = (multi >> 10) & 31u, tmask = code >> 16;
+        const bool sel = (tid & tmask) == tmask;
+        QS_IF(code, kcDense4) {
+#define QS_D4(P) \
+    if constexpr (RB > kPairB2[P]) { QS_IF(sub, 1u << P) dense4_case<T, RB, kPairB1[P], kPairB2[P]>(v, m4); }
+            QS_D4(0) QS_D4(1) QS_D4(2) QS_D4(3) QS_D4(4) QS_D4(5) QS_D4(6) QS_D4(7) QS_D4(8) QS_D4(9)
 #undef QS_D4
-    case kPhase + 0: phase_case<T, RB, false>(v, op, tid); break;
-    case kPhase + 1: phase_case<T, RB, true>(v, op, tid); break;
-    default: break;
+        }
+        QS_IF(code, kcNotM) {
+#define QS_C(B) if constexpr (RB > B) { QS_IF(sub, 1u << B) notm_case<T, RB, B>(v, rmask, sel); }
+            QS_C(0) QS_C(1) QS_C(2) QS_C(3) QS_C(4)
+#undef QS_C
+        }
+        QS_IF(code, kcOther) {
+            T m[8];
+#pragma unroll
+            for (int k = 0; k < 8; ++k) m[k] = rec->m[k];
+#define QS_O(B)                                                                          \
+    if constexpr (RB > B) {                                                              \
+        QS_IF(sub, 1u << B) dense_case<T, RB, B>(v, m, rmask, sel);                      \
+        QS_IF(sub, 256u << B) diag_case<T, RB, B>(v, m, rmask, sel);                     \
+    }
+            QS_O(0) QS_O(1) QS_O(2) QS_O(3) QS_O(4)
+#undef QS_O
+        }
     }
 }
+
+#undef QS_IF
 
 // XOR of img[b] over the set bits b of x (x < 2^NB).
 template <int NB, typename U>
@@ -340,34 +452,69 @@ __device__ __forceinline__ U span_sum(uint32_t x, const U* img)
     return s;
 }
 
+// Orders the workgroup's LDS accesses (only those: global loads stay in
+// flight).  A one-wave workgroup needs no barrier.
+template <int TB>
+__device__ __forceinline__ void lds_barrier()
+{
+    if constexpr (TB > 6) asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+    else asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+}
+
+// Write the tile in the layout being left, read it in the one entered; lane
+// e < 32 of `pw` holds word e of the FPhase.
 template <typename T, int TB, int RB>
 __device__ __forceinline__ void relayout(typename C2<T>::type (&v)[1 << RB],
-                                         typename C2<T>::type* lds, const FPhase& F, uint32_t tid)
+                                         typename C2<T>::type* lds, uint32_t pw, uint32_t tid)
 {
-    const uint32_t tw = span<TB, uint32_t>(tid, F.wthr);
-    const uint32_t tr = span<TB, uint32_t>(tid, F.rthr);
+    uint32_t tw = 0, tr = 0, wreg[RB], rreg[RB];
 #pragma unroll
-    for (int r = 0; r < (1 << RB); ++r) lds[tw ^ span<RB, uint32_t>((uint32_t)r, F.wreg)] = v[r];
-    __syncthreads();
+    for (int b = 0; b < TB; ++b) {
+        const uint32_t on = 0u - ((tid >> b) & 1u);
+        tw ^= on & lane_get(pw, b);
+        tr ^= on & lane_get(pw, kTBMax + kRBMax + b);
+    }
 #pragma unroll
-    for (int r = 0; r < (1 << RB); ++r) v[r] = lds[tr ^ span<RB, uint32_t>((uint32_t)r, F.rreg)];
-    __syncthreads();
+    for (int b = 0; b < RB; ++b) {
+        wreg[b] = lane_get(pw, kTBMax + b);
+        rreg[b] = lane_get(pw, 2 * kTBMax + kRBMax + b);
+    }
+#pragma unroll
+    for (int r = 0; r < (1 << RB); ++r) lds[tw ^ span<RB, uint32_t>((uint32_t)r, wreg)] = v[r];
+    lds_barrier<TB>();
+#pragma unroll
+    for (int r = 0; r < (1 << RB); ++r) v[r] = lds[tr ^ span<RB, uint32_t>((uint32_t)r, rreg)];
+    lds_barrier<TB>();
 }
 
 // One tile of a planned pass: load, apply every phase's ops with the
 // re-layouts between them, store.  `base` = tile index with zeros at the
 // tile's qubits.
+//
+// What bounds it is the op stream, not the arithmetic (a core on 16 complex128
+// registers is 64 multiply-adds, 256 cycles): read through the scalar cache
+// record by record, each op waited for two dependent loads and took about
+// 2,400 cycles.  So a wave loads up to 64 records of a phase at once, one
+// per lane, a phase ahead of their use, drops those whose outside controls
+// are 0 in this tile with one ballot, and gets each op's few words with
+// v_readlane.
 template <typename T, int TB, int RB>
 __device__ __forceinline__ void process_tile(typename C2<T>::type* __restrict__ amp, const FPass* __restrict__ P,
-                                             const FOp* __restrict__ ops, const T* __restrict__ m4tab,
+                                             const FRec<T>* __restrict__ recs, const T* __restrict__ m4tab,
                                              uint64_t tile, typename C2<T>::type* lds, uint32_t tid,
                                              bool zero_init = false)
 {
     using V = typename C2<T>::type;
     constexpr int E = 1 << RB;
+    // 1024 complex128 threads have 128 registers each: no room for a second set of records
+    constexpr bool kAhead = TB < 10 || sizeof(T) == 4;
+    const uint32_t lane = tid & 63u;
+    const int nph = P->nphases;
+    uint32_t pw = ((const uint32_t*)&P->ph[0])[lane & 31u];
+    uint32_t ob = lane_get(pw, 30), oe = lane_get(pw, 31);
+    OpLanes<T, RB> cur = load_ops<T, RB>(recs, ob, oe, lane);
     const uint64_t ld_t = span_sum<TB, uint64_t>(tid, P->ld_thr);
     const uint64_t st_t = span_sum<TB, uint64_t>(tid, P->st_thr);
-    const int nph = P->nphases;
     const uint64_t base = expand(tile, P->outside);
     V v[E];
     if (zero_init) {  // the tile of |0..0>: nothing to read
@@ -381,16 +528,54 @@ __device__ __forceinline__ void process_tile(typename C2<T>::type* __restrict__ 
 #pragma unroll
         for (int r = 0; r < E; ++r) v[r] = amp[base + ld_t + span_sum<RB, uint64_t>((uint32_t)r, P->ld_reg)];
     }
-    for (int ph = 0; ph < nph; ++ph) {
-        const FPhase& F = P->ph[ph];
-        if (ph > 0) relayout<T, TB, RB>(v, lds, F, tid);
-        for (int o = F.op_begin; o < F.op_end; ++o) {
-            const FOp& op = ops[o];
-            if ((base & op.gmask) != op.gmask) continue;  // same for the whole tile
-            apply_op<T, RB>(v, op, tid, m4tab);
+    const int nlay = nph + P->final_transpose;
+    for (int ph = 0; ph < nlay; ++ph) {
+        // the next phase's words and records, in flight during this one's ops
+        const uint32_t npw = ((const uint32_t*)&P->ph[ph + 1 < nlay ? ph + 1 : ph])[lane & 31u];
+        if (ph > 0) relayout<T, TB, RB>(v, lds, pw, tid);
+        const uint32_t nob = lane_get(npw, 30), noe = lane_get(npw, 31);
+        OpLanes<T, RB> nxt;
+        if constexpr (kAhead) nxt = load_ops<T, RB>(recs, nob, noe, lane);
+        for (uint32_t c = ob;;) {
+            uint64_t act = __ballot(c + lane < oe && (base & cur.gmask) == cur.gmask);
+            // signs on thread and outside bits alone
+            uint64_t lanes = act & __ballot((cur.code & kcLane) != 0);
+            act ^= lanes;
+            if (lanes) {
+                uint32_t s = 0;
+                while (lanes) {
+                    const uint32_t tmask = lane_get(cur.code, __builtin_ctzll(lanes)) >> 16;
+                    lanes &= lanes - 1;
+                    s ^= (tid & tmask) == tmask ? 0x80000000u : 0u;
+                }
+                sign_case<T, RB, 0>(v, s);
+            }
+            // the next 4x4 matrix, one value per lane, loaded ahead
+            uint64_t d4 = act & __ballot((cur.code & kcDense4) != 0);
+            const uint32_t entry = table_entry(cur.f0);
+            T m4 = T(0), m4n = T(0);
+            if (d4) m4n = m4tab[32 * (uint64_t)lane_get(entry, __builtin_ctzll(d4)) + (lane & 31u)];
+            while (act) {
+                const int i = __builtin_ctzll(act);
+                act &= act - 1;
+                const uint32_t code = lane_get(cur.code, i);
+                if (__builtin_expect((code & kcDense4) != 0, 0)) {
+                    m4 = m4n;
+                    d4 &= d4 - 1;
+                    if (d4) m4n = m4tab[32 * (uint64_t)lane_get(entry, __builtin_ctzll(d4)) + (lane & 31u)];
+                }
+                apply_op<T, RB>(v, cur, i, code, m4, recs + c + i, tid);
+            }
+            c += 64;
+            if (c >= oe) break;
+            cur = load_ops<T, RB>(recs, c, oe, lane);
         }
+        pw = npw;
+        ob = nob;
+        oe = noe;
+        if constexpr (kAhead) cur = nxt;
+        else cur = load_ops<T, RB>(recs, ob, oe, lane);
     }
-    if (P->final_transpose) relayout<T, TB, RB>(v, lds, P->fin, tid);
 #pragma unroll
     for (int r = 0; r < E; ++r) amp[base + st_t + span_sum<RB, uint64_t>((uint32_t)r, P->st_reg)] = v[r];
 }
@@ -398,13 +583,13 @@ __device__ __forceinline__ void process_tile(typename C2<T>::type* __restrict__ 
 template <typename T, int TB, int RB>
 __global__ __launch_bounds__(1 << TB) void k_fused(typename C2<T>::type* __restrict__ amp,
                                                    const FPass* __restrict__ P,
-                                                   const FOp* __restrict__ ops, const T* __restrict__ m4tab,
+                                                   const FRec<T>* __restrict__ recs, const T* __restrict__ m4tab,
                                                    uint64_t ntiles)
 {
     using V = typename C2<T>::type;
     __shared__ V lds[1 << (TB + RB)];
     for (uint64_t tile = blockIdx.x; tile < ntiles; tile += gridDim.x)
-        process_tile<T, TB, RB>(amp, P, ops, m4tab, tile, lds, threadIdx.x);
+        process_tile<T, TB, RB>(amp, P, recs, m4tab, tile, lds, threadIdx.x);
 }
 
 // Batched registers.  Every register's circuit is planned into passes; the
@@ -430,7 +615,7 @@ template <typename T, int TB, int RB>
 __global__ __launch_bounds__(1 << TB) void k_batch(const BatchReg* __restrict__ regs,
                                                    const BatchItem* __restrict__ items, int nitems,
                                                    const FPass* __restrict__ passes,
-                                                   const FOp* __restrict__ ops, const T* __restrict__ m4tab,
+                                                   const FRec<T>* __restrict__ recs, const T* __restrict__ m4tab,
                                                    int init)
 {
     using V = typename C2<T>::type;
@@ -442,7 +627,7 @@ __global__ __launch_bounds__(1 << TB) void k_batch(const BatchReg* __restrict__ 
         const FPass* P = passes + R.pass0 + it.pass;
         const bool zi = init && it.pass == 0;
         for (uint32_t tile = it.tile0; tile < it.tile1; ++tile)
-            process_tile<T, TB, RB>((V*)R.amp, P, ops, m4tab, tile, lds, tid, zi);
+            process_tile<T, TB, RB>((V*)R.amp, P, recs, m4tab, tile, lds, tid, zi);
     }
 }
 
@@ -504,6 +689,36 @@ void fill_phase(FPhase& F, const Layout& from, const Layout& to, int K)
     for (size_t b = 0; b < to.reg.size(); ++b) F.rreg[b] = img[to.reg[b]];
 }
 
+using Cx = std::complex<double>;
+
+// Sub-code of a phase or sign on the register bits of rmask.
+int phase_sub(uint32_t rmask)
+{
+    const int n = __builtin_popcount(rmask);
+    if (n == 0) return 0;
+    const int b1 = __builtin_ctz(rmask);
+    if (n == 1) return 1 + b1;
+    return n == 2 ? 6 + pair_of(b1, 31 - __builtin_clz(rmask)) : 16;
+}
+
+// Multiply the amplitudes whose register bits `rmask`, thread bits `tmask`
+// and outside qubits `gmask` are all 1 by f.
+FOp phase_fop(uint32_t rmask, uint32_t tmask, uint64_t gmask, Cx f)
+{
+    FOp o;
+    memset(&o, 0, sizeof(o));
+    const int sub = phase_sub(rmask);
+    // e^(i pi) in double is (-1, 1.2e-16): a sign to within half a unit in the last place
+    const bool sign = f.real() == -1.0 && fabs(f.imag()) < 1.5e-16 && sub < 16;
+    o.kind = (sign ? kSign : kPhase) + sub;
+    o.rmask = rmask;
+    o.tmask = tmask;
+    o.gmask = gmask;
+    o.m[0] = f.real();
+    o.m[1] = f.imag();
+    return o;
+}
+
 FOp encode_op(const OpRec& op, const PassPlan& P, const Layout& L)
 {
     FOp f;
@@ -528,38 +743,19 @@ FOp encode_op(const OpRec& op, const PassPlan& P, const Layout& L)
             }
     };
     for (int q : op.ctrls) classify(q);
-    if (op.kind == 2) {
-        f.kind = kPhase + (f.tmask ? 1 : 0);
-        f.m[0] = cos(op.angle);
-        f.m[1] = sin(op.angle);
-        return f;
-    }
+    if (op.kind == 2) return phase_fop(f.rmask, f.tmask, f.gmask, Cx(cos(op.angle), sin(op.angle)));
     const int jt = local[op.target];
     for (size_t b = 0; b < L.reg.size(); ++b)
         if (L.reg[b] == jt) f.rb = (int)b;
-    const int var = (f.rmask ? 1 : 0) | (f.tmask ? 2 : 0);
-    const bool diag = op.kind == 0 && op.u[2] == 0.0 && op.u[3] == 0.0 && op.u[4] == 0.0 && op.u[5] == 0.0;
-    f.kind = (op.kind == 0 ? (diag ? kDiag : kDense) : kNot) + 4 * f.rb + var;
-    if (op.kind == 0)
-        for (int k = 0; k < 8; ++k) f.m[k] = op.u[k];
+    if (op.kind == 1) {
+        const int nr = __builtin_popcount(f.rmask);
+        f.kind = f.tmask || nr > 1 ? kNotM + f.rb : kNot + 6 * f.rb + (nr ? __builtin_ctz(f.rmask) : 5);
+        return f;
+    }
+    const bool diag = op.u[2] == 0.0 && op.u[3] == 0.0 && op.u[4] == 0.0 && op.u[5] == 0.0;
+    f.kind = (diag ? kDiag : kOther) + f.rb;
+    for (int k = 0; k < 8; ++k) f.m[k] = op.u[k];
     return f;
-}
-
-using Cx = std::complex<double>;
-
-// Multiply the amplitudes whose register bits `rmask`, thread bits `tmask`
-// and outside qubits `gmask` are all 1 by f.
-FOp phase_fop(uint32_t rmask, uint32_t tmask, uint64_t gmask, Cx f)
-{
-    FOp o;
-    memset(&o, 0, sizeof(o));
-    o.kind = kPhase + (tmask ? 1 : 0);
-    o.rmask = rmask;
-    o.tmask = tmask;
-    o.gmask = gmask;
-    o.m[0] = f.real();
-    o.m[1] = f.imag();
-    return o;
 }
 
 // Diagonal factors deferred by the lowering (see lower_passes): the true
@@ -639,7 +835,7 @@ void serialize(const std::vector<PassPlan>& plan, const std::vector<OpRec>& ops,
             const Layout& L = P.phases[ph].lay;
             const Layout& prev = ph ? P.phases[ph - 1].lay : L;
             fill_phase(Fp, prev, L, K);
-            Fp.op_begin = (int)hops.size();
+            Fp.op_begin = (uint32_t)hops.size();
             auto reg_bit = [&](int q) {
                 for (int b = 0; b < RB; ++b)
                     if (L.reg[b] == local[q]) return b;
@@ -683,11 +879,9 @@ void serialize(const std::vector<PassPlan>& plan, const std::vector<OpRec>& ops,
                             for (int c = 0; c < 4; ++c) m[i][c] = t[i][c];
                         std::swap(b1, b2);
                     }
-                    int pair = 0;
-                    while (!(kPairB1[pair] == b1 && kPairB2[pair] == b2)) ++pair;
                     FOp f;
                     memset(&f, 0, sizeof(f));
-                    f.kind = kDense4 + pair;
+                    f.kind = kDense4 + pair_of(b1, b2);
                     f.aux = (uint32_t)(m4.size() / 32);
                     for (int i = 0; i < 4; ++i)
                         for (int c = 0; c < 4; ++c) {
@@ -706,21 +900,31 @@ void serialize(const std::vector<PassPlan>& plan, const std::vector<OpRec>& ops,
                         hops.push_back(f);
                         continue;
                     }
-                    hops.push_back(f);
-                    if (!d.has[t]) continue;
+                    if (!d.has[t]) {
+                        hops.push_back(f);
+                        continue;
+                    }
                     // X exp(i a x_t) = exp(i a) exp(-i a x_t) X where the controls hold
                     const double a = d.phi[t];
                     if (uncond) {
+                        hops.push_back(f);
                         d.gsc *= std::polar(1.0, a);
                         d.gsc_used = true;
                         d.phi[t] = -a;
                     } else if (__builtin_popcount(f.rmask) == 1) {
-                        // exp(i a (x_t xor x_c)) = exp(i a x_t) exp(i a x_c) exp(-2 i a x_t x_c)
+                        // exp(i a (x_t xor x_c)) = exp(i a x_t) exp(i a x_c) exp(-2 i a x_t x_c):
+                        // one op for the NOT and the phase of both bits
                         const int c = P.S[L.reg[__builtin_ctz(f.rmask)]];
                         d.phi[c] += a;
                         d.has[c] = true;
-                        hops.push_back(phase_fop(f.rmask | (1u << b), 0, 0, std::polar(1.0, -2.0 * a)));
+                        const Cx e = std::polar(1.0, -2.0 * a);
+                        f.cx = true;
+                        f.rmask |= 1u << b;
+                        f.m[0] = e.real();
+                        f.m[1] = e.imag();
+                        hops.push_back(f);
                     } else {
+                        hops.push_back(f);
                         hops.push_back(phase_fop(f.rmask, 0, 0, std::polar(1.0, a)));
                         hops.push_back(phase_fop(f.rmask | (1u << b), 0, 0, std::polar(1.0, -2.0 * a)));
                     }
@@ -746,14 +950,14 @@ void serialize(const std::vector<PassPlan>& plan, const std::vector<OpRec>& ops,
                             f.m[2 * (2 * i + c)] = u[i][c].real();
                             f.m[2 * (2 * i + c) + 1] = u[i][c].imag();
                         }
-                    f.kind = kDense + 4 * b;
+                    f.kind = kOther + b;
                     d.phi[t] = 0.0;
                     d.has[t] = false;
                     hops.push_back(f);
                     continue;
                 }
-                static const int kind_of[4] = {kNop, kNot, kCoreA, kCoreB};
-                f.kind = kind_of[cf.form] + (cf.form == 0 ? 0 : 4 * b);
+                const int kind_of[4] = {kNop, kNot + 6 * b + 5, kCoreA + b, kCoreB + b};
+                f.kind = kind_of[cf.form];
                 for (int k = 0; k < 8; ++k) f.m[k] = 0.0;
                 f.m[0] = cf.k.real();
                 f.m[1] = cf.k.imag();
@@ -782,7 +986,10 @@ void serialize(const std::vector<PassPlan>& plan, const std::vector<OpRec>& ops,
                             if (L.reg[b] == j) rb = b;
                         for (int b = 0; b < TB; ++b)
                             if (L.thr[b] == j) tb = b;
-                        hops.push_back(rb >= 0 ? phase_fop(1u << rb, 0, 0, e) : phase_fop(0, 1u << tb, 0, e));
+                        FOp f = rb >= 0 ? phase_fop(1u << rb, 0, 0, e) : phase_fop(0, 1u << tb, 0, e);
+                        const std::vector<int>& nr = P.phases[ph].narrow;
+                        f.lane = rb < 0 || (!nr.empty() && std::find(nr.begin(), nr.end(), j) == nr.end());
+                        hops.push_back(f);
                     }
                     d.phi[q] = 0.0;
                     d.has[q] = false;
@@ -791,12 +998,13 @@ void serialize(const std::vector<PassPlan>& plan, const std::vector<OpRec>& ops,
                 d.gsc = 1.0;
                 d.gsc_used = false;
             }
-            Fp.op_end = (int)hops.size();
+            Fp.op_end = (uint32_t)hops.size();
         }
         const Layout& last = P.phases.back().lay;
         F.final_transpose = (last.reg == P.store.reg && last.thr == P.store.thr) ? 0 : 1;
-        fill_phase(F.fin, last, P.store, K);
-        F.fin.op_begin = F.fin.op_end = 0;
+        FPhase& fin = F.ph[P.phases.size()];
+        fill_phase(fin, last, P.store, K);
+        fin.op_begin = fin.op_end = 0;
         hp.push_back(F);
     }
 }
@@ -812,23 +1020,23 @@ constexpr Shape kShapes64[] = {{6, 3}, {7, 3}, {8, 3}, {8, 4}, {9, 3}, {8, 5}, {
                                {9, 5}, {10, 4}};
 
 template <typename T, int TB, int RB>
-hipError_t launch_cfg(hipStream_t s, void* amp, const FPass* P, const FOp* ops, const void* m4, uint64_t ntiles)
+hipError_t launch_cfg(hipStream_t s, void* amp, const FPass* P, const void* recs, const void* m4, uint64_t ntiles)
 {
     using V = typename C2<T>::type;
     uint64_t grid = ntiles;
     const uint64_t cap = 256ull * 16;
     if (grid > cap) grid = cap;
-    hipLaunchKernelGGL((k_fused<T, TB, RB>), dim3((unsigned)grid), dim3(1 << TB), 0, s, (V*)amp, P, ops,
-                       (const T*)m4, ntiles);
+    hipLaunchKernelGGL((k_fused<T, TB, RB>), dim3((unsigned)grid), dim3(1 << TB), 0, s, (V*)amp, P,
+                       (const FRec<T>*)recs, (const T*)m4, ntiles);
     return hipGetLastError();
 }
 
 template <typename T>
-hipError_t launch_fused_pass(hipStream_t s, const FusedConfig& c, void* amp, const FPass* P, const FOp* ops,
+hipError_t launch_fused_pass(hipStream_t s, const FusedConfig& c, void* amp, const FPass* P, const void* recs,
                              const void* m4, uint64_t ntiles)
 {
 #define QS_SHAPE(tb, rb) \
-    if (c.TB == tb && c.RB == rb) return launch_cfg<T, tb, rb>(s, amp, P, ops, m4, ntiles);
+    if (c.TB == tb && c.RB == rb) return launch_cfg<T, tb, rb>(s, amp, P, recs, m4, ntiles);
     QS_SHAPE(6, 3) QS_SHAPE(7, 3) QS_SHAPE(8, 3) QS_SHAPE(8, 4) QS_SHAPE(9, 3)
     QS_SHAPE(9, 4) QS_SHAPE(10, 3)
     if constexpr (sizeof(T) == 4) {
@@ -865,6 +1073,72 @@ FusedConfig default_fused_config(int prec, int k, int n)
     return c;
 }
 
+// Tile shapes of a batch: 16 registers per thread where the single-register
+// default has 8 (tiles of 10 and 11 qubits).  A batch fills the chip with
+// tiles, so fewer, longer waves per tile cost nothing, each op record then
+// serves twice the amplitudes, and a 10-qubit tile is one wave, which needs no
+// barriers (60 registers of 10..20 qubits: 2.38 -> 2.17 ms in complex64, 3.39
+// -> 2.46 in complex128).
+static FusedConfig batch_config(int prec, int k, int n)
+{
+    FusedConfig c = default_fused_config(prec, k, n);
+    if (c.TB + c.RB == 10 || c.TB + c.RB == 11) {
+        c.TB = c.TB + c.RB - 4;
+        c.RB = 4;
+    }
+    return c;
+}
+
+// The passes of a batched register, planned for the default shape of its tile
+// and then laid out for `c`, whose wider phases hold one or more planned
+// phases each: the order of the ops, and so every rounding, is that of the
+// default shape.
+static std::vector<PassPlan> batch_plan(const std::vector<OpRec>& ops, int n, int prec, const FusedConfig& c)
+{
+    const int K = c.TB + c.RB;
+    const FusedConfig d = default_fused_config(prec, K, K);
+    const int contig = std::min(4, d.TB);
+    std::vector<PassPlan> plan = plan_passes(ops, n, d.TB, d.RB, kPhMax, 1 << 12, contig);
+    if (d.RB == c.RB) return plan;
+    for (PassPlan& P : plan) {
+        std::vector<PhasePlan> wide;
+        for (size_t ph = 0; ph < P.phases.size();) {
+            PhasePlan W = P.phases[ph];
+            std::vector<int> regs = W.lay.reg;
+            auto add = [&](const std::vector<int>& more, bool all) {
+                std::vector<int> u = regs;
+                for (int j : more)
+                    if (std::find(u.begin(), u.end(), j) == u.end() && (!wide.empty() || j >= contig)) {
+                        if (!all && (int)u.size() == c.RB) break;
+                        u.push_back(j);
+                    }
+                for (int j : more)
+                    if (all && std::find(u.begin(), u.end(), j) == u.end()) return false;
+                if ((int)u.size() > c.RB) return false;
+                regs = u;
+                return true;
+            };
+            W.narrow = regs;
+            for (++ph; ph < P.phases.size() && add(P.phases[ph].lay.reg, true); ++ph) {
+                W.ops.insert(W.ops.end(), P.phases[ph].ops.begin(), P.phases[ph].ops.end());
+                W.narrow = P.phases[ph].lay.reg;
+            }
+            // register bits to spare: the next phase's, else the highest
+            if (ph < P.phases.size()) add(P.phases[ph].lay.reg, false);
+            for (int j = K - 1; j >= 0 && (int)regs.size() < c.RB; --j) add({j}, false);
+            std::sort(regs.begin(), regs.end());
+            W.lay.reg = regs;
+            W.lay.thr.clear();
+            for (int j = 0; j < K; ++j)
+                if (std::find(regs.begin(), regs.end(), j) == regs.end()) W.lay.thr.push_back(j);
+            wide.push_back(W);
+        }
+        P.phases = wide;
+        P.store = coalesced(wide.back().lay, contig) ? wide.back().lay : wide.front().lay;
+    }
+    return plan;
+}
+
 // The 4x4 table in the register's precision.
 std::vector<char> m4_bytes(const std::vector<double>& m4, int prec)
 {
@@ -878,6 +1152,140 @@ std::vector<char> m4_bytes(const std::vector<double>& m4, int prec)
     if (out.empty()) out.resize(sizeof(double));
     return out;
 }
+
+namespace {
+
+// Puts FOps of a phase into records, several to one where they can share a
+// dispatch.  A record runs cores (ascending register bits), then a NOT (with
+// its phase) or a phase, then signs.  An op joins the open record only where
+// no rounding moves: NOTs and signs are exact and may change places with ops
+// on other register bits, cores and phases keep their order.  Ops with
+// thread-bit or outside controls, 4x4s and controlled dense gates stand alone.
+// Signs on thread and outside bits alone (sub 0) commute with everything
+// inside a lane and come first.
+template <typename T>
+uint32_t bundle(const FOp* ops, uint32_t count, FRec<T>* out)
+{
+    uint32_t n = 0, core_bits = 0, not_bits = 0, sign_bits = 0;
+    bool open = false, phase = false;
+    auto put = [&](int at, const FOp& f, int count_m) {
+        for (int k = 0; k < count_m; ++k) out[n - 1].m[at + k] = (T)f.m[k];
+    };
+    auto fresh = [&](bool joinable) {
+        memset(&out[n], 0, sizeof(out[n]));
+        ++n;
+        core_bits = not_bits = sign_bits = 0;
+        phase = false;
+        open = joinable;
+    };
+    for (uint32_t k = 0; k < count; ++k) {
+        const FOp& f = ops[k];
+        if (f.kind != kSign) continue;
+        fresh(false);
+        out[n - 1].code = kcLane | f.tmask << 16;
+        out[n - 1].gmask = f.gmask;
+    }
+    open = false;
+    for (uint32_t k = 0; k < count; ++k) {
+        const FOp& f = ops[k];
+        if (f.kind == kSign || f.kind == kNop) continue;
+        const int cls = f.kind & 0xe0, sub = f.kind & 31;
+        const bool plain = f.tmask == 0 && f.gmask == 0;
+        if (plain && (cls == kCoreA || cls == kCoreB)) {
+            const uint32_t bit = 1u << sub;
+            if (!open || phase || core_bits >= bit || ((not_bits | sign_bits) & bit)) fresh(true);
+            FRec<T>& r = out[n - 1];
+            r.code |= kcCore;
+            r.multi |= cls == kCoreA ? bit : bit << 5;
+            put(2 * sub, f, 2);
+            core_bits |= bit;
+        } else if (plain && cls == kNot) {
+            const uint32_t bits = f.rmask | 1u << f.rb;
+            if (!open || not_bits || phase || (sign_bits & bits)) fresh(true);
+            FRec<T>& r = out[n - 1];
+            r.code |= kcNot;
+            r.sub = 1u << sub;
+            not_bits = bits;
+            if (f.cx) {
+                r.code |= kcPhase;
+                r.ph = 1u << (phase_sub(f.rmask) - 1);
+                put(10, f, 2);
+                phase = true;
+            }
+        } else if (plain && cls == kPhase) {
+            if (!open || phase) fresh(true);
+            FRec<T>& r = out[n - 1];
+            r.code |= kcPhase;
+            r.multi |= f.rmask << 10;
+            r.ph = f.lane ? kPhAny : f.rmask ? 1u << (sub - 1) : kPhAll;
+            put(10, f, 2);
+            phase = true;
+        } else if (plain && cls == kSign) {
+            if (!open) fresh(true);
+            FRec<T>& r = out[n - 1];
+            r.code |= kcSign;
+            r.multi ^= (1u << 15) << (sub - 1);  // the same sign twice is none
+            sign_bits |= f.rmask;
+        } else {
+            fresh(false);
+            FRec<T>& r = out[n - 1];
+            r.gmask = f.gmask;
+            r.code = f.tmask << 16;
+            r.multi = f.rmask << 10;
+            r.sub = 1u << sub;
+            switch (cls) {
+            case kNot:
+                r.code |= kcNot;
+                break;
+            case kNotM:
+                r.code |= kcRare | kcNotM;
+                break;
+            case kPhase:
+                r.code |= kcPhase;
+                r.ph = sub ? 1u << (sub - 1) : f.tmask ? kPhAny : kPhAll;
+                put(10, f, 2);
+                break;
+            case kSign:
+                r.code |= kcSign;
+                r.multi |= (1u << 15) << (sub - 1);
+                break;
+            case kDense4:
+                r.code |= kcRare | kcDense4;
+                memcpy(&r.m[10], &f.aux, sizeof(f.aux));
+                break;
+            default:  // (cores have no controls)
+                r.code |= kcRare | kcOther;
+                put(0, f, 8);
+                break;
+            }
+        }
+    }
+    return n;
+}
+
+// Device records of the ops of the passes `hp`, in the ops' slots (fewer
+// records than ops: the rest of a phase's slots stay unused), and one more:
+// a wave reads the record at the begin of an empty range too.  Sets the ends
+// of the phases' ranges.
+template <typename T>
+std::vector<char> rec_bytes_t(std::vector<FPass>& hp, const std::vector<FOp>& hops)
+{
+    std::vector<char> out((hops.size() + 1) * sizeof(FRec<T>), 0);
+    FRec<T>* r = (FRec<T>*)out.data();
+    for (FPass& P : hp)
+        for (int ph = 0; ph < P.nphases; ++ph) {
+            FPhase& F = P.ph[ph];
+            F.op_end = F.op_begin + bundle<T>(hops.data() + F.op_begin, F.op_end - F.op_begin, r + F.op_begin);
+        }
+    return out;
+}
+
+std::vector<char> rec_bytes(std::vector<FPass>& hp, const std::vector<FOp>& hops, int prec)
+{
+    return prec == QS_C128 ? rec_bytes_t<double>(hp, hops) : rec_bytes_t<float>(hp, hops);
+}
+
+}  // namespace
 
 qs_status run_fused_sv(qs_reg r, const std::vector<OpRec>& circuit_ops, FusedConfig cfg, int* passes_out)
 {
@@ -904,14 +1312,13 @@ qs_status run_fused_sv(qs_reg r, const std::vector<OpRec>& circuit_ops, FusedCon
     std::vector<FOp> hops;
     std::vector<double> m4;
     serialize(plan, ops, TB, RB, r->prec, hp, hops, m4);
-    if (hops.empty()) hops.push_back(FOp{});
-    const std::vector<char> m4b = m4_bytes(m4, r->prec);
+    const std::vector<char> m4b = m4_bytes(m4, r->prec), recs = rec_bytes(hp, hops, r->prec);
 
-    const size_t pbytes = hp.size() * sizeof(FPass), obytes = hops.size() * sizeof(FOp);
-    const size_t moff = (pbytes + obytes + 255) & ~(size_t)255;
+    const size_t pbytes = hp.size() * sizeof(FPass), ooff = (pbytes + 15) & ~(size_t)15;
+    const size_t moff = (ooff + recs.size() + 255) & ~(size_t)255;
     std::vector<char> host(moff + m4b.size());
     memcpy(host.data(), hp.data(), pbytes);
-    memcpy(host.data() + pbytes, hops.data(), obytes);
+    memcpy(host.data() + ooff, recs.data(), recs.size());
     memcpy(host.data() + moff, m4b.data(), m4b.size());
     // stream-ordered plan buffer: no device-wide synchronisation, so
     // registers on other streams keep running
@@ -925,7 +1332,7 @@ qs_status run_fused_sv(qs_reg r, const std::vector<OpRec>& circuit_ops, FusedCon
         return hip_error(e, "plan upload");
     }
     const FPass* dP = (const FPass*)dbuf;
-    const FOp* dO = (const FOp*)((char*)dbuf + pbytes);
+    const void* dO = (const char*)dbuf + ooff;
     const void* dM = (const char*)dbuf + moff;
     const uint64_t ntiles = 1ull << (nbits - K);
     qs_status st = QS_OK;
@@ -955,7 +1362,7 @@ hipError_t batch_launch_t(qs_batch_s* b, const qs_batch_s::Launch& L, int init)
     const BatchItem* items = (const BatchItem*)(base + b->off_order);
     hipLaunchKernelGGL((k_batch<T, TB, RB>), dim3(std::min(L.count, L.grid)), dim3(1 << TB), 0, b->stream,
                        (const BatchReg*)(base + b->off_regs), items + L.off, L.count,
-                       (const FPass*)(base + b->off_passes), (const FOp*)(base + b->off_ops),
+                       (const FPass*)(base + b->off_passes), (const FRec<T>*)(base + b->off_ops),
                        (const T*)(base + b->off_m4), init);
     return hipGetLastError();
 }
@@ -967,9 +1374,9 @@ hipError_t batch_launch_p(qs_batch_s* b, int init)
         hipError_t e = hipErrorInvalidValue;
 #define QS_B(tb, rb) \
     if (L.TB == tb && L.RB == rb) e = batch_launch_t<T, tb, rb>(b, L, init);
-        QS_B(6, 3) QS_B(7, 3) QS_B(8, 3) QS_B(8, 4) QS_B(9, 3) QS_B(9, 4) QS_B(10, 3)
+        QS_B(6, 3) QS_B(6, 4) QS_B(7, 4) QS_B(8, 4) QS_B(9, 4)
         if constexpr (sizeof(T) == 4) {
-            QS_B(8, 5) QS_B(9, 5) QS_B(10, 4)
+            QS_B(8, 5) QS_B(9, 5)
         }
 #undef QS_B
         if (e != hipSuccess) return e;
@@ -990,9 +1397,9 @@ int batch_occupancy_p(int TB, int RB)
 {
 #define QS_O(tb, rb) \
     if (TB == tb && RB == rb) return batch_occupancy<T, tb, rb>();
-    QS_O(6, 3) QS_O(7, 3) QS_O(8, 3) QS_O(8, 4) QS_O(9, 3) QS_O(9, 4) QS_O(10, 3)
+    QS_O(6, 3) QS_O(6, 4) QS_O(7, 4) QS_O(8, 4) QS_O(9, 4)
     if constexpr (sizeof(T) == 4) {
-        QS_O(8, 5) QS_O(9, 5) QS_O(10, 4)
+        QS_O(8, 5) QS_O(9, 5)
     }
 #undef QS_O
     return 1;
@@ -1012,7 +1419,7 @@ qs_status batch_build(qs_batch_s* b, const std::vector<qs_reg>& regs,
 {
     int nmin = 64;
     for (qs_reg r : regs) nmin = std::min(nmin, r->n);
-    const FusedConfig cfg = default_fused_config(b->prec, tile_qubits, 64);
+    const FusedConfig cfg = batch_config(b->prec, tile_qubits, 64);
     if (cfg.TB == 0 || nmin < 9)
         return set_error(QS_E_ARG, "batched registers need at least 9 qubits and a tile of 9 or more");
     b->TB = cfg.TB;
@@ -1042,10 +1449,10 @@ qs_status batch_build(qs_batch_s* b, const std::vector<qs_reg>& regs,
             ops = &none;
         }
         // a register narrower than the batch tile is one tile of its own width
-        const FusedConfig rc = regs[i]->n >= cfg.TB + cfg.RB ? cfg : default_fused_config(b->prec, regs[i]->n, regs[i]->n);
+        const FusedConfig rc = regs[i]->n >= cfg.TB + cfg.RB ? cfg : batch_config(b->prec, regs[i]->n, regs[i]->n);
         b->reg_TB[i] = rc.TB;
         b->reg_RB[i] = rc.RB;
-        std::vector<PassPlan> plan = plan_passes(*ops, regs[i]->n, rc.TB, rc.RB, kPhMax, 1 << 12, std::min(4, rc.TB));
+        std::vector<PassPlan> plan = batch_plan(*ops, regs[i]->n, b->prec, rc);
         per_item[i] = 1ull << (regs[i]->n - (rc.TB + rc.RB));  // tile count, for now
         hr[i].amp = regs[i]->amp;
         hr[i].n = regs[i]->n;
@@ -1062,15 +1469,18 @@ qs_status batch_build(qs_batch_s* b, const std::vector<qs_reg>& regs,
         bp->placeholder.push_back(ops == &none);
     }
     // tiles per work item: up to 16, fewer when the batch holds too few
-    // tiles to give the 256 CUs about 8 items each
+    // tiles to give the 256 CUs about 64 items each (60 registers of 10..20
+    // qubits in complex64: 2.17 ms with 8 items per CU, 1.58 with 16, 1.39
+    // with 64 or more)
     uint64_t total_tiles = 0;
     for (uint64_t t : per_item) total_tiles += t;
-    const uint64_t per = std::max<uint64_t>(1, std::min<uint64_t>(16, (total_tiles + 2047) / 2048));
+    const uint64_t per = std::max<uint64_t>(1, std::min<uint64_t>(16, total_tiles / 16384));
     for (uint64_t& t : per_item) t = std::min(t, per);
     if (hp.empty()) hp.push_back(FPass{});
-    if (hops.empty()) hops.push_back(FOp{});
     b->circ_ops.assign(circs.begin(), circs.end());
-    b->host_ops.assign((const char*)hops.data(), (const char*)(hops.data() + hops.size()));
+    b->host_ops = rec_bytes(hp, hops, b->prec);
+    b->reg_pass_begin.assign(regs.size(), 0);
+    for (size_t i = 0; i < regs.size(); ++i) b->reg_pass_begin[i] = hr[i].pass0;
     b->host_m4 = m4;
     const std::vector<char> m4b = m4_bytes(m4, b->prec);
     // items level by level; within a level the largest registers first
@@ -1106,13 +1516,13 @@ qs_status batch_build(qs_batch_s* b, const std::vector<qs_reg>& regs,
     b->off_order = align(hr.size() * sizeof(BatchReg));
     b->off_passes = align(b->off_order + items.size() * sizeof(BatchItem));
     b->off_ops = align(b->off_passes + hp.size() * sizeof(FPass));
-    b->off_m4 = align(b->off_ops + hops.size() * sizeof(FOp));
+    b->off_m4 = align(b->off_ops + b->host_ops.size());
     const size_t total = align(b->off_m4 + m4b.size());
     std::vector<char> host(total, 0);
     memcpy(host.data() + b->off_regs, hr.data(), hr.size() * sizeof(BatchReg));
     memcpy(host.data() + b->off_order, items.data(), items.size() * sizeof(BatchItem));
     memcpy(host.data() + b->off_passes, hp.data(), hp.size() * sizeof(FPass));
-    memcpy(host.data() + b->off_ops, hops.data(), hops.size() * sizeof(FOp));
+    memcpy(host.data() + b->off_ops, b->host_ops.data(), b->host_ops.size());
     memcpy(host.data() + b->off_m4, m4b.data(), m4b.size());
     // stream-ordered allocation and upload: creating a batch does not wait
     // for work on other streams (a plain free or a synchronous copy would)
@@ -1130,9 +1540,11 @@ qs_status batch_build(qs_batch_s* b, const std::vector<qs_reg>& regs,
 qs_status batch_update(qs_batch_s* b)
 {
     // lower every register's plan again with the circuits' current values:
-    // the structure (and so the op count) is unchanged, only the kernel data
-    // (matrices, core coefficients, deferred phases) follows the parameters
-    FOp* ops = (FOp*)b->host_ops.data();
+    // the structure (and so the slots of its ops) is unchanged; the kernel
+    // data (matrices, core coefficients, deferred phases) and the ends of the
+    // phases' op ranges follow the parameters
+    const size_t rsz = b->prec == QS_C128 ? sizeof(FRec<double>) : sizeof(FRec<float>);
+    FPass* passes = (FPass*)(b->host_plan.data() + b->off_passes);
     for (size_t i = 0; i < b->regs.size(); ++i) {
         if (b->plans->placeholder[i]) continue;
         std::vector<FPass> hp;
@@ -1141,11 +1553,14 @@ qs_status batch_update(qs_batch_s* b)
         serialize(b->plans->plans[i], *b->circ_ops[i], b->reg_TB[i], b->reg_RB[i], b->prec, hp, hops, m4);
         if (hops.size() != b->reg_op_count[i] || m4.size() != b->reg_m4_count[i])
             return set_error(QS_E_ARG, "a batched circuit changed its structure");
-        for (size_t k = 0; k < hops.size(); ++k) {
-            FOp f = hops[k];
-            if (f.kind >= kDense4 && f.kind < kDense4 + 10) f.aux += (uint32_t)(b->reg_m4_begin[i] / 32);
-            ops[b->reg_op_begin[i] + k] = f;
-        }
+        for (FOp& f : hops)
+            if ((f.kind & 0xe0) == kDense4) f.aux += (uint32_t)(b->reg_m4_begin[i] / 32);
+        const std::vector<char> recs = rec_bytes(hp, hops, b->prec);
+        memcpy(b->host_ops.data() + b->reg_op_begin[i] * rsz, recs.data(), hops.size() * rsz);
+        for (size_t p = 0; p < hp.size(); ++p)
+            for (int ph = 0; ph < hp[p].nphases; ++ph)
+                passes[b->reg_pass_begin[i] + p].ph[ph].op_end =
+                    (uint32_t)b->reg_op_begin[i] + hp[p].ph[ph].op_end;
         std::copy(m4.begin(), m4.end(), b->host_m4.begin() + b->reg_m4_begin[i]);
     }
     // from pageable memory the copies have left the host tables when the
@@ -1153,6 +1568,9 @@ qs_status batch_update(qs_batch_s* b)
     // later ones
     hipError_t e = hipMemcpyAsync((char*)b->dbuf + b->off_ops, b->host_ops.data(), b->host_ops.size(),
                                   hipMemcpyHostToDevice, b->stream);
+    if (e != hipSuccess) return hip_error(e, "batch parameter upload");
+    e = hipMemcpyAsync((char*)b->dbuf + b->off_passes, passes, (size_t)b->passes_total * sizeof(FPass),
+                       hipMemcpyHostToDevice, b->stream);
     if (e != hipSuccess) return hip_error(e, "batch parameter upload");
     if (!b->host_m4.empty()) {
         b->host_m4b = m4_bytes(b->host_m4, b->prec);

@@ -86,7 +86,7 @@ struct qs_batch_s {
     std::vector<qs_reg> regs;
     std::vector<hipStream_t> reg_streams;  // distinct streams of the registers
     hipEvent_t ev_in, ev_out;
-    void* dbuf = nullptr;          // BatchReg[] + BatchItem[] + FPass[] + FOp[] + 4x4 table
+    void* dbuf = nullptr;          // BatchReg[] + BatchItem[] + FPass[] + op records + 4x4 table
     size_t off_regs, off_order, off_passes, off_ops, off_m4;
     int nitems = 0;
     // launches in order: pass level by pass level, one per tile shape that
@@ -106,7 +106,7 @@ struct qs_batch_s {
     // ops occupy, and host copies of the op table and the 4x4 table
     std::vector<const std::vector<OpRec>*> circ_ops;
     qs::BatchPlans* plans = nullptr;
-    std::vector<size_t> reg_op_begin, reg_op_count, reg_m4_begin, reg_m4_count;
+    std::vector<size_t> reg_op_begin, reg_op_count, reg_m4_begin, reg_m4_count, reg_pass_begin;
     std::vector<char> host_ops;
     std::vector<double> host_m4;
     // host sources of the asynchronous uploads on the batch stream (kept

@@ -21,6 +21,7 @@ struct Layout {
 struct PhasePlan {
     Layout lay;
     std::vector<int> ops;  // indices into the circuit, in application order
+    std::vector<int> narrow;  // if not empty: lay.reg before the phase was laid out wider
 };
 
 struct PassPlan {

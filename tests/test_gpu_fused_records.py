@@ -1,0 +1,124 @@
+"""The generic fused kernel's op records against the oracle: every tile shape,
+every record class, several ops under one dispatch, ranges of more than 64
+records, and batches whose ops change form when their parameters change.
+
+Tolerances: a gate computed with unit round-off e adds at most about 4 e to
+the 2-norm error of a normalised state (8 multiply-adds per component pair,
+two roundings each), so the largest amplitude is off by at most 4 e per op."""
+import math
+
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+EPS = {'C128': 2.0 ** -53, 'C64': 2.0 ** -24}
+SHAPES = [(6, 3), (7, 3), (8, 3), (8, 4), (9, 3), (9, 4), (10, 3)]
+SHAPES64 = SHAPES + [(8, 5), (9, 5), (10, 4)]
+
+
+@pytest.fixture(scope='module')
+def q():
+    import paper_1802_08032_amd as m
+    return m
+
+
+@pytest.fixture(scope='module')
+def env(q):
+    e = q.Env(0)
+    yield e
+    e.close()
+
+
+def mixed_ops(n, seed):
+    """Rotations and CZ ladders (cores, signs), CNOT bricks (NOTs with phases),
+    phases and controlled gates with up to 3 controls, repeated signs, diagonal
+    and anti-diagonal gates."""
+    from workloads import Op, X, layered_circuit, param_circuit, random_gate_ops, rz
+    ops = param_circuit(n, 2, seed) + layered_circuit(n, 2, seed + 1, mcphase=True)
+    ops += random_gate_ops(n, 40, seed + 2)
+    for a in range(n - 3):
+        ops.append(Op('phase', qubits=(a, a + 3), angle=math.pi))
+        ops.append(Op('phase', qubits=(a, a + 3), angle=math.pi if a % 2 else 0.7))
+        ops.append(Op('u', target=a, u=rz(0.3)))
+        ops.append(Op('x', target=a + 1))
+        ops.append(Op('x', target=a, controls=(a + 1, a + 2, a + 3)))
+        ops.append(Op('u', target=a, controls=(a + 2,), u=rz(0.9) @ X))
+        ops.append(Op('u', target=a, controls=(a + 1,), u=rz(1.1)))
+    return ops
+
+
+@pytest.mark.parametrize('extra', [0, 2])
+@pytest.mark.parametrize('prec,shape', [('C128', s) for s in SHAPES] + [('C64', s) for s in SHAPES64])
+def test_records_of_every_shape(q, env, oracle_lib, prec, shape, extra):
+    tb, rb = shape
+    n = tb + rb + extra
+    ops = mixed_ops(n, 31 * n + rb)
+    want = oracle_lib.run_sv(n, ops)
+    reg = q.Register(env, n, q.STATEVEC, getattr(q, prec))
+    reg.init_zero()
+    c = q.Circuit(ops)
+    c.run_tiled(reg, tb + rb, tb)
+    err = float(np.max(np.abs(reg.get_amps() - want)))
+    c.close()
+    reg.close()
+    assert err <= 4 * EPS[prec] * len(ops)
+
+
+@pytest.mark.parametrize('prec', ['C128', 'C64'])
+@pytest.mark.parametrize('count', [63, 64, 65, 129])
+def test_long_ranges_of_records(q, env, oracle_lib, prec, count):
+    """`count` records in one phase: cores on one qubit cannot share a record."""
+    from workloads import Op, haar_unitary
+    rng = np.random.default_rng(count)
+    n = 11
+    ops = [Op('u', target=10, u=haar_unitary(rng)) for _ in range(count)]
+    want = oracle_lib.run_sv(n, ops)
+    reg = q.Register(env, n, q.STATEVEC, getattr(q, prec))
+    reg.init_zero()
+    c = q.Circuit(ops)
+    c.run(reg, 11)
+    err = float(np.max(np.abs(reg.get_amps() - want)))
+    c.close()
+    reg.close()
+    assert err <= 4 * EPS[prec] * count
+
+
+@pytest.mark.parametrize('prec', ['C128', 'C64'])
+@pytest.mark.parametrize('tile', [9, 10, 11, 12, 13])
+def test_batch_shapes_updates_and_probabilities(q, env, oracle_lib, prec, tile):
+    """Registers around the tile width and the probability pieces; an update
+    turns general gates into diagonal and anti-diagonal ones and back."""
+    from workloads import X, haar_unitary, rz
+    rng = np.random.default_rng(tile)
+    sizes = [9, 10, 11, 12, 13, 14, 17]
+    circuits = [mixed_ops(n, 100 * tile + n) for n in sizes]
+    regs = [q.Register(env, n, q.STATEVEC, getattr(q, prec)) for n in sizes]
+    circs = [q.Circuit(o) for o in circuits]
+    b = q.Batch(regs, circs, tile)
+    b.capture(init_zero=True)
+    for forms in (None, 'special', 'general'):
+        if forms:
+            for ops, c in zip(circuits, circs):
+                for k, o in enumerate(ops):
+                    if o.kind == 'u' and not o.controls:
+                        o.u = haar_unitary(rng) if forms == 'general' else (rz(0.4 + k) if k % 2 else rz(0.2 * k) @ X)
+                        c.set_unitary(k, o.u)
+                    elif o.kind == 'phase':
+                        o.angle = 0.1 * k if forms == 'general' else math.pi
+                        c.set_phase(k, o.angle)
+            b.update()
+        b.replay()
+        for qubit in (0, 8):
+            p0, total = b.probs(qubit)
+            for i, (n, ops, reg) in enumerate(zip(sizes, circuits, regs)):
+                amps = reg.get_amps()
+                if qubit == 0:
+                    want = oracle_lib.run_sv(n, ops)
+                    assert float(np.max(np.abs(amps - want))) <= 4 * EPS[prec] * len(ops), (forms, n)
+                # sums of the stored state: compensated, in double
+                assert abs(total[i] - oracle_lib.sv_total_prob(amps, n)) <= 1e-14
+                assert abs(p0[i] - oracle_lib.sv_prob_outcome(amps, n, qubit, 0)) <= 1e-14
+    b.close()
+    for h in circs + regs:
+        h.close()
