@@ -603,8 +603,9 @@ struct BatchReg {
     void* amp;
     int n;
     int npasses;
-    uint32_t pass0;  // first pass of the register in the pass array
-    uint32_t pad;
+    uint32_t pass0;   // first pass of the register in the pass array
+    uint32_t piece0;  // first of its pieces in the probability sums
+    uint32_t logc, pad;
 };
 
 struct BatchItem {
@@ -631,48 +632,93 @@ __global__ __launch_bounds__(1 << TB) void k_batch(const BatchReg* __restrict__ 
     }
 }
 
-// Per-register probabilities: out[2 i] = P(qubit q = 0), out[2 i + 1] =
-// total probability, both as compensated double sums.
+// Per-register probabilities, P(qubit q = 0) and the total, as compensated
+// double sums.  A register is cut into 2^logc pieces of at least 4096
+// amplitudes (BatchReg::logc), one workgroup each; k_batch_probs_final adds
+// a register's pieces in a fixed order.  One workgroup per register left a
+// batch's largest register to a single CU: 60 registers of 10..20 qubits in
+// complex64 took 1,300 us.
+struct ProbItem {
+    uint32_t reg, piece;
+};
+
 template <typename T>
-__global__ __launch_bounds__(256) void k_batch_probs(const BatchReg* __restrict__ regs, int nregs, int q,
-                                                     double* __restrict__ out)
+__global__ __launch_bounds__(256) void k_batch_probs(const BatchReg* __restrict__ regs,
+                                                     const ProbItem* __restrict__ items, int q,
+                                                     double* __restrict__ partials)
 {
     using V = typename C2<T>::type;
+    constexpr int U = 8;
     __shared__ double sh[4][4];
-    for (int i = blockIdx.x; i < nregs; i += gridDim.x) {
-        const BatchReg R = regs[i];
-        const V* amp = (const V*)R.amp;
-        const uint64_t len = 1ull << R.n;
-        NSum s0 = {0.0, 0.0}, st = {0.0, 0.0};
-        for (uint64_t e = threadIdx.x; e < len; e += 256) {
-            const V a = amp[e];
-            const double p = (double)a.x * (double)a.x + (double)a.y * (double)a.y;
+    const ProbItem it = items[blockIdx.x];
+    const BatchReg R = regs[it.reg];
+    const uint64_t len = 1ull << (R.n - R.logc);  // at least 512, the smallest register
+    const uint64_t e0 = (uint64_t)it.piece * len;
+    const V* amp = (const V*)R.amp + e0;
+    NSum s0 = {0.0, 0.0}, st = {0.0, 0.0};
+    for (uint64_t b = 0; b < len; b += 256 * U) {
+        V a[U];
+#pragma unroll
+        for (int j = 0; j < U; ++j) {
+            const uint64_t e = b + 256 * j + threadIdx.x;
+            a[j].x = a[j].y = T(0);
+            if (b + 256 * j < len) a[j] = amp[e];
+        }
+#pragma unroll
+        for (int j = 0; j < U; ++j) {
+            const uint64_t e = e0 + b + 256 * j + threadIdx.x;
+            const double p = (double)a[j].x * (double)a[j].x + (double)a[j].y * (double)a[j].y;
             nadd(s0, ((e >> q) & 1) ? 0.0 : p);
             nadd(st, p);
         }
+    }
 #pragma unroll
-        for (int off = 32; off >= 1; off >>= 1) {
-            s0 = nmerge(s0, NSum{__shfl_xor(s0.s, off, 64), __shfl_xor(s0.c, off, 64)});
-            st = nmerge(st, NSum{__shfl_xor(st.s, off, 64), __shfl_xor(st.c, off, 64)});
+    for (int off = 32; off >= 1; off >>= 1) {
+        s0 = nmerge(s0, NSum{__shfl_xor(s0.s, off, 64), __shfl_xor(s0.c, off, 64)});
+        st = nmerge(st, NSum{__shfl_xor(st.s, off, 64), __shfl_xor(st.c, off, 64)});
+    }
+    const int w = threadIdx.x >> 6;
+    if ((threadIdx.x & 63) == 0) {
+        sh[0][w] = s0.s;
+        sh[1][w] = s0.c;
+        sh[2][w] = st.s;
+        sh[3][w] = st.c;
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        NSum a = {sh[0][0], sh[1][0]}, b = {sh[2][0], sh[3][0]};
+        for (int k = 1; k < 4; ++k) {
+            a = nmerge(a, NSum{sh[0][k], sh[1][k]});
+            b = nmerge(b, NSum{sh[2][k], sh[3][k]});
         }
-        const int w = threadIdx.x >> 6;
-        if ((threadIdx.x & 63) == 0) {
-            sh[0][w] = s0.s;
-            sh[1][w] = s0.c;
-            sh[2][w] = st.s;
-            sh[3][w] = st.c;
-        }
-        __syncthreads();
-        if (threadIdx.x == 0) {
-            NSum a = {sh[0][0], sh[1][0]}, b = {sh[2][0], sh[3][0]};
-            for (int k = 1; k < 4; ++k) {
-                a = nmerge(a, NSum{sh[0][k], sh[1][k]});
-                b = nmerge(b, NSum{sh[2][k], sh[3][k]});
-            }
-            out[2 * i] = a.s + a.c;
-            out[2 * i + 1] = b.s + b.c;
-        }
-        __syncthreads();
+        double* o = partials + 4 * (uint64_t)blockIdx.x;
+        o[0] = a.s;
+        o[1] = a.c;
+        o[2] = b.s;
+        o[3] = b.c;
+    }
+}
+
+// One wave per register; out[2 i] = P(q = 0), out[2 i + 1] = total.
+__global__ __launch_bounds__(64) void k_batch_probs_final(const BatchReg* __restrict__ regs,
+                                                          const double* __restrict__ partials,
+                                                          double* __restrict__ out)
+{
+    const int i = blockIdx.x;
+    const double* p = partials + 4 * (uint64_t)regs[i].piece0;
+    NSum s0 = {0.0, 0.0}, st = {0.0, 0.0};
+    for (uint32_t k = threadIdx.x; k < 1u << regs[i].logc; k += 64) {
+        s0 = nmerge(s0, NSum{p[4 * k], p[4 * k + 1]});
+        st = nmerge(st, NSum{p[4 * k + 2], p[4 * k + 3]});
+    }
+#pragma unroll
+    for (int off = 32; off >= 1; off >>= 1) {
+        s0 = nmerge(s0, NSum{__shfl_xor(s0.s, off, 64), __shfl_xor(s0.c, off, 64)});
+        st = nmerge(st, NSum{__shfl_xor(st.s, off, 64), __shfl_xor(st.c, off, 64)});
+    }
+    if (threadIdx.x == 0) {
+        out[2 * i] = s0.s + s0.c;
+        out[2 * i + 1] = st.s + st.c;
     }
 }
 
@@ -1428,6 +1474,7 @@ qs_status batch_build(qs_batch_s* b, const std::vector<qs_reg>& regs,
     std::vector<FOp> hops;
     std::vector<double> m4;
     std::vector<BatchReg> hr(regs.size());
+    std::vector<ProbItem> pieces;
     int maxpasses = 0;
     b->reg_TB.assign(regs.size(), 0);
     b->reg_RB.assign(regs.size(), 0);
@@ -1459,6 +1506,9 @@ qs_status batch_build(qs_batch_s* b, const std::vector<qs_reg>& regs,
         hr[i].pass0 = (uint32_t)hp.size();
         hr[i].npasses = (int)plan.size();
         hr[i].pad = 0;
+        hr[i].logc = (uint32_t)std::min(12, std::max(0, regs[i]->n - 12));
+        hr[i].piece0 = (uint32_t)pieces.size();
+        for (uint32_t k = 0; k < 1u << hr[i].logc; ++k) pieces.push_back(ProbItem{(uint32_t)i, k});
         maxpasses = std::max(maxpasses, (int)plan.size());
         b->reg_op_begin[i] = hops.size();
         b->reg_m4_begin[i] = m4.size();
@@ -1517,8 +1567,12 @@ qs_status batch_build(qs_batch_s* b, const std::vector<qs_reg>& regs,
     b->off_passes = align(b->off_order + items.size() * sizeof(BatchItem));
     b->off_ops = align(b->off_passes + hp.size() * sizeof(FPass));
     b->off_m4 = align(b->off_ops + b->host_ops.size());
-    const size_t total = align(b->off_m4 + m4b.size());
+    b->off_pieces = align(b->off_m4 + m4b.size());
+    b->npieces = (int)pieces.size();
+    const size_t total = align(b->off_pieces + pieces.size() * sizeof(ProbItem));
+    b->off_partials = total;  // written by the device only
     std::vector<char> host(total, 0);
+    memcpy(host.data() + b->off_pieces, pieces.data(), pieces.size() * sizeof(ProbItem));
     memcpy(host.data() + b->off_regs, hr.data(), hr.size() * sizeof(BatchReg));
     memcpy(host.data() + b->off_order, items.data(), items.size() * sizeof(BatchItem));
     memcpy(host.data() + b->off_passes, hp.data(), hp.size() * sizeof(FPass));
@@ -1527,7 +1581,7 @@ qs_status batch_build(qs_batch_s* b, const std::vector<qs_reg>& regs,
     // stream-ordered allocation and upload: creating a batch does not wait
     // for work on other streams (a plain free or a synchronous copy would)
     b->host_plan = std::move(host);
-    hipError_t e = hipMallocAsync(&b->dbuf, total, b->stream);
+    hipError_t e = hipMallocAsync(&b->dbuf, total + pieces.size() * 4 * sizeof(double), b->stream);
     if (e != hipSuccess) return hip_error(e, "batch plan buffer");
     e = hipMemcpyAsync(b->dbuf, b->host_plan.data(), total, hipMemcpyHostToDevice, b->stream);
     if (e != hipSuccess) return hip_error(e, "batch plan upload");
@@ -1588,12 +1642,15 @@ hipError_t batch_launch(qs_batch_s* b, int init)
 
 hipError_t batch_probs_launch(qs_batch_s* b, int q, double* dev_out)
 {
-    const BatchReg* regs = (const BatchReg*)((const char*)b->dbuf + b->off_regs);
-    const int grid = std::min(b->count, 2048);
+    char* base = (char*)b->dbuf;
+    const BatchReg* regs = (const BatchReg*)(base + b->off_regs);
+    const ProbItem* items = (const ProbItem*)(base + b->off_pieces);
+    double* partials = (double*)(base + b->off_partials);
     if (b->prec == QS_C128)
-        hipLaunchKernelGGL(k_batch_probs<double>, dim3(grid), dim3(256), 0, b->stream, regs, b->count, q, dev_out);
+        hipLaunchKernelGGL(k_batch_probs<double>, dim3(b->npieces), dim3(256), 0, b->stream, regs, items, q, partials);
     else
-        hipLaunchKernelGGL(k_batch_probs<float>, dim3(grid), dim3(256), 0, b->stream, regs, b->count, q, dev_out);
+        hipLaunchKernelGGL(k_batch_probs<float>, dim3(b->npieces), dim3(256), 0, b->stream, regs, items, q, partials);
+    hipLaunchKernelGGL(k_batch_probs_final, dim3(b->count), dim3(64), 0, b->stream, regs, partials, dev_out);
     return hipGetLastError();
 }
 

@@ -86,9 +86,10 @@ struct qs_batch_s {
     std::vector<qs_reg> regs;
     std::vector<hipStream_t> reg_streams;  // distinct streams of the registers
     hipEvent_t ev_in, ev_out;
-    void* dbuf = nullptr;          // BatchReg[] + BatchItem[] + FPass[] + op records + 4x4 table
-    size_t off_regs, off_order, off_passes, off_ops, off_m4;
-    int nitems = 0;
+    // BatchReg[] + BatchItem[] + FPass[] + op records + 4x4 table + ProbItem[] + probability partials
+    void* dbuf = nullptr;
+    size_t off_regs, off_order, off_passes, off_ops, off_m4, off_pieces, off_partials;
+    int nitems = 0, npieces = 0;
     // launches in order: pass level by pass level, one per tile shape that
     // has items at that level (registers narrower than the batch tile are
     // one tile of their own width)
