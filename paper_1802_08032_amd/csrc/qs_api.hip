@@ -1165,7 +1165,7 @@ qs_status qs_circuit_run(qs_reg r, qs_circuit c, int fusion_qubits, int* n_passe
     if (s) return s;
     if (fusion_qubits < 0) return qs::set_error(QS_E_ARG, "negative fusion width");
     if (fusion_qubits > 0 && r->kind == QS_STATEVEC)
-        return qs::run_fused_sv(r, c->ops, qs::default_fused_config(r->prec, fusion_qubits, r->n), n_passes);
+        return qs::run_fused_sv(r, c, qs::default_fused_config(r->prec, fusion_qubits, r->n), n_passes);
     if (fusion_qubits > 0 && r->kind == QS_DENSITY) {
         // density matrices fuse through the compiled passes on their 2N-qubit vector
         qs::FusedConfig cfg = qs::default_fused_config(r->prec, fusion_qubits, r->nbits);
@@ -1187,7 +1187,7 @@ qs_status qs_circuit_run_tiled(qs_reg r, qs_circuit c, int tile_qubits, int thre
         return qs::set_error(QS_E_ARG, "unsupported tile shape");
     if (tile_qubits > r->nbits) return qs::set_error(QS_E_ARG, "tile wider than the register");
     if (max_phases < 0) return qs::set_error(QS_E_ARG, "negative phase cap");
-    return qs::run_fused_sv(r, c->ops, qs::FusedConfig{thread_bits, RB, max_phases}, n_passes);
+    return qs::run_fused_sv(r, c, qs::FusedConfig{thread_bits, RB, max_phases}, n_passes);
 }
 
 // Shapes the run-time compiled passes accept: 6..10 thread bits, 1..5

@@ -1333,56 +1333,92 @@ std::vector<char> rec_bytes(std::vector<FPass>& hp, const std::vector<FOp>& hops
 
 }  // namespace
 
-qs_status run_fused_sv(qs_reg r, const std::vector<OpRec>& circuit_ops, FusedConfig cfg, int* passes_out)
+// The passes of one circuit for one register shape and tile, as uploaded.
+struct FusedPlan {
+    int nbits, kind, prec, TB, RB, max_phases;
+    size_t nops;
+    uint64_t version;
+    size_t npasses, off_recs, off_m4;
+    std::vector<char> host;  // FPass[], op records, 4x4 table
+};
+
+namespace {
+
+// The circuit's plan for this register and tile: the one it keeps, or a new
+// one, which it keeps from then on.  Planning takes 0.3 ms or more for a few
+// hundred ops, ten times what their kernels take on a small register.
+std::shared_ptr<const FusedPlan> fused_plan(qs_reg r, qs_circuit_s* c, const FusedConfig& cfg)
+{
+    std::lock_guard<std::mutex> g(c->fused_mu);
+    const FusedPlan* k = c->fused.get();
+    if (k && k->nbits == r->nbits && k->kind == r->kind && k->prec == r->prec && k->TB == cfg.TB && k->RB == cfg.RB &&
+        k->max_phases == cfg.max_phases && k->nops == c->ops.size() && k->version == c->version)
+        return c->fused;
+    // a density matrix runs as its 2N-qubit vector (Eq. 2): gates on q and
+    // conj on q + N, channels as 4x4 superoperators on (q, q + N)
+    std::vector<OpRec> dm_ops;
+    if (r->kind == QS_DENSITY) dm_ops = dm_vector_ops(c->ops, r->n);
+    const std::vector<OpRec>& ops = r->kind == QS_DENSITY ? dm_ops : c->ops;
+    const std::vector<PassPlan> plan =
+        plan_passes(ops, r->nbits, cfg.TB, cfg.RB, cfg.max_phases, 1 << 12, std::min(4, cfg.TB));
+    std::vector<FPass> hp;
+    std::vector<FOp> hops;
+    std::vector<double> m4;
+    serialize(plan, ops, cfg.TB, cfg.RB, r->prec, hp, hops, m4);
+    const std::vector<char> m4b = m4_bytes(m4, r->prec), recs = rec_bytes(hp, hops, r->prec);
+    std::shared_ptr<FusedPlan> p = std::make_shared<FusedPlan>();
+    p->nbits = r->nbits;
+    p->kind = r->kind;
+    p->prec = r->prec;
+    p->TB = cfg.TB;
+    p->RB = cfg.RB;
+    p->max_phases = cfg.max_phases;
+    p->nops = c->ops.size();
+    p->version = c->version;
+    p->npasses = hp.size();
+    const size_t pbytes = hp.size() * sizeof(FPass);
+    p->off_recs = (pbytes + 15) & ~(size_t)15;
+    p->off_m4 = (p->off_recs + recs.size() + 255) & ~(size_t)255;
+    p->host.resize(p->off_m4 + m4b.size());
+    memcpy(p->host.data(), hp.data(), pbytes);
+    memcpy(p->host.data() + p->off_recs, recs.data(), recs.size());
+    memcpy(p->host.data() + p->off_m4, m4b.data(), m4b.size());
+    c->fused = p;
+    return p;
+}
+
+}  // namespace
+
+qs_status run_fused_sv(qs_reg r, qs_circuit_s* c, FusedConfig cfg, int* passes_out)
 {
     if (cfg.max_phases <= 0 || cfg.max_phases > kPhMax) cfg.max_phases = kPhMax;
     const int nbits = r->nbits;
     if (cfg.TB == 0 || cfg.TB + cfg.RB > nbits) {  // too small to tile: one kernel per op
-        for (const OpRec& op : circuit_ops) {
+        for (const OpRec& op : c->ops) {
             qs_status s = apply_op(r, op);
             if (s) return s;
         }
-        if (passes_out) *passes_out = (int)circuit_ops.size();
+        if (passes_out) *passes_out = (int)c->ops.size();
         return QS_OK;
     }
-    // a density matrix runs as its 2N-qubit vector (Eq. 2): gates on q and
-    // conj on q + N, channels as 4x4 superoperators on (q, q + N)
-    std::vector<OpRec> dm_ops;
-    if (r->kind == QS_DENSITY) dm_ops = dm_vector_ops(circuit_ops, r->n);
-    const std::vector<OpRec>& ops = r->kind == QS_DENSITY ? dm_ops : circuit_ops;
-    const int TB = cfg.TB, RB = cfg.RB, K = TB + RB;
-    std::vector<PassPlan> plan = plan_passes(ops, nbits, TB, RB, cfg.max_phases, 1 << 12, std::min(4, TB));
-
-    // serialise passes + ops
-    std::vector<FPass> hp;
-    std::vector<FOp> hops;
-    std::vector<double> m4;
-    serialize(plan, ops, TB, RB, r->prec, hp, hops, m4);
-    const std::vector<char> m4b = m4_bytes(m4, r->prec), recs = rec_bytes(hp, hops, r->prec);
-
-    const size_t pbytes = hp.size() * sizeof(FPass), ooff = (pbytes + 15) & ~(size_t)15;
-    const size_t moff = (ooff + recs.size() + 255) & ~(size_t)255;
-    std::vector<char> host(moff + m4b.size());
-    memcpy(host.data(), hp.data(), pbytes);
-    memcpy(host.data() + ooff, recs.data(), recs.size());
-    memcpy(host.data() + moff, m4b.data(), m4b.size());
+    const std::shared_ptr<const FusedPlan> plan = fused_plan(r, c, cfg);
     // stream-ordered plan buffer: no device-wide synchronisation, so
     // registers on other streams keep running
     void* dbuf = nullptr;
-    hipError_t e = hipMallocAsync(&dbuf, host.size(), r->stream);
+    hipError_t e = hipMallocAsync(&dbuf, plan->host.size(), r->stream);
     if (e != hipSuccess) return hip_error(e, "plan buffer");
-    // from pageable memory the copy has left `host` when the call returns
-    e = hipMemcpyAsync(dbuf, host.data(), host.size(), hipMemcpyHostToDevice, r->stream);
+    // from pageable memory the copy has left the plan when the call returns
+    e = hipMemcpyAsync(dbuf, plan->host.data(), plan->host.size(), hipMemcpyHostToDevice, r->stream);
     if (e != hipSuccess) {
         (void)hipFreeAsync(dbuf, r->stream);
         return hip_error(e, "plan upload");
     }
     const FPass* dP = (const FPass*)dbuf;
-    const void* dO = (const char*)dbuf + ooff;
-    const void* dM = (const char*)dbuf + moff;
-    const uint64_t ntiles = 1ull << (nbits - K);
+    const void* dO = (const char*)dbuf + plan->off_recs;
+    const void* dM = (const char*)dbuf + plan->off_m4;
+    const uint64_t ntiles = 1ull << (nbits - cfg.TB - cfg.RB);
     qs_status st = QS_OK;
-    for (size_t p = 0; p < hp.size() && st == QS_OK; ++p) {
+    for (size_t p = 0; p < plan->npasses && st == QS_OK; ++p) {
         st = profiled(r, QS_K_FUSED, [&](int*) {
             return r->prec == QS_C128 ? launch_fused_pass<double>(r->stream, cfg, r->amp, dP + p, dO, dM, ntiles)
                                       : launch_fused_pass<float>(r->stream, cfg, r->amp, dP + p, dO, dM, ntiles);
@@ -1392,7 +1428,7 @@ qs_status run_fused_sv(qs_reg r, const std::vector<OpRec>& circuit_ops, FusedCon
     e = hipFreeAsync(dbuf, r->stream);
     if (st) return st;
     if (e != hipSuccess) return hip_error(e, "plan free");
-    if (passes_out) *passes_out = (int)hp.size();
+    if (passes_out) *passes_out = (int)plan->npasses;
     return QS_OK;
 }
 

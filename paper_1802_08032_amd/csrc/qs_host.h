@@ -4,6 +4,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <memory>
 #include <mutex>
 #include <string>
 #include <vector>
@@ -64,6 +65,7 @@ struct JitPlan;
 void jit_plan_free(JitPlan* p);
 struct BatchPlans;
 void batch_plans_free(BatchPlans* p);
+struct FusedPlan;
 }  // namespace qs
 
 struct qs_circuit_s {
@@ -71,6 +73,10 @@ struct qs_circuit_s {
     std::vector<OpRec> ops;
     uint64_t version = 0;  // bumped by every parameter change (qs_circuit_set_*)
     qs::JitPlan* jit = nullptr;  // cached run-time compiled form (qs_jit.hip)
+    // the generic fused kernel's passes for the register shape and tile last
+    // run (host copy; qs_fused.hip); never changed once it is here
+    std::mutex fused_mu;
+    std::shared_ptr<const qs::FusedPlan> fused;
 };
 
 // A batch of registers run together by one persistent launch (qs_fused.hip).
@@ -152,7 +158,7 @@ struct FusedConfig {
 };
 bool fused_shape_supported(int prec, int TB, int RB);
 FusedConfig default_fused_config(int prec, int k, int n);
-qs_status run_fused_sv(qs_reg r, const std::vector<OpRec>& ops, FusedConfig cfg, int* passes);
+qs_status run_fused_sv(qs_reg r, qs_circuit_s* c, FusedConfig cfg, int* passes);
 // Batched registers (qs_fused.hip).
 qs_status batch_build(qs_batch_s* b, const std::vector<qs_reg>& regs,
                       const std::vector<const std::vector<OpRec>*>& circs, int K);

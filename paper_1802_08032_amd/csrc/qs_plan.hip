@@ -28,6 +28,43 @@ uint64_t qubit_mask(const OpRec& op)
     return m;
 }
 
+namespace {
+
+// The ops with their qubit and target masks, formed once per plan: the
+// planner's inner loops look at nothing else.
+struct Ops {
+    const std::vector<OpRec>& v;
+    std::vector<uint64_t> q, t;
+    uint64_t all_q = 0;
+    explicit Ops(const std::vector<OpRec>& ops) : v(ops)
+    {
+        for (const OpRec& op : ops) {
+            q.push_back(qubit_mask(op));
+            t.push_back(target_mask(op));
+            all_q |= q.back();
+        }
+    }
+    size_t size() const { return v.size(); }
+    const OpRec& operator[](size_t i) const { return v[i]; }
+};
+
+// Passes planned so far: the partitions of one plan often start alike.
+struct Planned {
+    std::vector<int> S, ops;  // as given to plan_phases
+    PassPlan pass;
+};
+
+// Every RB-subset of K bits, descending.
+std::vector<uint32_t> subsets(int K, int RB)
+{
+    std::vector<uint32_t> sets;
+    for (uint32_t s = (1u << K) - 1; s; --s)
+        if (__builtin_popcount(s) == RB) sets.push_back(s);
+    return sets;
+}
+
+}  // namespace
+
 // A layout is coalesced when its first `contig` thread bits carry local
 // qubits 0..contig-1 (= global qubits 0..contig-1): consecutive lanes then
 // touch consecutive amplitudes in HBM.
@@ -73,9 +110,10 @@ std::vector<int> pick_regs(int TB, int RB, const std::vector<int>& pref, bool co
 // Assign the pass's ops to register layouts in dependency order.  Returns
 // false if more than kPhMax phases would be needed; then `keep` receives how
 // many of the pass ops (a dependency-closed prefix set) fit.
-void plan_phases(PassPlan& P, const std::vector<OpRec>& all, int TB, int RB, int max_phases, int contig)
+void plan_phases(PassPlan& P, const Ops& all, int TB, int RB, int max_phases, int contig)
 {
     const int K = TB + RB;
+    const std::vector<uint32_t> sets = subsets(K, RB);
     std::vector<int> local(64, -1);
     for (int j = 0; j < K; ++j) local[P.S[j]] = j;
     auto ltargets = [&](const OpRec& op) -> uint32_t {
@@ -110,17 +148,26 @@ void plan_phases(PassPlan& P, const std::vector<OpRec>& all, int TB, int RB, int
         for (int idx : ops_left) push_targets(all[idx]);
         return pref;
     };
-    // number of remaining ops a phase with register qubits `regm` admits
-    auto admitted = [&](uint32_t regm) {
+    // local target and qubit masks of the remaining ops, less those of no
+    // tile qubit (phases outside the tile), which every phase admits
+    struct LocalMask {
+        uint32_t t, m;
+    };
+    std::vector<LocalMask> masks;
+    int nfree = 0;
+    // number of remaining ops a phase with register qubits `regm` admits;
+    // stops early (with a count of at most `atleast`) once it cannot exceed it
+    auto admitted = [&](uint32_t regm, int atleast) {
         uint32_t blocked = 0;
-        int count = 0;
-        for (int idx : rem) {
-            const OpRec& op = all[idx];
-            const uint32_t m = lmask(op);
-            if (!(m & blocked) && (ltargets(op) & ~regm) == 0) {
+        int count = nfree;
+        const uint32_t tile = (1u << K) - 1;
+        for (size_t i = 0; i < masks.size(); ++i) {
+            const LocalMask& k = masks[i];
+            if (!(k.m & blocked) && (k.t & ~regm) == 0) {
                 ++count;
             } else {
-                blocked |= m;
+                blocked |= k.m;
+                if (blocked == tile || count + (int)(masks.size() - 1 - i) <= atleast) break;
             }
         }
         return count;
@@ -128,17 +175,24 @@ void plan_phases(PassPlan& P, const std::vector<OpRec>& all, int TB, int RB, int
     bool first = true;
     while (!rem.empty()) {
         if ((int)P.phases.size() == max_phases) break;
+        masks.clear();
+        nfree = 0;
+        for (int idx : rem) {
+            const LocalMask k = {ltargets(all[idx]), lmask(all[idx])};
+            if (k.m) masks.push_back(k);
+            else ++nfree;
+        }
         PhasePlan ph;
         // the preferred register set, unless another RB-subset of the tile
         // qubits admits more ops (fewer phases, fewer re-layouts)
         std::vector<int> regs = pick_regs(TB, RB, preferred(rem), first, contig);
         uint32_t best = 0;
         for (int j : regs) best |= 1u << j;
-        int best_n = admitted(best);
+        int best_n = admitted(best, -1);
         const uint32_t allowed = ((1u << K) - 1) & ~(first ? (1u << contig) - 1 : 0u);
-        for (uint32_t s = allowed; s; s = (s - 1) & allowed) {
-            if (__builtin_popcount(s) != RB) continue;
-            const int c = admitted(s);
+        for (uint32_t s : sets) {
+            if (s & ~allowed) continue;
+            const int c = admitted(s, best_n);
             if (c > best_n) {
                 best_n = c;
                 best = s;
@@ -150,8 +204,8 @@ void plan_phases(PassPlan& P, const std::vector<OpRec>& all, int TB, int RB, int
         const uint32_t low = (1u << contig) - 1;
         if (best_n == (int)rem.size() && (best & low)) {
             const uint32_t hi = allowed & ~low;
-            for (uint32_t s = hi; s; s = (s - 1) & hi)
-                if (__builtin_popcount(s) == RB && admitted(s) == best_n) {
+            for (uint32_t s : sets)
+                if (!(s & ~hi) && admitted(s, best_n - 1) == best_n) {
                     best = s;
                     break;
                 }
@@ -188,20 +242,20 @@ void plan_phases(PassPlan& P, const std::vector<OpRec>& all, int TB, int RB, int
 // One pass's ops: walk the remaining ops in order and take an op when no
 // earlier untaken op shares a qubit with it and its targets lie in S.  With
 // `grow`, S may take in new target qubits up to K of them.
-std::vector<int> scan_pass(const std::vector<OpRec>& all, const std::vector<char>& done, size_t first,
+std::vector<int> scan_pass(const Ops& all, const std::vector<char>& done, size_t first,
                            uint64_t& S, int& ssize, int K, int max_ops, bool grow)
 {
     uint64_t blocked = 0;
     std::vector<int> take;
     for (size_t i = first; i < all.size() && (int)take.size() < max_ops; ++i) {
         if (done[i]) continue;
-        const OpRec& op = all[i];
-        const uint64_t m = qubit_mask(op);
+        const uint64_t m = all.q[i];
         if (m & blocked) {
             blocked |= m;
+            if (blocked == all.all_q) break;
             continue;
         }
-        const uint64_t need = target_mask(op) & ~S;
+        const uint64_t need = all.t[i] & ~S;
         const int extra = __builtin_popcountll(need);
         if (extra == 0 || (grow && ssize + extra <= K)) {
             S |= need;
@@ -222,8 +276,9 @@ std::vector<int> scan_pass(const std::vector<OpRec>& all, const std::vector<char
 // candidate that
 // admits the most ops wins (the greedy one on ties).  Runs suit circuits
 // with nearest-neighbour two-qubit gates, whose light cones are intervals.
-std::vector<PassPlan> partition(const std::vector<OpRec>& all, int n, int TB, int RB, int max_phases,
-                                int max_ops, int contig, int windows, bool lookahead)
+std::vector<PassPlan> partition(const Ops& all, int n, int TB, int RB, int max_phases,
+                                int max_ops, int contig, int windows, bool lookahead,
+                                std::vector<Planned>& planned)
 {
     const int K = TB + RB;
     std::vector<PassPlan> passes;
@@ -294,7 +349,14 @@ std::vector<PassPlan> partition(const std::vector<OpRec>& all, int n, int TB, in
         for (int q = 0; q < n; ++q)
             if ((S >> q) & 1) P.S.push_back(q);
         P.ops = take;
-        plan_phases(P, all, TB, RB, max_phases, contig);
+        size_t known = 0;
+        while (known < planned.size() && (planned[known].ops != take || planned[known].S != P.S)) ++known;
+        if (known < planned.size()) {
+            P = planned[known].pass;
+        } else {
+            plan_phases(P, all, TB, RB, max_phases, contig);
+            planned.push_back(Planned{P.S, take, P});
+        }
         for (int idx : P.ops) {
             done[idx] = 1;
             ++ndone;
@@ -313,7 +375,7 @@ double op_cost(const OpRec& op, int nregctrl);
 // region the pass does not need).  Partial partitions that applied the same
 // ops are merged (Zobrist hash of the set).  Returns an empty plan if a
 // pass's ops need more register layouts than allowed.
-std::vector<PassPlan> partition_beam(const std::vector<OpRec>& all, int n, int TB, int RB, int max_phases,
+std::vector<PassPlan> partition_beam(const Ops& all, int n, int TB, int RB, int max_phases,
                                      int max_ops, int contig, int width)
 {
     const int K = TB + RB;
@@ -413,7 +475,7 @@ std::vector<PassPlan> partition_beam(const std::vector<OpRec>& all, int n, int T
 // between register layouts (about two dense gates' worth of time where the
 // pass is bound by its arithmetic).
 constexpr double kRelayoutCost = 8.0;
-double pass_cost(const PassPlan& P, const std::vector<OpRec>& all)
+double pass_cost(const PassPlan& P, const Ops& all)
 {
     uint64_t inS = 0;
     for (int q : P.S) inS |= 1ull << q;
@@ -428,7 +490,7 @@ double pass_cost(const PassPlan& P, const std::vector<OpRec>& all)
     return c + kRelayoutCost * (P.phases.empty() ? 0 : P.phases.size() - 1);
 }
 
-bool replan(PassPlan& P, const std::vector<OpRec>& all, int TB, int RB, int max_phases, int contig)
+bool replan(PassPlan& P, const Ops& all, int TB, int RB, int max_phases, int contig)
 {
     const size_t want = P.ops.size();
     std::sort(P.ops.begin(), P.ops.end());
@@ -447,7 +509,7 @@ bool replan(PassPlan& P, const std::vector<OpRec>& all, int TB, int RB, int max_
 // with it lies between (so for any two ops sharing a qubit the earlier one
 // still runs in the same or an earlier pass, and within a pass ops run in
 // circuit order).
-void rebalance(std::vector<PassPlan>& passes, const std::vector<OpRec>& all, int TB, int RB, int max_phases,
+void rebalance(std::vector<PassPlan>& passes, const Ops& all, int TB, int RB, int max_phases,
                int contig, double hbm)
 {
     if (hbm <= 0.0 || passes.size() < 2) return;
@@ -535,12 +597,14 @@ void rebalance(std::vector<PassPlan>& passes, const std::vector<OpRec>& all, int
 // the next pass could then admit; it is kept only if it needs fewer passes.
 // That costs about as many scans as the candidates squared per pass (tens
 // of milliseconds for a few hundred ops), worth it where a plan is reused.
-std::vector<PassPlan> plan_passes(const std::vector<OpRec>& all, int n, int TB, int RB, int max_phases,
+std::vector<PassPlan> plan_passes(const std::vector<OpRec>& ops, int n, int TB, int RB, int max_phases,
                                   int max_ops, int contig, bool lookahead, double balance)
 {
+    const Ops all(ops);
+    std::vector<Planned> planned;
     std::vector<std::vector<PassPlan>> cands;
-    for (int mode = 0; mode <= 2; ++mode) cands.push_back(partition(all, n, TB, RB, max_phases, max_ops, contig, mode, false));
-    if (lookahead) cands.push_back(partition(all, n, TB, RB, max_phases, max_ops, contig, 2, true));
+    for (int mode = 0; mode <= 2; ++mode) cands.push_back(partition(all, n, TB, RB, max_phases, max_ops, contig, mode, false, planned));
+    if (lookahead) cands.push_back(partition(all, n, TB, RB, max_phases, max_ops, contig, 2, true, planned));
     if (lookahead && balance > 0.0 && all.size() <= 1500) {
         // a wider search for fewer passes (compiled plans are reused; the
         // search costs about a millisecond per op)
@@ -558,7 +622,7 @@ std::vector<PassPlan> plan_passes(const std::vector<OpRec>& all, int n, int TB, 
         if (heaviest > 1.25 * balance)
             for (double f : {1.25, 1.4, 1.5, 1.6, 1.75, 2.0}) {
                 const int cap = (int)ceil(f * avg);
-                if (cap < max_ops) cands.push_back(partition(all, n, TB, RB, max_phases, cap, contig, 2, true));
+                if (cap < max_ops) cands.push_back(partition(all, n, TB, RB, max_phases, cap, contig, 2, true, planned));
             }
     }
     if (balance <= 0.0) {

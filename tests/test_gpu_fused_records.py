@@ -122,3 +122,32 @@ def test_batch_shapes_updates_and_probabilities(q, env, oracle_lib, prec, tile):
     b.close()
     for h in circs + regs:
         h.close()
+
+
+def test_kept_plan_follows_the_circuit(q, env, oracle_lib):
+    """One circuit run on registers of several shapes, with new parameters and
+    with ops added: each run sees the circuit and the register as they are."""
+    from workloads import Op, haar_unitary, noisy_circuit
+    rng = np.random.default_rng(3)
+    ops = [o for o in mixed_ops(8, 5) if o.kind in ('u', 'x', 'phase')]
+    c = q.Circuit(ops)
+
+    def check(n, prec, dm=False, fusion=9):
+        want = oracle_lib.run_dm(n, ops) if dm else oracle_lib.run_sv(n, ops)
+        reg = q.Register(env, n, q.DENSITY if dm else q.STATEVEC, getattr(q, prec))
+        reg.init_zero()
+        c.run_tiled(reg, fusion, 6 if fusion == 9 else 7)
+        err = float(np.max(np.abs(reg.get_amps() - want)))
+        reg.close()
+        assert err <= 8 * EPS[prec] * len(ops), (n, prec, dm, fusion)
+
+    for n, prec, dm, fusion in [(11, 'C128', False, 9), (11, 'C64', False, 9), (12, 'C128', False, 9),
+                                (8, 'C128', True, 9), (12, 'C128', False, 10), (12, 'C128', False, 10)]:
+        check(n, prec, dm, fusion)
+    ops[0].u = haar_unitary(rng)
+    c.set_unitary(0, ops[0].u)
+    check(12, 'C128', False, 10)
+    ops.append(Op('u', target=3, u=haar_unitary(rng)))
+    c.add(ops[-1])
+    check(12, 'C128', False, 10)
+    c.close()
