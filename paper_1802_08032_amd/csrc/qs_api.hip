@@ -1560,29 +1560,17 @@ qs_status check_finite(const qs_cplx* a, size_t count)
     return QS_OK;
 }
 
-// Copy a d x d complex matrix (interleaved doubles) into matrix slot `slot`
-// (0 or 1) of the register's scratch, in the register's precision, ordered
-// on its stream after earlier work; returns the device address.
-qs_status upload_matrix(qs_reg r, int slot, const std::vector<double>& m, const void** dev)
-{
-    char* dst = (char*)(r->scratch + qs::kScratchMatOff) + (size_t)slot * (32 * 32 * 2 * sizeof(double));
-    if (r->prec == QS_C128) {
-        QS_HIP(hipMemcpyAsync(dst, m.data(), m.size() * sizeof(double), hipMemcpyHostToDevice, r->stream));
-    } else {
-        std::vector<float> f(m.begin(), m.end());
-        QS_HIP(hipMemcpyAsync(dst, f.data(), f.size() * sizeof(float), hipMemcpyHostToDevice, r->stream));
-    }
-    *dev = dst;
-    return QS_OK;
-}
-
-qs_status group_launch(qs_reg r, const int* targets, int k, const int* ctrls, int nc, const void* dev_m, int klass)
+// m on the groups of the given vector bits; matrices of k >= 4 go through
+// slot 0 or 1 of the register's scratch, ordered on its stream.
+qs_status group_launch(qs_reg r, const int* targets, int k, const int* ctrls, int nc, const std::complex<double>* m,
+                       int slot, int klass)
 {
     const qs::Launch L = launch_of(r);
+    void* dm = (char*)(r->scratch + qs::kScratchMatOff) + (size_t)slot * (32 * 32 * 2 * sizeof(double));
     return qs::profiled(r, klass, [&](int*) {
         return r->prec == QS_C128
-                   ? qs::launch_group_gate<double>(L, r->amp, r->nbits, targets, k, ctrls, nc, (const double*)dev_m)
-                   : qs::launch_group_gate<float>(L, r->amp, r->nbits, targets, k, ctrls, nc, (const float*)dev_m);
+                   ? qs::launch_group_gate<double>(L, r->amp, r->nbits, targets, k, ctrls, nc, m, (double*)dm)
+                   : qs::launch_group_gate<float>(L, r->amp, r->nbits, targets, k, ctrls, nc, m, (float*)dm);
     });
 }
 
@@ -1603,22 +1591,31 @@ qs_status qs_multi_qubit_unitary(qs_reg r, const int* controls, int n_controls, 
     const int d = 1 << n_targets;
     if ((s = check_finite(u, (size_t)d * d))) return s;
     if (identity_error(u, d, 1, false) > 1e-10) return qs::set_error(QS_E_NOT_UNITARY, "matrix is not unitary");
-    std::vector<double> m(2 * d * d);
-    for (int i = 0; i < d * d; ++i) {
-        m[2 * i] = u[i].re;
-        m[2 * i + 1] = u[i].im;
-    }
-    const void* dm = nullptr;
-    if ((s = upload_matrix(r, 0, m, &dm))) return s;
-    if ((s = group_launch(r, targets, n_targets, controls, n_controls, dm, QS_K_GATE))) return s;
-    if (r->kind != QS_DENSITY) return QS_OK;
-    // Eq. 2: conj(U) on the column qubits, controls shifted likewise
-    for (int i = 0; i < d * d; ++i) m[2 * i + 1] = -m[2 * i + 1];
+    std::vector<std::complex<double>> m(d * d);
+    for (int i = 0; i < d * d; ++i) m[i] = {u[i].re, u[i].im};
+    if (r->kind != QS_DENSITY) return group_launch(r, targets, n_targets, controls, n_controls, m.data(), 0, QS_K_GATE);
     int ct[5], cc[64];
     for (int j = 0; j < n_targets; ++j) ct[j] = targets[j] + r->n;
     for (int j = 0; j < n_controls; ++j) cc[j] = controls[j] + r->n;
-    if ((s = upload_matrix(r, 1, m, &dm))) return s;
-    return group_launch(r, ct, n_targets, cc, n_controls, dm, QS_K_GATE);
+    if (n_targets <= 2 && n_controls == 0) {
+        // Eq. 2 as one operator on rows and columns, conj(U) (x) U: one pass
+        // over rho instead of two
+        std::vector<std::complex<double>> both((size_t)d * d * d * d);
+        for (int rc = 0; rc < d * d; ++rc)
+            for (int c2 = 0; c2 < d * d; ++c2)
+                both[rc * d * d + c2] = std::conj(m[(rc / d) * d + c2 / d]) * m[(rc % d) * d + c2 % d];
+        int vt[4];
+        for (int j = 0; j < n_targets; ++j) {
+            vt[j] = targets[j];
+            vt[n_targets + j] = ct[j];
+        }
+        return group_launch(r, vt, 2 * n_targets, nullptr, 0, both.data(), 0, QS_K_GATE);
+    }
+    // Eq. 2: U on the row qubits, then conj(U) on the column qubits, controls
+    // shifted likewise
+    if ((s = group_launch(r, targets, n_targets, controls, n_controls, m.data(), 0, QS_K_GATE))) return s;
+    for (auto& z : m) z = std::conj(z);
+    return group_launch(r, ct, n_targets, cc, n_controls, m.data(), 1, QS_K_GATE);
 }
 
 qs_status qs_two_qubit_unitary(qs_reg r, int target1, int target2, const qs_cplx u[16])
@@ -1665,7 +1662,7 @@ qs_status qs_mix_multi_kraus(qs_reg r, const int* targets, int n_targets, const 
     // S[(a + d b)][(a' + d b')] = sum_m K_m[a][a'] conj(K_m[b][b']): row
     // index a on the targets, column index b on the targets + N
     const int D = d * d;
-    std::vector<double> S(2 * D * D, 0.0);
+    std::vector<std::complex<double>> S(D * D);
     for (int m = 0; m < n_ops; ++m) {
         const qs_cplx* K = ops + (size_t)m * d * d;
         for (int a = 0; a < d; ++a)
@@ -1674,8 +1671,7 @@ qs_status qs_mix_multi_kraus(qs_reg r, const int* targets, int n_targets, const 
                     for (int b2 = 0; b2 < d; ++b2) {
                         const qs_cplx x = K[a * d + a2], y = K[b * d + b2];
                         const size_t e = (size_t)(a + d * b) * D + (a2 + d * b2);
-                        S[2 * e] += x.re * y.re + x.im * y.im;
-                        S[2 * e + 1] += x.im * y.re - x.re * y.im;
+                        S[e] += std::complex<double>(x.re * y.re + x.im * y.im, x.im * y.re - x.re * y.im);
                     }
     }
     int vt[4];
@@ -1683,9 +1679,7 @@ qs_status qs_mix_multi_kraus(qs_reg r, const int* targets, int n_targets, const 
         vt[j] = targets[j];
         vt[n_targets + j] = targets[j] + r->n;
     }
-    const void* dm = nullptr;
-    if ((s = upload_matrix(r, 0, S, &dm))) return s;
-    return group_launch(r, vt, 2 * n_targets, nullptr, 0, dm, QS_K_DM_CHANNEL);
+    return group_launch(r, vt, 2 * n_targets, nullptr, 0, S.data(), 0, QS_K_DM_CHANNEL);
 }
 
 qs_status qs_mix_kraus(qs_reg r, int target, const qs_cplx* ops, int n_ops)

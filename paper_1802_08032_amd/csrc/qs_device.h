@@ -87,6 +87,35 @@ __device__ __forceinline__ uint64_t expand(uint64_t i, const BitInsert& b)
     return i | b.ones;
 }
 
+// expand() without the ones.  The inserted bits split no bit of i, so the
+// images of disjoint parts of an index add up: a kernel deposits the thread's
+// part once and the uniform parts with scalar instructions.
+__device__ __forceinline__ uint64_t deposit(uint64_t i, const BitInsert& b)
+{
+    for (int k = 0; k < b.count; ++k) {
+        const int p = b.pos[k];
+        i = ((i >> p) << (p + 1)) | (i & ((1ull << p) - 1ull));
+    }
+    return i;
+}
+
+// Controls, targets and phase bits below kLineBits lie within a 128-byte line.
+template <typename T>
+constexpr int kLineBits = sizeof(T) == 8 ? 3 : 4;
+
+// Value of lane (lane ^ mask), any mask below 64; all lanes must be active.
+__device__ __forceinline__ float lane_across(float v, int src4)
+{
+    return __int_as_float(__builtin_amdgcn_ds_bpermute(src4, __float_as_int(v)));
+}
+__device__ __forceinline__ double lane_across(double v, int src4)
+{
+    const long long b = __double_as_longlong(v);
+    const unsigned lo = (unsigned)__builtin_amdgcn_ds_bpermute(src4, (int)b);
+    const unsigned hi = (unsigned)__builtin_amdgcn_ds_bpermute(src4, (int)(b >> 32));
+    return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
+}
+
 // out = a * x + b * y for complex a, b (interleaved re/im in T[2]).
 template <typename T, typename V>
 __device__ __forceinline__ V cmac2(T ar, T ai, V x, T br, T bi, V y)

@@ -4,6 +4,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <complex>
+
 #include "qstate.h"
 
 namespace qs {
@@ -80,10 +82,12 @@ constexpr int kScratchDoubles = kScratchMatOff + kScratchMatDoubles;
 
 // --- k-qubit groups, initialisation variants, overlaps ---------------------
 // Replace every group of 2^k amplitudes (k = 1..5 targets; matrix index bit j
-// <-> targets[j]) whose control bits are all 1 by dev_m times it; dev_m is a
-// device array of 2^k x 2^k complex T pairs, row-major.
+// <-> targets[j]) whose control bits are all 1 by m times it; m is 2^k x 2^k,
+// row-major, rounded to T once.  dev_m: device memory for 2^k x 2^k complex T
+// pairs (written here, on the stream, for k >= 4).
 template <typename T> hipError_t launch_group_gate(const Launch& L, void* amp, int nbits, const int* targets,
-                                                   int k, const int* ctrls, int nc, const T* dev_m);
+                                                   int k, const int* ctrls, int nc, const std::complex<double>* m,
+                                                   T* dev_m);
 // Every amplitude set to (re, im).  Write-only.
 template <typename T> hipError_t launch_init_fill(const Launch& L, void* amp, uint64_t len, double re, double im);
 // rho = |psi><psi| in the Eq. 2 layout; psi holds 2^N amplitudes.

@@ -8,6 +8,8 @@
 // blocks per CU; the streaming kernels take kPer amplitudes per thread per
 // step (see qs_device.h).
 #include <algorithm>
+#include <complex>
+#include <vector>
 
 #include "qs_device.h"
 
@@ -689,12 +691,19 @@ __global__ __launch_bounds__(kBlock) void k_diag_dm(const typename C2<T>::type* 
 // ---------------------------------------------------------------------------
 // k-qubit groups.  Eq. 1 and the Eq. 2 identity hold for gates on several
 // qubits (Sec. II.B.1): a group is the D = 2^k amplitudes that agree on
-// every bit outside the target set, member r at base + the sum of
-// tbit[j] = 2^targets[j] over the set bits j of r; the group is replaced by
-// m times it (m: D x D complex, row-major, interleaved, read with uniform
-// loads).  `ins` inserts a 0 at every target and a 1 at every control.  One
-// thread holds one group and writes each output row as soon as it is formed
-// (all D inputs are already in registers).
+// every bit outside the target set, member r at base + the sum of the target
+// bits whose bit of r is set; the group is replaced by m times it (m: D x D
+// complex, row-major, interleaved).  Targets and member bits are in ascending
+// order of the qubits.  Controls below the line size are the bits of
+// `lowmask`, tested per group: unselected groups are written back unchanged.
+//
+// k <= 3, no target within a line: one thread holds P groups, all D members
+// of each, and the matrix is read with scalar loads.
+template <typename T, int K>
+struct MatK {
+    T m[2 << (2 * K)];
+};
+
 template <int K>
 struct GroupBits {
     uint64_t tbit[K];
@@ -710,40 +719,262 @@ __device__ __forceinline__ uint64_t group_off(const GroupBits<K>& gb, int r)
     return o;
 }
 
-template <typename T, int K>
+template <typename T, int K, int P>
 __global__ __launch_bounds__(kBlock) void k_group_gate(typename C2<T>::type* __restrict__ amp,
                                                        uint64_t ngroups, BitInsert ins, GroupBits<K> gb,
-                                                       const T* __restrict__ m)
+                                                       uint64_t lowmask, MatK<T, K> mk)
 {
     using V = typename C2<T>::type;
     constexpr int D = 1 << K;
-    const uint64_t stride = (uint64_t)gridDim.x * kBlock;
-    for (uint64_t g = (uint64_t)blockIdx.x * kBlock + threadIdx.x; g < ngroups; g += stride) {
-        const uint64_t b = expand(g, ins);
-        V x[D];
+    const uint64_t tb = deposit(threadIdx.x, ins);
+    for (uint64_t g0 = (uint64_t)blockIdx.x * kBlock * P; g0 < ngroups; g0 += (uint64_t)gridDim.x * kBlock * P) {
+        uint64_t b[P];
+        bool on[P];
+        V x[P][D];
 #pragma unroll
-        for (int j = 0; j < D; ++j) x[j] = ldnt(amp + b + group_off<K>(gb, j));
+        for (int p = 0; p < P; ++p) {
+            b[p] = tb + (deposit(g0 + (uint64_t)p * kBlock, ins) | ins.ones);
+            on[p] = g0 + (uint64_t)p * kBlock + threadIdx.x < ngroups;
 #pragma unroll
-        for (int i = 0; i < D; ++i) {
-            const T* row = m + 2 * D * i;
-            // one product or multiply-add per statement: every term is a
-            // fused multiply-add
-            T re = row[0] * x[0].x;
-            T im = row[0] * x[0].y;
-            re = -row[1] * x[0].y + re;
-            im = row[1] * x[0].x + im;
-#pragma unroll
-            for (int j = 1; j < D; ++j) {
-                re = row[2 * j] * x[j].x + re;
-                re = -row[2 * j + 1] * x[j].y + re;
-                im = row[2 * j] * x[j].y + im;
-                im = row[2 * j + 1] * x[j].x + im;
+            for (int j = 0; j < D; ++j) {
+                x[p][j].x = x[p][j].y = T(0);
+                if (on[p]) x[p][j] = ldnt(amp + b[p] + group_off<K>(gb, j));
             }
-            V y;
-            y.x = re;
-            y.y = im;
-            stnt(amp + b + group_off<K>(gb, i), y);
         }
+#pragma unroll
+        for (int p = 0; p < P; ++p) {
+            if (!on[p]) continue;
+            const bool ok = (b[p] & lowmask) == lowmask;
+#pragma unroll
+            for (int i = 0; i < D; ++i) {
+                const T* row = mk.m + 2 * D * i;
+                // one product or multiply-add per statement: every term is a
+                // fused multiply-add
+                T re = row[0] * x[p][0].x;
+                T im = row[0] * x[p][0].y;
+                re = -row[1] * x[p][0].y + re;
+                im = row[1] * x[p][0].x + im;
+#pragma unroll
+                for (int j = 1; j < D; ++j) {
+                    re = row[2 * j] * x[p][j].x + re;
+                    re = -row[2 * j + 1] * x[p][j].y + re;
+                    im = row[2 * j] * x[p][j].y + im;
+                    im = row[2 * j + 1] * x[p][j].x + im;
+                }
+                V y;
+                y.x = ok ? re : x[p][i].x;
+                y.y = ok ? im : x[p][i].y;
+                stnt(amp + b[p] + group_off<K>(gb, i), y);
+            }
+        }
+    }
+}
+
+// k <= 3 with L targets within a line: those select the lane, the K - L others
+// the register, and a lane gets the members of the other lanes of its group by
+// cross-lane reads.  Loads and stores stay whole lines; with one group per
+// thread each load of a wave touched 64 lines (k = 3 on qubits 0, 1, 2 of 25
+// in complex128: 1,535 us against 190 on high qubits).  `ins` inserts a 0 at
+// the targets of at least a line and a 1 at the high controls.
+template <typename T, int K, int L, int P>
+__global__ __launch_bounds__(kBlock) void k_group_lane(typename C2<T>::type* __restrict__ amp, uint64_t nitems,
+                                                       BitInsert ins, GroupBits<K> gb, uint64_t lowmask,
+                                                       MatK<T, K> mk)
+{
+    using V = typename C2<T>::type;
+    constexpr int D = 1 << K, X = 1 << L, R = 1 << (K - L);
+    static_assert(P % 2 == 0, "the step order alternates two half-runs");
+    const int lane = threadIdx.x & 63;
+    uint32_t own = 0;  // this lane's low member bits
+    int src[X];        // byte index of the lane that differs in the member bits of x
+#pragma unroll
+    for (int j = 0; j < L; ++j) own |= ((uint32_t)lane & (uint32_t)gb.tbit[j]) ? 1u << j : 0u;
+#pragma unroll
+    for (int x = 0; x < X; ++x) {
+        uint32_t mask = 0;
+#pragma unroll
+        for (int j = 0; j < L; ++j)
+            if ((x >> j) & 1) mask |= (uint32_t)gb.tbit[j];
+        src[x] = (int)(((uint32_t)lane ^ mask) << 2);
+    }
+    // c[r][x][s]: entry (own + r X, (own ^ x) + s X)
+    T cr[R][X][R], ci[R][X][R];
+#pragma unroll
+    for (int r = 0; r < R; ++r)
+#pragma unroll
+        for (int x = 0; x < X; ++x)
+#pragma unroll
+            for (int s = 0; s < R; ++s) {
+                T vr = T(0), vi = T(0);
+#pragma unroll
+                for (uint32_t o = 0; o < (uint32_t)X; ++o) {
+                    const int e = 2 * (((int)o + r * X) * D + (((int)o ^ x) + s * X));
+                    vr = own == o ? mk.m[e] : vr;
+                    vi = own == o ? mk.m[e + 1] : vi;
+                }
+                cr[r][x][s] = vr;
+                ci[r][x][s] = vi;
+            }
+    uint64_t hoff[R];
+#pragma unroll
+    for (int r = 0; r < R; ++r) hoff[r] = group_off<K>(gb, r * X);
+    const uint64_t tb = deposit(threadIdx.x, ins);
+    const uint64_t ps = (uint64_t)kBlock * P;
+    for (uint64_t st = blockIdx.x; step_base(st, ps) < nitems; st += gridDim.x) {
+        const uint64_t c = step_base(st, ps);
+        V v[P][R];
+        bool on[P];
+        uint64_t e[P];
+#pragma unroll
+        for (int p = 0; p < P; ++p) {
+            const uint64_t u = c + (uint64_t)(p & 1) * ps + (uint64_t)(p >> 1) * kBlock;
+            on[p] = u + threadIdx.x < nitems;
+            e[p] = tb + (deposit(u, ins) | ins.ones);
+#pragma unroll
+            for (int r = 0; r < R; ++r) {
+                v[p][r].x = v[p][r].y = T(0);
+                if (on[p]) v[p][r] = ldnt(amp + e[p] + hoff[r]);
+            }
+        }
+#pragma unroll
+        for (int p = 0; p < P; ++p) {
+            V y[R], z[R];  // products with the real and with the imaginary parts of m: two short sums
+#pragma unroll
+            for (int r = 0; r < R; ++r) y[r].x = y[r].y = z[r].x = z[r].y = T(0);
+#pragma unroll
+            for (int x = 0; x < X; ++x)
+#pragma unroll
+                for (int s = 0; s < R; ++s) {
+                    // every lane of a wave takes part, also those past the end
+                    const T ax = x ? lane_across(v[p][s].x, src[x]) : v[p][s].x;
+                    const T ay = x ? lane_across(v[p][s].y, src[x]) : v[p][s].y;
+#pragma unroll
+                    for (int r = 0; r < R; ++r) {
+                        y[r].x = cr[r][x][s] * ax + y[r].x;
+                        z[r].x = ci[r][x][s] * ay + z[r].x;
+                        y[r].y = cr[r][x][s] * ay + y[r].y;
+                        z[r].y = ci[r][x][s] * ax + z[r].y;
+                    }
+                }
+            if (!on[p]) continue;
+            const bool ok = (e[p] & lowmask) == lowmask;
+#pragma unroll
+            for (int r = 0; r < R; ++r) {
+                V o;
+                o.x = ok ? y[r].x - z[r].x : v[p][r].x;
+                o.y = ok ? y[r].y + z[r].y : v[p][r].y;
+                stnt(amp + e[p] + hoff[r], o);
+            }
+        }
+    }
+}
+
+// k = 4 and 5 on the matrix cores: a wave takes 16 groups at a time as the
+// columns of a D x 16 matrix.  Lane (g, q) = (lane & 15, lane >> 4) holds the
+// members 4 s + q of group g, which is both the B operand of step s and, with
+// the rows of m in the order below, the place where the products come out, so
+// amplitudes go from memory to the matrix cores and back without passing
+// through LDS.  m stays in registers for the whole launch (Re and Im apart).
+// The two lowest targets select q, so that a load of a wave covers
+// consecutive amplitudes as far as the targets allow; where lines are shared
+// between the loads of a wave (targets within a line) the caches hold them:
+// plain loads there, non-temporal ones else.
+//
+// One thread per group held 2^k amplitudes and waited for the matrix row by
+// row: k = 5 on 25 qubits in complex128 took 620 us on high qubits and 1,414
+// us on qubits 0..4; memory alone needs about 180 us, the multiply-adds 110.
+typedef double Acc64 __attribute__((ext_vector_type(4)));
+typedef float Acc32 __attribute__((ext_vector_type(4)));
+template <typename T> struct MfmaAcc;
+template <> struct MfmaAcc<double> { using type = Acc64; };
+template <> struct MfmaAcc<float> { using type = Acc32; };
+
+__device__ __forceinline__ Acc64 mfma(double a, double b, Acc64 c)
+{
+    return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
+}
+__device__ __forceinline__ Acc32 mfma(float a, float b, Acc32 c)
+{
+    return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
+}
+
+template <typename T, int K, bool NT>
+__global__ __launch_bounds__(kBlock, 2) void k_group_mfma(typename C2<T>::type* __restrict__ amp, uint64_t ngroups,
+                                                          BitInsert ins, GroupBits<K> gb, uint64_t lowmask,
+                                                          const T* __restrict__ m)
+{
+    using V = typename C2<T>::type;
+    using Acc = typename MfmaAcc<T>::type;
+    constexpr int D = 1 << K, S = D / 4, B = D / 16;
+    const int lane = threadIdx.x & 63, g = lane & 15, q = lane >> 4;
+    // Operand rows: result element r of lane (g, q) in block b is row 4 q + r
+    // of the block in single precision and row q + 4 r in double; it has to be
+    // member 4 (r + 4 b) + q.
+    T ur[B][S], ui[B][S];
+#pragma unroll
+    for (int b = 0; b < B; ++b)
+#pragma unroll
+        for (int s = 0; s < S; ++s) {
+            const int row = sizeof(T) == 8 ? 16 * b + g : 16 * b + 4 * (g & 3) + (g >> 2);
+            const T* e = m + 2 * (row * D + 4 * s + q);
+            ur[b][s] = e[0];
+            ui[b][s] = e[1];
+        }
+    uint64_t off[S];
+#pragma unroll
+    for (int s = 0; s < S; ++s) off[s] = group_off<K>(gb, 4 * s);
+    const bool on = (uint64_t)g < ngroups;  // a register of fewer than 16 groups is one set
+    const uint64_t le = deposit(on ? g : 0, ins) + ((q & 1) ? gb.tbit[0] : 0) + ((q & 2) ? gb.tbit[1] : 0);
+    const uint64_t nsets = (ngroups + 15) / 16, nw = (uint64_t)gridDim.x * (kBlock / 64);
+    uint64_t set = (uint64_t)blockIdx.x * (kBlock / 64) + (uint64_t)__builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    if (set >= nsets) return;
+    auto load = [&](const V* p) { return NT ? ldnt(p) : *p; };
+    uint64_t e = le + (deposit(set * 16, ins) | ins.ones);
+    V x[S];
+#pragma unroll
+    for (int s = 0; s < S; ++s) x[s] = load(amp + e + off[s]);
+    for (;;) {
+        // the next set's amplitudes, in flight during the products
+        const uint64_t next = set + nw;
+        uint64_t ne = e;
+        V nx[S];
+        if (next < nsets) ne = le + (deposit(next * 16, ins) | ins.ones);
+#pragma unroll
+        for (int s = 0; s < S; ++s) nx[s] = x[s];
+        if (next < nsets) {
+#pragma unroll
+            for (int s = 0; s < S; ++s) nx[s] = load(amp + ne + off[s]);
+        }
+        // the two products of each part apart: half as long a chain of sums
+        // (smaller rounding errors) and independent accumulators
+        Acc re[B], im[B], re2[B], im2[B];
+#pragma unroll
+        for (int b = 0; b < B; ++b) re[b] = im[b] = re2[b] = im2[b] = Acc{T(0), T(0), T(0), T(0)};
+#pragma unroll
+        for (int s = 0; s < S; ++s)
+#pragma unroll
+            for (int b = 0; b < B; ++b) {
+                re[b] = mfma(ur[b][s], x[s].x, re[b]);
+                im[b] = mfma(ur[b][s], x[s].y, im[b]);
+                re2[b] = mfma(ui[b][s], x[s].y, re2[b]);
+                im2[b] = mfma(ui[b][s], x[s].x, im2[b]);
+            }
+        const bool ok = (e & lowmask) == lowmask;
+        if (on) {
+#pragma unroll
+            for (int s = 0; s < S; ++s) {
+                V y;
+                y.x = ok ? re[s >> 2][s & 3] - re2[s >> 2][s & 3] : x[s].x;
+                y.y = ok ? im[s >> 2][s & 3] + im2[s >> 2][s & 3] : x[s].y;
+                if (NT) stnt(amp + e + off[s], y);
+                else amp[e + off[s]] = y;
+            }
+        }
+        if (next >= nsets) return;
+        set = next;
+        e = ne;
+#pragma unroll
+        for (int s = 0; s < S; ++s) x[s] = nx[s];
     }
 }
 
@@ -869,10 +1100,8 @@ __global__ __launch_bounds__(kBlock) void k_fid_dm(const typename C2<T>::type* _
 // Launchers
 
 // Controls (and phase bits) below kLineBits select within a 128-byte line:
-// the pair and phase kernels walk those bits too and test them per item, so
-// that loads and stores stay contiguous.
-template <typename T>
-constexpr int kLineBits = sizeof(T) == 8 ? 3 : 4;
+// the pair, group and phase kernels walk those bits too and test them per
+// item, so that loads and stores stay contiguous.
 
 // Small registers take kSmallPer items (amplitudes, pairs or 4-groups) per
 // thread per step instead of 256 bytes' worth, so that the grid still
@@ -1179,36 +1408,157 @@ hipError_t launch_collapse_dm(const Launch& L, void* rho, int N, int q, int outc
     return hipGetLastError();
 }
 
+// Sorts the targets, with the bits of the matrix index in the same order.
 template <typename T>
-hipError_t launch_group_gate(const Launch& L, void* amp, int nbits, const int* targets, int k, const int* ctrls,
-                             int nc, const T* dev_m)
+static void sort_targets(const int* targets, int k, const std::complex<double>* m, int* st, T* sm)
+{
+    const int d = 1 << k;
+    int order[5];
+    for (int j = 0; j < k; ++j) order[j] = j;
+    std::sort(order, order + k, [&](int a, int b) { return targets[a] < targets[b]; });
+    int from[32];  // matrix index of member r
+    for (int r = 0; r < d; ++r) {
+        from[r] = 0;
+        for (int j = 0; j < k; ++j)
+            if ((r >> j) & 1) from[r] |= 1 << order[j];
+    }
+    for (int j = 0; j < k; ++j) st[j] = targets[order[j]];
+    for (int r = 0; r < d; ++r)
+        for (int c = 0; c < d; ++c) {
+            sm[2 * (r * d + c)] = (T)m[from[r] * d + from[c]].real();
+            sm[2 * (r * d + c) + 1] = (T)m[from[r] * d + from[c]].imag();
+        }
+}
+
+template <typename T, int K, int L>
+static hipError_t group_lane(const Launch& L0, void* amp, int nbits, const int* st, const int* pos, int np, uint64_t ones,
+                             uint64_t lowmask, const GroupBits<K>& gb, const MatK<T, K>& mk)
 {
     using V = typename C2<T>::type;
-    int pos[64];
-    int np = 0;
-    uint64_t ones = 0;
-    for (int j = 0; j < k; ++j) pos[np++] = targets[j];
+    // 128 bytes per lane in flight, less where the 8 x 8 rows fill the registers
+    constexpr int P = std::max(2, (sizeof(T) == 8 ? (K == 3 && L == 3 ? 4 : 8) : 16) >> (K - L));
+    int ip[64];
+    int ni = 0;
+    for (int j = L; j < K; ++j) ip[ni++] = st[j];
+    for (int j = 0; j < np; ++j) ip[ni++] = pos[j];
+    const uint64_t nitems = 1ull << (nbits - ni);
+    const BitInsert ins = make_insert(ip, ni, ones);
+    if (wide(nitems, P))
+        hipLaunchKernelGGL((k_group_lane<T, K, L, P>), dim3(grid_for(nitems, P)), dim3(kBlock), 0, L0.stream, (V*)amp,
+                           nitems, ins, gb, lowmask, mk);
+    else
+        hipLaunchKernelGGL((k_group_lane<T, K, L, kSmallPer>), dim3(grid_for(nitems, kSmallPer)), dim3(kBlock), 0,
+                           L0.stream, (V*)amp, nitems, ins, gb, lowmask, mk);
+    return hipGetLastError();
+}
+
+template <typename T, int K>
+static hipError_t group_small(const Launch& L, void* amp, int nbits, const int* targets, const int* ctrls, int nc,
+                              const std::complex<double>* m)
+{
+    using V = typename C2<T>::type;
+    int st[5], pos[64];
+    MatK<T, K> mk;
+    sort_targets<T>(targets, K, m, st, mk.m);
+    int np = 0, nlow = 0;
+    uint64_t ones = 0, lowmask = 0;
     for (int j = 0; j < nc; ++j) {
+        if (ctrls[j] < kLineBits<T>) {
+            lowmask |= 1ull << ctrls[j];
+            continue;
+        }
+        pos[np++] = ctrls[j];
+        ones |= 1ull << ctrls[j];
+    }
+    GroupBits<K> gb;
+    for (int j = 0; j < K; ++j) {
+        gb.tbit[j] = 1ull << st[j];
+        nlow += st[j] < kLineBits<T>;
+    }
+    // cross-lane reads need whole waves of items: 2^6 of them
+    switch (nlow) {
+    case 1: return group_lane<T, K, 1>(L, amp, nbits, st, pos, np, ones, lowmask, gb, mk);
+    case 2: return group_lane<T, K, 2>(L, amp, nbits, st, pos, np, ones, lowmask, gb, mk);
+    case 3:
+        if constexpr (K == 3) return group_lane<T, K, 3>(L, amp, nbits, st, pos, np, ones, lowmask, gb, mk);
+        break;
+    default: break;
+    }
+    for (int j = 0; j < K; ++j) pos[np++] = st[j];
+    const BitInsert ins = make_insert(pos, np, ones);
+    const uint64_t ngroups = 1ull << (nbits - np);
+    constexpr int P = std::max(1, (sizeof(T) == 8 ? 8 : 16) >> K);
+    if (wide(ngroups, P))
+        hipLaunchKernelGGL((k_group_gate<T, K, P>), dim3(grid_for(ngroups, P)), dim3(kBlock), 0, L.stream, (V*)amp,
+                           ngroups, ins, gb, lowmask, mk);
+    else
+        hipLaunchKernelGGL((k_group_gate<T, K, 1>), dim3(grid_for(ngroups, 1)), dim3(kBlock), 0, L.stream, (V*)amp,
+                           ngroups, ins, gb, lowmask, mk);
+    return hipGetLastError();
+}
+
+template <typename T, int K>
+static hipError_t group_mfma(const Launch& L, void* amp, int nbits, const int* targets, const int* ctrls, int nc,
+                             const std::complex<double>* m, T* dev_m)
+{
+    using V = typename C2<T>::type;
+    constexpr int D = 1 << K;
+    int st[5], pos[64];
+    std::vector<T> sm(2 * D * D);
+    sort_targets<T>(targets, K, m, st, sm.data());
+    // from pageable memory the copy has left `sm` when the call returns
+    const hipError_t e = hipMemcpyAsync(dev_m, sm.data(), sm.size() * sizeof(T), hipMemcpyHostToDevice, L.stream);
+    if (e != hipSuccess) return e;
+    int np = 0;
+    uint64_t ones = 0, lowmask = 0;
+    GroupBits<K> gb;
+    for (int j = 0; j < K; ++j) {
+        gb.tbit[j] = 1ull << st[j];
+        pos[np++] = st[j];
+    }
+    for (int j = 0; j < nc; ++j) {
+        if (ctrls[j] < kLineBits<T>) {
+            lowmask |= 1ull << ctrls[j];
+            continue;
+        }
         pos[np++] = ctrls[j];
         ones |= 1ull << ctrls[j];
     }
     const BitInsert ins = make_insert(pos, np, ones);
     const uint64_t ngroups = 1ull << (nbits - np);
-    const int grid = grid_for(ngroups, 1);
-    switch (k) {
-#define QS_GROUP(KK) case KK: {                                                                        \
-        GroupBits<KK> gb;                                                                              \
-        for (int j = 0; j < KK; ++j) gb.tbit[j] = 1ull << targets[j];                                  \
-        hipLaunchKernelGGL((k_group_gate<T, KK>), dim3(grid), dim3(kBlock), 0, L.stream, (V*)amp, ngroups, \
-                           ins, gb, dev_m);                                                            \
-        break;                                                                                         \
-    }
-        QS_GROUP(1) QS_GROUP(2) QS_GROUP(3) QS_GROUP(4) QS_GROUP(5)
-#undef QS_GROUP
-    default:
-        return hipErrorInvalidValue;
-    }
+    const uint64_t blocks = (ngroups + 63) / 64;  // four waves of 16 groups
+    // two blocks per CU: as fast as more in complex128, faster in complex64
+    // (k = 5 on 25 qubits 118 us; with four 150)
+    const uint64_t most = 256 * 2;
+    const dim3 grid((unsigned)std::min(blocks, most));
+    if (st[0] < kLineBits<T>)
+        hipLaunchKernelGGL((k_group_mfma<T, K, false>), grid, dim3(kBlock), 0, L.stream, (V*)amp, ngroups, ins, gb, lowmask,
+                           dev_m);
+    else
+        hipLaunchKernelGGL((k_group_mfma<T, K, true>), grid, dim3(kBlock), 0, L.stream, (V*)amp, ngroups, ins, gb, lowmask,
+                           dev_m);
     return hipGetLastError();
+}
+
+template <typename T>
+hipError_t launch_group_gate(const Launch& L, void* amp, int nbits, const int* targets, int k, const int* ctrls,
+                             int nc, const std::complex<double>* m, T* dev_m)
+{
+    switch (k) {
+    case 1: {
+        Mat2<T> u;
+        for (int i = 0; i < 4; ++i) {
+            u.m[2 * i] = (T)m[i].real();
+            u.m[2 * i + 1] = (T)m[i].imag();
+        }
+        return launch_gate<T>(L, amp, nbits, targets[0], ctrls, nc, u, nullptr);
+    }
+    case 2: return group_small<T, 2>(L, amp, nbits, targets, ctrls, nc, m);
+    case 3: return group_small<T, 3>(L, amp, nbits, targets, ctrls, nc, m);
+    case 4: return group_mfma<T, 4>(L, amp, nbits, targets, ctrls, nc, m, dev_m);
+    case 5: return group_mfma<T, 5>(L, amp, nbits, targets, ctrls, nc, m, dev_m);
+    default: return hipErrorInvalidValue;
+    }
 }
 
 template <typename T>
@@ -1297,7 +1647,7 @@ hipError_t launch_fid_dm(const Launch& L, const void* rho, int N, const void* ps
     template hipError_t launch_collapse_sv<T>(const Launch&, void*, int, int, int, double);            \
     template hipError_t launch_collapse_dm<T>(const Launch&, void*, int, int, int, double); \
     template hipError_t launch_group_gate<T>(const Launch&, void*, int, const int*, int, const int*, int, \
-                                             const T*);                                                \
+                                             const std::complex<double>*, T*);                         \
     template hipError_t launch_init_fill<T>(const Launch&, void*, uint64_t, double, double);           \
     template hipError_t launch_dm_from_pure<T>(const Launch&, void*, int, const void*);                \
     template hipError_t launch_inner_sv<T>(const Launch&, const void*, const void*, int, double*, double*); \
