@@ -190,18 +190,8 @@ qs_status do_phase(qs_reg r, const int* qubits, int nq, double angle)
     uint64_t mask = 0;
     for (int k = 0; k < nq; ++k) mask |= 1ull << qubits[k];
     const double c = cos(angle), s = sin(angle);
-    if (r->kind == QS_DENSITY) {
-        // rows with all bits set gain exp(i a), columns with all bits set
-        // gain exp(-i a); entries with both keep their value.
-        const uint64_t cmask = mask << r->n;
-        qs_status st = qs::profiled(r, QS_K_PHASE, [&](int*) {
-            return qs::launch_phase<T>(L, r->amp, r->nbits, mask, cmask, c, s);
-        });
-        if (st != QS_OK) return st;
-        return qs::profiled(r, QS_K_PHASE, [&](int*) {
-            return qs::launch_phase<T>(L, r->amp, r->nbits, cmask, mask, c, -s);
-        });
-    }
+    if (r->kind == QS_DENSITY)  // rows with all bits set gain exp(i a), columns exp(-i a)
+        return qs::profiled(r, QS_K_PHASE, [&](int*) { return qs::launch_dm_phase<T>(L, r->amp, r->n, mask, c, s); });
     return qs::profiled(r, QS_K_PHASE, [&](int*) {
         return qs::launch_phase<T>(L, r->amp, r->nbits, mask, 0, c, s);
     });

@@ -99,6 +99,32 @@ __device__ __forceinline__ uint64_t deposit(uint64_t i, const BitInsert& b)
     return i;
 }
 
+// Where the items of a step sit after deposit().  Item j of a step is base +
+// (j & 1) PS + (j >> 1) `row` + the thread's part, three disjoint sets of bits
+// of the index, so only the base has to be deposited per step (with scalar
+// instructions): depositing each item by itself was up to half the time of
+// the complex64 kernels, which have twice as many items per byte.
+template <int U>
+struct StepItems {
+    static constexpr int kLog = U >= 64 ? 5 : U >= 32 ? 4 : U >= 16 ? 3 : U >= 8 ? 2 : U >= 4 ? 1 : 0;
+    static_assert(U >= 2 && (U & (U - 1)) == 0 && U <= 64, "a step is a power of two of items");
+    uint64_t odd, bit[kLog > 0 ? kLog : 1];
+    __device__ __forceinline__ StepItems(uint64_t ps, uint64_t row, const BitInsert& ins)
+    {
+        odd = deposit(ps, ins);
+#pragma unroll
+        for (int k = 0; k < kLog; ++k) bit[k] = deposit(row << k, ins);
+    }
+    __device__ __forceinline__ uint64_t operator()(int j) const
+    {
+        uint64_t o = (j & 1) ? odd : 0;
+#pragma unroll
+        for (int k = 0; k < kLog; ++k)
+            if ((j >> (k + 1)) & 1) o += bit[k];
+        return o;
+    }
+};
+
 // Controls, targets and phase bits below kLineBits lie within a 128-byte line.
 template <typename T>
 constexpr int kLineBits = sizeof(T) == 8 ? 3 : 4;

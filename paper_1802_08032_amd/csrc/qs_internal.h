@@ -46,6 +46,9 @@ template <typename T> hipError_t launch_phase(const Launch& L, void* amp, int nb
                                               uint64_t skip, double fre, double fim);
 
 // --- density-matrix kernels ------------------------------------------------
+// Phase f on the rows with all bits of `rmask` set, conj(f) on the columns.
+template <typename T> hipError_t launch_dm_phase(const Launch& L, void* rho, int N, uint64_t rmask, double fre,
+                                                 double fim);
 template <typename T> hipError_t launch_dm_gate(const Launch& L, void* rho, int N, int t,
                                                 const int* ctrls, int nc, const Mat2<T>& u);
 template <typename T> hipError_t launch_dm_channel(const Launch& L, void* rho, int N, int t,

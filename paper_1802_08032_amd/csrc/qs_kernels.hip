@@ -64,30 +64,32 @@ __global__ __launch_bounds__(kBlock) void k_gate_pair(typename C2<T>::type* __re
                                                       uint64_t lowmask, Mat2<T> u)
 {
     using V = typename C2<T>::type;
-    static_assert(P % 2 == 0, "the step order alternates two half-runs");
     const uint64_t ps = (uint64_t)kBlock * P;
+    const StepItems<P> at(ps, kBlock, ins);
+    const uint64_t et = deposit(threadIdx.x, ins);
+    const bool ok = (et & lowmask) == lowmask;  // bits within a line are the thread's own
     for (uint64_t s = blockIdx.x; step_base(s, ps) < npairs; s += gridDim.x) {
         const uint64_t c = step_base(s, ps);
-        uint64_t a[P];
+        const uint64_t ec = deposit(c, ins) | ins.ones;
         V x[P], y[P];
-#pragma unroll
-        for (int j = 0; j < P; ++j) {
-            const uint64_t i = step_item(c, j, ps);
-            a[j] = expand(i < npairs ? i : npairs - 1, ins);  // a clamped lane only reads
-        }
+        bool on[P];
         // all low halves, then all high halves: each run of loads alternates
         // between the step's two half-runs
 #pragma unroll
-        for (int j = 0; j < P; ++j) x[j] = ldnt(amp + a[j]);
+        for (int j = 0; j < P; ++j) {
+            on[j] = step_item(c, j, ps) < npairs;
+            x[j].x = x[j].y = y[j].x = y[j].y = T(0);
+            if (on[j]) x[j] = ldnt(amp + (et + (ec + at(j))));
+        }
 #pragma unroll
-        for (int j = 0; j < P; ++j) y[j] = ldnt(amp + a[j] + tb);
+        for (int j = 0; j < P; ++j)
+            if (on[j]) y[j] = ldnt(amp + (et + (ec + at(j) + tb)));
 #pragma unroll
         for (int j = 0; j < P; ++j) {
             // controls below the line size are tested per pair: unselected
             // pairs are written back unchanged, so every store is a full line
             V nx = x[j], ny = y[j];
             apply2<T, V>(u.m, nx, ny);
-            const bool ok = (a[j] & lowmask) == lowmask;
             // component-wise selects: a select of whole vector structs puts
             // the arrays in scratch memory
             x[j].x = ok ? nx.x : x[j].x;
@@ -97,10 +99,10 @@ __global__ __launch_bounds__(kBlock) void k_gate_pair(typename C2<T>::type* __re
         }
 #pragma unroll
         for (int j = 0; j < P; ++j)
-            if (step_item(c, j, ps) < npairs) stnt(amp + a[j], x[j]);
+            if (on[j]) stnt(amp + (et + (ec + at(j))), x[j]);
 #pragma unroll
         for (int j = 0; j < P; ++j)
-            if (step_item(c, j, ps) < npairs) stnt(amp + a[j] + tb, y[j]);
+            if (on[j]) stnt(amp + (et + (ec + at(j) + tb)), y[j]);
     }
 }
 
@@ -161,22 +163,20 @@ __global__ __launch_bounds__(kBlock) void k_gate_low(typename C2<T>::type* __res
     // chunks play the role of items: a workgroup step of PS = 4 * kPer
     // chunks is two half-runs PS apart, alternated as in step_item (with
     // the 4 waves in place of the threads)
-    const int w = threadIdx.x >> 6;
+    const uint64_t w = (uint64_t)__builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const uint64_t ps = (uint64_t)(kBlock / 64) * U;
-    auto chunk = [&](uint64_t base, int j) {
-        return base + (uint64_t)(j & 1) * ps + (uint64_t)(j >> 1) * (kBlock / 64) + w;
-    };
+    const StepItems<U> at(ps, kBlock / 64, hi);
     for (uint64_t s = blockIdx.x; step_base(s, ps) < nchunks; s += gridDim.x) {
-        const uint64_t c0 = step_base(s, ps);
+        const uint64_t c0 = step_base(s, ps) + w;
+        const uint64_t ec = deposit(c0, hi) | hi.ones;
         V v[U];
-        uint64_t e[U];
+        bool on[U];
 #pragma unroll
         for (int j = 0; j < U; ++j) {
-            const uint64_t c = chunk(c0, j);
-            e[j] = (expand(c < nchunks ? c : nchunks - 1, hi) << 6) | (uint64_t)lane;
+            on[j] = c0 + (uint64_t)(j & 1) * ps + (uint64_t)(j >> 1) * (kBlock / 64) < nchunks;  // uniform over the wave
             v[j].x = T(0);
             v[j].y = T(0);
-            if (act) v[j] = ldnt(amp + e[j]);
+            if (act && on[j]) v[j] = ldnt(amp + (((ec + at(j)) << 6) + (uint64_t)lane));
         }
 #pragma unroll
         for (int j = 0; j < U; ++j) {
@@ -191,7 +191,7 @@ __global__ __launch_bounds__(kBlock) void k_gate_low(typename C2<T>::type* __res
             V o;
             o.x = ok ? r.x : v[j].x;
             o.y = ok ? r.y : v[j].y;
-            if (act && chunk(c0, j) < nchunks) stnt(amp + e[j], o);
+            if (act && on[j]) stnt(amp + (((ec + at(j)) << 6) + (uint64_t)lane), o);
         }
     }
 }
@@ -203,26 +203,28 @@ __global__ __launch_bounds__(kBlock) void k_not(typename C2<T>::type* __restrict
                                                 uint64_t npairs, uint64_t tb, BitInsert ins, uint64_t lowmask)
 {
     using V = typename C2<T>::type;
-    static_assert(P % 2 == 0, "the step order alternates two half-runs");
     const uint64_t ps = (uint64_t)kBlock * P;
+    const StepItems<P> at(ps, kBlock, ins);
+    const uint64_t et = deposit(threadIdx.x, ins);
+    const bool ok = (et & lowmask) == lowmask;  // bits within a line are the thread's own
     for (uint64_t s = blockIdx.x; step_base(s, ps) < npairs; s += gridDim.x) {
         const uint64_t c = step_base(s, ps);
-        uint64_t a[P];
+        const uint64_t ec = deposit(c, ins) | ins.ones;
         V x[P], y[P];
-#pragma unroll
-        for (int j = 0; j < P; ++j) {
-            const uint64_t i = step_item(c, j, ps);
-            a[j] = expand(i < npairs ? i : npairs - 1, ins);  // a clamped lane only reads
-        }
+        bool on[P];
         // all low halves, then all high halves: each run of loads alternates
         // between the step's two half-runs
 #pragma unroll
-        for (int j = 0; j < P; ++j) x[j] = ldnt(amp + a[j]);
+        for (int j = 0; j < P; ++j) {
+            on[j] = step_item(c, j, ps) < npairs;
+            x[j].x = x[j].y = y[j].x = y[j].y = T(0);
+            if (on[j]) x[j] = ldnt(amp + (et + (ec + at(j))));
+        }
 #pragma unroll
-        for (int j = 0; j < P; ++j) y[j] = ldnt(amp + a[j] + tb);
+        for (int j = 0; j < P; ++j)
+            if (on[j]) y[j] = ldnt(amp + (et + (ec + at(j) + tb)));
 #pragma unroll
         for (int j = 0; j < P; ++j) {
-            const bool ok = (a[j] & lowmask) == lowmask;  // unselected pairs keep their order
             const T x0 = x[j].x, x1 = x[j].y;
             x[j].x = ok ? y[j].x : x0;
             x[j].y = ok ? y[j].y : x1;
@@ -231,55 +233,95 @@ __global__ __launch_bounds__(kBlock) void k_not(typename C2<T>::type* __restrict
         }
 #pragma unroll
         for (int j = 0; j < P; ++j)
-            if (step_item(c, j, ps) < npairs) stnt(amp + a[j], x[j]);
+            if (on[j]) stnt(amp + (et + (ec + at(j))), x[j]);
 #pragma unroll
         for (int j = 0; j < P; ++j)
-            if (step_item(c, j, ps) < npairs) stnt(amp + a[j] + tb, y[j]);
+            if (on[j]) stnt(amp + (et + (ec + at(j) + tb)), y[j]);
     }
 }
 
 // Diagonal phase on the amplitudes whose `ins.ones` bits are all set,
-// except those that also have every bit of `skip` set (skip != 0).
+// except those that also have every bit of `skip` set (skip != 0; no bit of
+// it lies within a line), which are not touched.
 template <typename T, int U>
 __global__ __launch_bounds__(kBlock) void k_phase(typename C2<T>::type* __restrict__ amp,
                                                   uint64_t count, BitInsert ins, uint64_t lowmask,
                                                   uint64_t skip, T fr, T fi)
 {
-    static_assert(U % 2 == 0, "the step order alternates two half-runs");
     using V = typename C2<T>::type;
     const uint64_t ps = (uint64_t)kBlock * U;
+    const StepItems<U> at(ps, kBlock, ins);
+    const uint64_t et = deposit(threadIdx.x, ins);
+    // bits within a line are the thread's own: its other values are written
+    // back unchanged so that every store is a full line
+    const bool ok = (et & lowmask) == lowmask;
+    const uint64_t none = skip ? 0 : ~0ull;  // with no skip bits nothing is left out
     for (uint64_t s = blockIdx.x; step_base(s, ps) < count; s += gridDim.x) {
         const uint64_t c = step_base(s, ps);
-        uint64_t e[U];
+        const uint64_t ec = deposit(c, ins) | ins.ones;
         bool on[U];
         V v[U];
 #pragma unroll
         for (int j = 0; j < U; ++j) {
-            const uint64_t i = step_item(c, j, ps);
-            e[j] = expand(i < count ? i : count - 1, ins);
-            on[j] = i < count;
-            if (on[j]) v[j] = ldnt(amp + e[j]);
+            const uint64_t e = et + (ec + at(j));
+            on[j] = step_item(c, j, ps) < count && (e & skip) != (skip | none);
+            v[j].x = v[j].y = T(0);
+            if (on[j]) v[j] = ldnt(amp + e);
         }
 #pragma unroll
         for (int j = 0; j < U; ++j) {
-            if (!on[j]) continue;
-            // phase bits below kLineBits are tested per element; the others
-            // are written back unchanged so that every store is a full line
-            const bool hit = (e[j] & lowmask) == lowmask && !(skip != 0 && (e[j] & skip) == skip);
             const V m = cmul<T, V>(fr, fi, v[j]);
-            V r;
-            r.x = hit ? m.x : v[j].x;
-            r.y = hit ? m.y : v[j].y;
-            stnt(amp + e[j], r);
+            v[j].x = ok ? m.x : v[j].x;
+            v[j].y = ok ? m.y : v[j].y;
         }
+#pragma unroll
+        for (int j = 0; j < U; ++j)
+            if (on[j]) stnt(amp + (et + (ec + at(j))), v[j]);
     }
 }
 
-// ---------------------------------------------------------------------------
-// Density matrix, Eq. 2 fused into one pass.  A group is the four entries
-// (rho[r][c]) with row bit t = r and column bit t+N = c; the gate is
-// rho -> (R ? U : I) rho (C ? U^dagger : I), R / C = row / column controls
-// all set.  Columns multiplied by U^dagger is conj(U) on the column qubit.
+// Phase of a density matrix whose qubits lie within a line, rows and columns
+// in one pass: rows with all bits of `rmask` set gain (fr, fi), columns with
+// all bits of `cmask` set its conjugate, entries with both nothing.  Two
+// passes of k_phase read and write most lines twice (CZ on qubits 0 and 1 of
+// 13: complex128 512 us, 365 so; complex64 455, 162).
+template <typename T, int U>
+__global__ __launch_bounds__(kBlock) void k_dm_phase(typename C2<T>::type* __restrict__ rho, uint64_t len,
+                                                     uint64_t rmask, uint64_t cmask, T fr, T fi)
+{
+    using V = typename C2<T>::type;
+    const uint64_t ps = (uint64_t)kBlock * U;
+    constexpr uint64_t kIn = (1ull << kLineBits<T>) - 1;
+    const bool rin = ((threadIdx.x & rmask) & kIn) == (rmask & kIn), cin = ((threadIdx.x & cmask) & kIn) == (cmask & kIn);
+    const uint64_t rline = rmask & ~kIn, cline = cmask & ~kIn;
+    for (uint64_t s = blockIdx.x; step_base(s, ps) < len; s += gridDim.x) {
+        const uint64_t c = step_base(s, ps);
+        bool r[U], k[U];
+        V v[U];
+#pragma unroll
+        for (int j = 0; j < U; ++j) {
+            const uint64_t e = step_item(c, j, ps);
+            r[j] = e < len && (e & rline) == rline;
+            k[j] = e < len && (e & cline) == cline;
+            v[j].x = v[j].y = T(0);
+            if (r[j] || k[j]) v[j] = ldnt(rho + e);
+        }
+#pragma unroll
+        for (int j = 0; j < U; ++j) {
+            const bool row = r[j] && rin, col = k[j] && cin;
+            const V m = cmul<T, V>(fr, row ? fi : -fi, v[j]);
+            v[j].x = row != col ? m.x : v[j].x;
+            v[j].y = row != col ? m.y : v[j].y;
+        }
+#pragma unroll
+        for (int j = 0; j < U; ++j)
+            if (r[j] || k[j]) stnt(rho + step_item(c, j, ps), v[j]);
+    }
+}
+
+// `rline`, `cline`: the parts of rmask and cmask at or above a line; a lane
+// whose line holds no selected entry touches nothing, the others store whole
+// lines.
 template <typename T, int G>
 __global__ __launch_bounds__(kBlock) void k_dm_gate(typename C2<T>::type* __restrict__ rho,
                                                     uint64_t ngroups, uint64_t tb, uint64_t cb,
@@ -290,20 +332,21 @@ __global__ __launch_bounds__(kBlock) void k_dm_gate(typename C2<T>::type* __rest
     T uc[8];
 #pragma unroll
     for (int k = 0; k < 8; ++k) uc[k] = (k & 1) ? -u.m[k] : u.m[k];
-    static_assert(G % 2 == 0, "the step order alternates two half-runs");
+    const uint64_t rline = rmask & ~((1ull << kLineBits<T>) - 1), cline = cmask & ~((1ull << kLineBits<T>) - 1);
     const uint64_t ps = (uint64_t)kBlock * G;
+    const StepItems<G> at(ps, kBlock, ins);
+    const uint64_t et = deposit(threadIdx.x, ins);
     for (uint64_t s = blockIdx.x; step_base(s, ps) < ngroups; s += gridDim.x) {
         const uint64_t c = step_base(s, ps);
+        const uint64_t ec = deposit(c, ins);
         uint64_t b[G];
-        bool R[G], Cc[G];
+        bool act[G];
         V m00[G], m10[G], m01[G], m11[G];
 #pragma unroll
         for (int j = 0; j < G; ++j) {
-            const uint64_t g = step_item(c, j, ps);
-            b[j] = expand(g < ngroups ? g : ngroups - 1, ins);
-            R[j] = g < ngroups && (b[j] & rmask) == rmask;
-            Cc[j] = g < ngroups && (b[j] & cmask) == cmask;
-            if (R[j] || Cc[j]) {
+            b[j] = et + (ec + at(j));
+            act[j] = step_item(c, j, ps) < ngroups && ((b[j] & rline) == rline || (b[j] & cline) == cline);
+            if (act[j]) {
                 m00[j] = ldnt(rho + b[j]);
                 m10[j] = ldnt(rho + b[j] + tb);
                 m01[j] = ldnt(rho + b[j] + cb);
@@ -312,12 +355,12 @@ __global__ __launch_bounds__(kBlock) void k_dm_gate(typename C2<T>::type* __rest
         }
 #pragma unroll
         for (int j = 0; j < G; ++j) {
-            if (!R[j] && !Cc[j]) continue;
-            if (R[j]) {  // U on the row index, for each column
+            if (!act[j]) continue;
+            if ((b[j] & rmask) == rmask) {  // U on the row index, for each column
                 apply2<T, V>(u.m, m00[j], m10[j]);
                 apply2<T, V>(u.m, m01[j], m11[j]);
             }
-            if (Cc[j]) {  // conj(U) on the column index, for each row
+            if ((b[j] & cmask) == cmask) {  // conj(U) on the column index, for each row
                 apply2<T, V>(uc, m00[j], m01[j]);
                 apply2<T, V>(uc, m10[j], m11[j]);
             }
@@ -325,6 +368,73 @@ __global__ __launch_bounds__(kBlock) void k_dm_gate(typename C2<T>::type* __rest
             stnt(rho + b[j] + tb, m10[j]);
             stnt(rho + b[j] + cb, m01[j]);
             stnt(rho + b[j] + tb + cb, m11[j]);
+        }
+    }
+}
+
+// The same for a target within a line: a lane holds the two entries (column
+// bit 0 and 1) of its own row bit and gets the other row's from the lane that
+// holds them, so that every access covers whole lines.  One 4-group per
+// thread touched each line twice, half of it at a time.  13 qubits, target 0:
+// complex128 637 us before, 350 now; complex64 247, 173 (6.2 TB/s).
+template <typename T, int G>
+__global__ __launch_bounds__(kBlock) void k_dm_gate_low(typename C2<T>::type* __restrict__ rho, uint64_t nitems,
+                                                        uint64_t tb, uint64_t cb, BitInsert ins, uint64_t rmask,
+                                                        uint64_t cmask, Mat2<T> u)
+{
+    using V = typename C2<T>::type;
+    const bool up = (threadIdx.x & tb) != 0;
+    const int src = (int)(((threadIdx.x & 63) ^ tb) << 2);
+    const T sr = up ? u.m[6] : u.m[0], si = up ? u.m[7] : u.m[1];
+    const T pr = up ? u.m[4] : u.m[2], pi = up ? u.m[5] : u.m[3];
+    T uc[8];
+#pragma unroll
+    for (int k = 0; k < 8; ++k) uc[k] = (k & 1) ? -u.m[k] : u.m[k];
+    const uint64_t rline = rmask & ~((1ull << kLineBits<T>) - 1), cline = cmask & ~((1ull << kLineBits<T>) - 1);
+    const uint64_t ps = (uint64_t)kBlock * G;
+    const StepItems<G> at(ps, kBlock, ins);
+    const uint64_t et = deposit(threadIdx.x, ins);
+    for (uint64_t s = blockIdx.x; step_base(s, ps) < nitems; s += gridDim.x) {
+        const uint64_t c = step_base(s, ps);
+        const uint64_t ec = deposit(c, ins);
+        uint64_t b[G];
+        bool act[G];
+        V v0[G], v1[G];
+#pragma unroll
+        for (int j = 0; j < G; ++j) {
+            b[j] = et + (ec + at(j));
+            act[j] = step_item(c, j, ps) < nitems && ((b[j] & rline) == rline || (b[j] & cline) == cline);
+            v0[j].x = v0[j].y = v1[j].x = v1[j].y = T(0);
+            if (act[j]) {
+                v0[j] = ldnt(rho + b[j]);
+                v1[j] = ldnt(rho + b[j] + cb);
+            }
+        }
+#pragma unroll
+        for (int j = 0; j < G; ++j) {
+            V p0, p1;  // all lanes take part; a lane and its partner are both active or both not
+            p0.x = lane_across(v0[j].x, src);
+            p0.y = lane_across(v0[j].y, src);
+            p1.x = lane_across(v1[j].x, src);
+            p1.y = lane_across(v1[j].y, src);
+            if (!act[j]) continue;
+            const bool r = (b[j] & rmask) == rmask, k = (b[j] & cmask) == cmask;
+            // U on the row index (its first term is the row with bit 0)
+            const V n0 = up ? cmac2<T, V>(pr, pi, p0, sr, si, v0[j]) : cmac2<T, V>(sr, si, v0[j], pr, pi, p0);
+            const V n1 = up ? cmac2<T, V>(pr, pi, p1, sr, si, v1[j]) : cmac2<T, V>(sr, si, v1[j], pr, pi, p1);
+            V a, d;
+            a.x = r ? n0.x : v0[j].x;
+            a.y = r ? n0.y : v0[j].y;
+            d.x = r ? n1.x : v1[j].x;
+            d.y = r ? n1.y : v1[j].y;
+            V o0 = a, o1 = d;
+            apply2<T, V>(uc, o0, o1);
+            a.x = k ? o0.x : a.x;
+            a.y = k ? o0.y : a.y;
+            d.x = k ? o1.x : d.x;
+            d.y = k ? o1.y : d.y;
+            stnt(rho + b[j], a);
+            stnt(rho + b[j] + cb, d);
         }
     }
 }
@@ -342,16 +452,18 @@ __global__ __launch_bounds__(kBlock) void k_dm_channel(typename C2<T>::type* __r
                                                        BitInsert ins, double p0, double p1, double f)
 {
     using V = typename C2<T>::type;
-    static_assert(G % 2 == 0, "the step order alternates two half-runs");
     const uint64_t ps = (uint64_t)kBlock * G;
+    const StepItems<G> at(ps, kBlock, ins);
+    const uint64_t et = deposit(threadIdx.x, ins);
     for (uint64_t s = blockIdx.x; step_base(s, ps) < ngroups; s += gridDim.x) {
         const uint64_t c = step_base(s, ps);
+        const uint64_t ec = deposit(c, ins);
         uint64_t b[G];
         V m00[G], m10[G], m01[G], m11[G];
 #pragma unroll
         for (int j = 0; j < G; ++j) {
-            const uint64_t g = step_item(c, j, ps);
-            b[j] = expand(g < ngroups ? g : ngroups - 1, ins);
+            b[j] = et + (ec + at(j));
+            if (step_item(c, j, ps) >= ngroups) continue;
             m10[j] = ldnt(rho + b[j] + tb);
             m01[j] = ldnt(rho + b[j] + cb);
             if constexpr (CH != QS_DEPHASING) {
@@ -386,6 +498,74 @@ __global__ __launch_bounds__(kBlock) void k_dm_channel(typename C2<T>::type* __r
                 stnt(rho + b[j], n00);
                 stnt(rho + b[j] + tb + cb, n11);
             }
+        }
+    }
+}
+
+// The same for a target within a line (see k_dm_gate_low): a lane holds one
+// diagonal and one off-diagonal entry of its group, and the other diagonal
+// entry comes from the partner lane.  Depolarising on qubit 0 of 13: complex128
+// 710 us with one group per thread, 343 so; complex64 305, 168.  Dephasing
+// rewrites whole lines here, half of them unchanged: 575 and 355 us.
+template <typename T, int CH, int G>
+__global__ __launch_bounds__(kBlock) void k_dm_channel_low(typename C2<T>::type* __restrict__ rho, uint64_t nitems,
+                                                           uint64_t tb, uint64_t cb, BitInsert ins, double p0,
+                                                           double p1, double f)
+{
+    using V = typename C2<T>::type;
+    const bool up = (threadIdx.x & tb) != 0;
+    const int src = (int)(((threadIdx.x & 63) ^ tb) << 2);
+    const uint64_t ps = (uint64_t)kBlock * G;
+    const StepItems<G> at(ps, kBlock, ins);
+    const uint64_t et = deposit(threadIdx.x, ins);
+    for (uint64_t s = blockIdx.x; step_base(s, ps) < nitems; s += gridDim.x) {
+        const uint64_t c = step_base(s, ps);
+        const uint64_t ec = deposit(c, ins);
+        uint64_t b[G];
+        bool on[G];
+        V v0[G], v1[G];
+#pragma unroll
+        for (int j = 0; j < G; ++j) {
+            b[j] = et + (ec + at(j));
+            on[j] = step_item(c, j, ps) < nitems;
+            v0[j].x = v0[j].y = v1[j].x = v1[j].y = T(0);
+            if (on[j]) {
+                v0[j] = ldnt(rho + b[j]);
+                v1[j] = ldnt(rho + b[j] + cb);
+            }
+        }
+#pragma unroll
+        for (int j = 0; j < G; ++j) {
+            // the diagonal entry is the one whose column bit is the lane's row bit
+            V d, n, m;
+            d.x = up ? v1[j].x : v0[j].x;
+            d.y = up ? v1[j].y : v0[j].y;
+            m.x = up ? v0[j].x : v1[j].x;
+            m.y = up ? v0[j].y : v1[j].y;
+            n = d;
+            if constexpr (CH != QS_DEPHASING) {
+                const double q0 = lane_across(d.x, src), q1 = lane_across(d.y, src);
+                const double d0 = d.x, d1 = d.y;
+                if constexpr (CH == QS_DEPOLARISING) {  // p0 = 1 - 2p/3, p1 = 2p/3
+                    n.x = (T)(p0 * d0 + p1 * q0);
+                    n.y = (T)(p0 * d1 + p1 * q1);
+                } else {  // damping: p0 = gamma, p1 = 1 - gamma
+                    n.x = up ? (T)(p1 * d0) : (T)(d0 + p0 * q0);
+                    n.y = up ? (T)(p1 * d1) : (T)(d1 + p0 * q1);
+                }
+            }
+            m.x = (T)(f * (double)m.x);
+            m.y = (T)(f * (double)m.y);
+            v0[j].x = up ? m.x : n.x;
+            v0[j].y = up ? m.y : n.y;
+            v1[j].x = up ? n.x : m.x;
+            v1[j].y = up ? n.y : m.y;
+        }
+#pragma unroll
+        for (int j = 0; j < G; ++j) {
+            if (!on[j]) continue;
+            stnt(rho + b[j], v0[j]);
+            stnt(rho + b[j] + cb, v1[j]);
         }
     }
 }
@@ -1111,6 +1291,27 @@ constexpr int kSmallPer = 2;
 
 inline bool wide(uint64_t items, int per) { return items >= (uint64_t)512 * kBlock * per; }
 
+// Grid and LDS reserve of a streaming pass over `items` items that touches
+// `amps` amplitudes.  From 512 MiB on, which is past the 256 MiB last-level cache,
+// the pass runs at the HBM's rate, and that falls when many workgroups read
+// and write far apart: a reserve of 64 KB of LDS, never touched, keeps two
+// workgroups on a CU, and more of them in the grid let the dispatcher even
+// out the CUs.  complex128, 29 qubits: gate on qubit 17 5.4 TB/s with six
+// workgroups on a CU, 5.7 with four, 6.0 with two; T gate 5.3 to 5.9;
+// complex64, 30 qubits, CNOT 5.6 to 6.2.  Data within the cache wants the
+// waves instead (complex64, 128 MiB, gate on qubit 4: 43 us, 47 with two).
+struct StreamShape {
+    dim3 grid;
+    unsigned lds;
+};
+template <typename T>
+static StreamShape stream_shape(uint64_t items, int per, uint64_t amps)
+{
+    if (amps * 2 * sizeof(T) < (512ull << 20)) return {dim3(grid_for(items, per)), 0};
+    const uint64_t blocks = items / ((uint64_t)kBlock * per);
+    return {dim3((unsigned)std::min<uint64_t>(blocks, 4 * kMaxGrid)), 64 << 10};
+}
+
 template <typename T>
 hipError_t launch_init_basis(const Launch& L, void* amp, uint64_t len, uint64_t index, double re, double im)
 {
@@ -1173,14 +1374,14 @@ hipError_t launch_gate(const Launch& L, void* amp, int nbits, int t, const int* 
         const uint64_t nchunks = 1ull << (nbits - 6 - nh);
         // one wave-row of 64 lanes per chunk, U chunks per wave per step
         const bool big = wide(nchunks * 64, kPer<T>);
-        const int grid = grid_for(nchunks * 64, big ? kPer<T> : kSmallPer);
+        const StreamShape sh = stream_shape<T>(nchunks * 64, big ? kPer<T> : kSmallPer, nchunks * 64);
         switch (t) {
 #define QS_LOW(TT) case TT:                                                                              \
     if (big)                                                                                             \
-        hipLaunchKernelGGL((k_gate_low<T, TT, kPer<T>>), dim3(grid), dim3(kBlock), 0, L.stream, (V*)amp, \
+        hipLaunchKernelGGL((k_gate_low<T, TT, kPer<T>>), sh.grid, dim3(kBlock), sh.lds, L.stream, (V*)amp, \
                            nchunks, hi, lowmask, u);                                                     \
     else                                                                                                 \
-        hipLaunchKernelGGL((k_gate_low<T, TT, kSmallPer>), dim3(grid), dim3(kBlock), 0, L.stream, (V*)amp, \
+        hipLaunchKernelGGL((k_gate_low<T, TT, kSmallPer>), sh.grid, dim3(kBlock), 0, L.stream, (V*)amp, \
                            nchunks, hi, lowmask, u);                                                     \
     break;
             QS_LOW(0) QS_LOW(1) QS_LOW(2) QS_LOW(3) QS_LOW(4) QS_LOW(5)
@@ -1203,8 +1404,9 @@ hipError_t launch_gate(const Launch& L, void* amp, int nbits, int t, const int* 
     pos[np] = t;
     const BitInsert ins = make_insert(pos, np + 1, ones);
     const uint64_t npairs = 1ull << (nbits - 1 - np);
+    const StreamShape sh = stream_shape<T>(npairs, kPer<T> / 2, 2 * npairs);
     if (wide(npairs, kPer<T> / 2))
-        hipLaunchKernelGGL((k_gate_pair<T, kPer<T> / 2>), dim3(grid_for(npairs, kPer<T> / 2)), dim3(kBlock), 0, L.stream,
+        hipLaunchKernelGGL((k_gate_pair<T, kPer<T> / 2>), sh.grid, dim3(kBlock), sh.lds, L.stream,
                            (V*)amp, npairs, 1ull << t, ins, lowmask, u);
     else
         hipLaunchKernelGGL((k_gate_pair<T, kSmallPer>), dim3(grid_for(npairs, kSmallPer)), dim3(kBlock), 0,
@@ -1238,8 +1440,9 @@ hipError_t launch_not(const Launch& L, void* amp, int nbits, int t, const int* c
     pos[np] = t;
     const BitInsert ins = make_insert(pos, np + 1, ones);
     const uint64_t npairs = 1ull << (nbits - 1 - np);
+    const StreamShape sh = stream_shape<T>(npairs, kPer<T> / 2, 2 * npairs);
     if (wide(npairs, kPer<T> / 2))
-        hipLaunchKernelGGL((k_not<T, kPer<T> / 2>), dim3(grid_for(npairs, kPer<T> / 2)), dim3(kBlock), 0, L.stream,
+        hipLaunchKernelGGL((k_not<T, kPer<T> / 2>), sh.grid, dim3(kBlock), sh.lds, L.stream,
                            (V*)amp, npairs, 1ull << t, ins, lowmask);
     else
         hipLaunchKernelGGL((k_not<T, kSmallPer>), dim3(grid_for(npairs, kSmallPer)), dim3(kBlock), 0, L.stream,
@@ -1259,8 +1462,9 @@ hipError_t launch_phase(const Launch& L, void* amp, int nbits, uint64_t mask, ui
         if ((mask >> q) & 1) pos[np++] = q;
     const BitInsert ins = make_insert(pos, np, mask & ~lowmask);
     const uint64_t count = 1ull << (nbits - np);
+    const StreamShape sh = stream_shape<T>(count, kPer<T>, count);
     if (wide(count, kPer<T>))
-        hipLaunchKernelGGL((k_phase<T, kPer<T>>), dim3(grid_for(count, kPer<T>)), dim3(kBlock), 0, L.stream,
+        hipLaunchKernelGGL((k_phase<T, kPer<T>>), sh.grid, dim3(kBlock), sh.lds, L.stream,
                            (V*)amp, count, ins, lowmask, skip, (T)fre, (T)fim);
     else
         hipLaunchKernelGGL((k_phase<T, kSmallPer>), dim3(grid_for(count, kSmallPer)), dim3(kBlock), 0, L.stream,
@@ -1269,63 +1473,92 @@ hipError_t launch_phase(const Launch& L, void* amp, int nbits, uint64_t mask, ui
 }
 
 template <typename T>
+hipError_t launch_dm_phase(const Launch& L, void* rho, int N, uint64_t rmask, double fre, double fim)
+{
+    using V = typename C2<T>::type;
+    // qubits within a line: one pass over everything; the lines a pass for the
+    // rows and one for the columns would leave out are few
+    if (rmask & ((1ull << kLineBits<T>) - 1)) {
+        const uint64_t len = 1ull << (2 * N);
+        constexpr int U = kPer<double>;  // complex64 too: its 32 index tests per step cost more than the fewer steps save
+        const bool big = wide(len, U);
+        const StreamShape sh = stream_shape<T>(len, big ? U : kSmallPer, len);
+        if (big)
+            hipLaunchKernelGGL((k_dm_phase<T, U>), sh.grid, dim3(kBlock), sh.lds, L.stream, (V*)rho, len, rmask, rmask << N, (T)fre, (T)fim);
+        else
+            hipLaunchKernelGGL((k_dm_phase<T, kSmallPer>), sh.grid, dim3(kBlock), 0, L.stream, (V*)rho, len, rmask, rmask << N, (T)fre,
+                               (T)fim);
+        return hipGetLastError();
+    }
+    // rows with all bits set gain the phase, columns its conjugate; entries
+    // with both keep their value
+    const hipError_t e = launch_phase<T>(L, rho, 2 * N, rmask, rmask << N, fre, fim);
+    return e != hipSuccess ? e : launch_phase<T>(L, rho, 2 * N, rmask << N, rmask, fre, -fim);
+}
+
+template <typename T>
 hipError_t launch_dm_gate(const Launch& L, void* rho, int N, int t, const int* ctrls, int nc,
                           const Mat2<T>& u)
 {
     using V = typename C2<T>::type;
-    const int pos[2] = {t, t + N};
-    const BitInsert ins = make_insert(pos, 2, 0);
+    const int pos[2] = {t + N, t};
+    const bool low = t < kLineBits<T>;
+    const BitInsert ins = make_insert(pos, low ? 1 : 2, 0);
     uint64_t rmask = 0;
     for (int k = 0; k < nc; ++k) rmask |= 1ull << ctrls[k];
-    const uint64_t ngroups = 1ull << (2 * N - 2);
-    if (wide(ngroups, kPer<T> / 4))
-        hipLaunchKernelGGL((k_dm_gate<T, kPer<T> / 4>), dim3(grid_for(ngroups, kPer<T> / 4)), dim3(kBlock), 0,
-                           L.stream, (V*)rho, ngroups, 1ull << t, 1ull << (t + N), ins, rmask, rmask << N, u);
-    else
-        hipLaunchKernelGGL((k_dm_gate<T, kSmallPer>), dim3(grid_for(ngroups, kSmallPer)), dim3(kBlock), 0, L.stream,
-                           (V*)rho, ngroups, 1ull << t, 1ull << (t + N), ins, rmask, rmask << N, u);
+    // items: 4-groups, or for a low target the pairs (column bit 0, 1) of a row
+    const uint64_t items = 1ull << (2 * N - (low ? 1 : 2));
+    const uint64_t tb = 1ull << t, cb = 1ull << (t + N);
+    constexpr int G = kPer<T> / 4, G2 = kPer<T> / 2;
+    const bool big = wide(items, low ? G2 : G);
+    const StreamShape sh = stream_shape<T>(items, !big ? kSmallPer : low ? G2 : G,
+                                             (nc ? 3ull : 4ull) << (2 * N - 2));
+#define QS_DM(K) hipLaunchKernelGGL(K, sh.grid, dim3(kBlock), sh.lds, L.stream, (V*)rho, items, tb, cb, ins, rmask, rmask << N, u)
+    if (low) {
+        if (big) QS_DM((k_dm_gate_low<T, G2>));
+        else QS_DM((k_dm_gate_low<T, kSmallPer>));
+    } else {
+        if (big) QS_DM((k_dm_gate<T, G>));
+        else QS_DM((k_dm_gate<T, kSmallPer>));
+    }
+#undef QS_DM
+    return hipGetLastError();
+}
+
+template <typename T, int CH>
+static hipError_t dm_channel(const Launch& L, void* rho, int N, int t, double p0, double p1, double f)
+{
+    using V = typename C2<T>::type;
+    const int pos[2] = {t + N, t};
+    const bool low = t < kLineBits<T>;
+    const BitInsert ins = make_insert(pos, low ? 1 : 2, 0);
+    const uint64_t items = 1ull << (2 * N - (low ? 1 : 2));
+    const uint64_t tb = 1ull << t, cb = 1ull << (t + N);
+    constexpr int G = kPer<T> / 4, G2 = kPer<T> / 2;
+    const bool big = wide(items, low ? G2 : G);
+    const StreamShape sh = stream_shape<T>(items, !big ? kSmallPer : low ? G2 : G,
+                                             (CH == QS_DEPHASING && !low ? 1ull : 2ull) << (2 * N - 1));
+#define QS_CH(K) hipLaunchKernelGGL(K, sh.grid, dim3(kBlock), sh.lds, L.stream, (V*)rho, items, tb, cb, ins, p0, p1, f)
+    if (low) {
+        if (big) QS_CH((k_dm_channel_low<T, CH, G2>));
+        else QS_CH((k_dm_channel_low<T, CH, kSmallPer>));
+    } else {
+        if (big) QS_CH((k_dm_channel<T, CH, G>));
+        else QS_CH((k_dm_channel<T, CH, kSmallPer>));
+    }
+#undef QS_CH
     return hipGetLastError();
 }
 
 template <typename T>
 hipError_t launch_dm_channel(const Launch& L, void* rho, int N, int t, int channel, double p)
 {
-    using V = typename C2<T>::type;
-    const int pos[2] = {t, t + N};
-    const BitInsert ins = make_insert(pos, 2, 0);
-    const uint64_t ngroups = 1ull << (2 * N - 2);
-    const bool big = wide(ngroups, kPer<T> / 4);
-    const dim3 grid(grid_for(ngroups, big ? kPer<T> / 4 : kSmallPer)), block(kBlock);
-    const uint64_t tb = 1ull << t, cb = 1ull << (t + N);
     switch (channel) {
-    case QS_DEPHASING:
-        if (big)
-            hipLaunchKernelGGL((k_dm_channel<T, QS_DEPHASING, kPer<T> / 4>), grid, block, 0, L.stream, (V*)rho, ngroups,
-                               tb, cb, ins, 0.0, 0.0, 1.0 - 2.0 * p);
-        else
-            hipLaunchKernelGGL((k_dm_channel<T, QS_DEPHASING, kSmallPer>), grid, block, 0, L.stream, (V*)rho, ngroups,
-                               tb, cb, ins, 0.0, 0.0, 1.0 - 2.0 * p);
-        break;
+    case QS_DEPHASING: return dm_channel<T, QS_DEPHASING>(L, rho, N, t, 0.0, 0.0, 1.0 - 2.0 * p);
     case QS_DEPOLARISING:
-        if (big)
-            hipLaunchKernelGGL((k_dm_channel<T, QS_DEPOLARISING, kPer<T> / 4>), grid, block, 0, L.stream, (V*)rho, ngroups,
-                               tb, cb, ins, 1.0 - 2.0 * p / 3.0, 2.0 * p / 3.0,
-                           1.0 - 4.0 * p / 3.0);
-        else
-            hipLaunchKernelGGL((k_dm_channel<T, QS_DEPOLARISING, kSmallPer>), grid, block, 0, L.stream, (V*)rho, ngroups,
-                               tb, cb, ins, 1.0 - 2.0 * p / 3.0, 2.0 * p / 3.0,
-                           1.0 - 4.0 * p / 3.0);
-        break;
-    default:
-        if (big)
-            hipLaunchKernelGGL((k_dm_channel<T, QS_DAMPING, kPer<T> / 4>), grid, block, 0, L.stream, (V*)rho, ngroups,
-                               tb, cb, ins, p, 1.0 - p, sqrt(1.0 - p));
-        else
-            hipLaunchKernelGGL((k_dm_channel<T, QS_DAMPING, kSmallPer>), grid, block, 0, L.stream, (V*)rho, ngroups,
-                               tb, cb, ins, p, 1.0 - p, sqrt(1.0 - p));
-        break;
+        return dm_channel<T, QS_DEPOLARISING>(L, rho, N, t, 1.0 - 2.0 * p / 3.0, 2.0 * p / 3.0, 1.0 - 4.0 * p / 3.0);
+    default: return dm_channel<T, QS_DAMPING>(L, rho, N, t, p, 1.0 - p, sqrt(1.0 - p));
     }
-    return hipGetLastError();
 }
 
 template <typename T>
@@ -1385,8 +1618,9 @@ hipError_t launch_collapse_sv(const Launch& L, void* amp, int nbits, int q, int 
 {
     using V = typename C2<T>::type;
     const uint64_t len = 1ull << nbits;
+    const StreamShape sh = stream_shape<T>(len, kPer<T>, len);
     if (wide(len, kPer<T>))
-        hipLaunchKernelGGL((k_collapse_sv<T, kPer<T>>), dim3(grid_for(len, kPer<T>)), dim3(kBlock), 0, L.stream,
+        hipLaunchKernelGGL((k_collapse_sv<T, kPer<T>>), sh.grid, dim3(kBlock), sh.lds, L.stream,
                            (V*)amp, len, q, outcome, scale);
     else
         hipLaunchKernelGGL((k_collapse_sv<T, kSmallPer>), dim3(grid_for(len, kSmallPer)), dim3(kBlock), 0, L.stream,
@@ -1399,8 +1633,9 @@ hipError_t launch_collapse_dm(const Launch& L, void* rho, int N, int q, int outc
 {
     using V = typename C2<T>::type;
     const uint64_t len = 1ull << (2 * N);
+    const StreamShape sh = stream_shape<T>(len, kPer<T>, len);
     if (wide(len, kPer<T>))
-        hipLaunchKernelGGL((k_collapse_dm<T, kPer<T>>), dim3(grid_for(len, kPer<T>)), dim3(kBlock), 0, L.stream,
+        hipLaunchKernelGGL((k_collapse_dm<T, kPer<T>>), sh.grid, dim3(kBlock), sh.lds, L.stream,
                            (V*)rho, len, q, N, outcome, scale);
     else
         hipLaunchKernelGGL((k_collapse_dm<T, kSmallPer>), dim3(grid_for(len, kSmallPer)), dim3(kBlock), 0, L.stream,
@@ -1443,8 +1678,9 @@ static hipError_t group_lane(const Launch& L0, void* amp, int nbits, const int* 
     for (int j = 0; j < np; ++j) ip[ni++] = pos[j];
     const uint64_t nitems = 1ull << (nbits - ni);
     const BitInsert ins = make_insert(ip, ni, ones);
+    const StreamShape sh = stream_shape<T>(nitems, P, nitems << (K - L));
     if (wide(nitems, P))
-        hipLaunchKernelGGL((k_group_lane<T, K, L, P>), dim3(grid_for(nitems, P)), dim3(kBlock), 0, L0.stream, (V*)amp,
+        hipLaunchKernelGGL((k_group_lane<T, K, L, P>), sh.grid, dim3(kBlock), sh.lds, L0.stream, (V*)amp,
                            nitems, ins, gb, lowmask, mk);
     else
         hipLaunchKernelGGL((k_group_lane<T, K, L, kSmallPer>), dim3(grid_for(nitems, kSmallPer)), dim3(kBlock), 0,
@@ -1488,8 +1724,9 @@ static hipError_t group_small(const Launch& L, void* amp, int nbits, const int* 
     const BitInsert ins = make_insert(pos, np, ones);
     const uint64_t ngroups = 1ull << (nbits - np);
     constexpr int P = std::max(1, (sizeof(T) == 8 ? 8 : 16) >> K);
+    const StreamShape sh = stream_shape<T>(ngroups, P, ngroups << K);
     if (wide(ngroups, P))
-        hipLaunchKernelGGL((k_group_gate<T, K, P>), dim3(grid_for(ngroups, P)), dim3(kBlock), 0, L.stream, (V*)amp,
+        hipLaunchKernelGGL((k_group_gate<T, K, P>), sh.grid, dim3(kBlock), sh.lds, L.stream, (V*)amp,
                            ngroups, ins, gb, lowmask, mk);
     else
         hipLaunchKernelGGL((k_group_gate<T, K, 1>), dim3(grid_for(ngroups, 1)), dim3(kBlock), 0, L.stream, (V*)amp,
@@ -1638,6 +1875,7 @@ hipError_t launch_fid_dm(const Launch& L, const void* rho, int N, const void* ps
                                        int*);                                                          \
     template hipError_t launch_not<T>(const Launch&, void*, int, int, const int*, int);                \
     template hipError_t launch_phase<T>(const Launch&, void*, int, uint64_t, uint64_t, double, double); \
+    template hipError_t launch_dm_phase<T>(const Launch&, void*, int, uint64_t, double, double);       \
     template hipError_t launch_dm_gate<T>(const Launch&, void*, int, int, const int*, int,             \
                                           const Mat2<T>&);                                             \
     template hipError_t launch_dm_channel<T>(const Launch&, void*, int, int, int, double);             \
