@@ -220,33 +220,20 @@ qs_status check_channel(qs_reg r, int channel, int t, double p)
 }
 
 // Probabilities: out[0] = sum over bit q == 0, out[1] = bit q == 1 (q < 0:
-// total in out[0]).  Synchronous.
-// Neumaier compensated sum on the host.
-struct HSum {
-    double s, c;
-};
-
-void hadd(HSum& a, double v)
-{
-    const double t = a.s + v;
-    a.c += (fabs(a.s) >= fabs(v)) ? ((a.s - t) + v) : ((v - t) + a.s);
-    a.s = t;
-}
-
+// total in out[0]).  Synchronous: the last kernel leaves the sums in the
+// register's pinned memory.
 qs_status probs(qs_reg r, int q, double out[2])
 {
     const qs::Launch L = launch_of(r);
     double* partials = r->scratch;
-    double* dev_out = r->scratch + 4 * qs::kReduceBlocks;
     qs_status st = qs::profiled(r, QS_K_REDUCE, [&](int*) {
         if (r->kind == QS_DENSITY)
-            return r->prec == QS_C128 ? qs::launch_prob_dm<double>(L, r->amp, r->n, q, partials, dev_out)
-                                      : qs::launch_prob_dm<float>(L, r->amp, r->n, q, partials, dev_out);
-        return r->prec == QS_C128 ? qs::launch_prob_sv<double>(L, r->amp, r->nbits, q, partials, dev_out)
-                                  : qs::launch_prob_sv<float>(L, r->amp, r->nbits, q, partials, dev_out);
+            return r->prec == QS_C128 ? qs::launch_prob_dm<double>(L, r->amp, r->n, q, partials, r->host_res)
+                                      : qs::launch_prob_dm<float>(L, r->amp, r->n, q, partials, r->host_res);
+        return r->prec == QS_C128 ? qs::launch_prob_sv<double>(L, r->amp, r->nbits, q, partials, r->host_res)
+                                  : qs::launch_prob_sv<float>(L, r->amp, r->nbits, q, partials, r->host_res);
     });
     if (st) return st;
-    QS_HIP(hipMemcpyAsync(r->host_res, dev_out, 2 * sizeof(double), hipMemcpyDeviceToHost, r->stream));
     if ((st = sync_stream(r))) return st;
     out[0] = r->host_res[0];
     out[1] = r->host_res[1];
@@ -498,7 +485,7 @@ static qs_status reg_common(qs_env env, int n, int kind, int prec, void* stream,
     if (!scratch) {
         const size_t sbytes = qs::kScratchDoubles * sizeof(double);
         hipError_t e = dev_alloc(&scratch, sbytes);
-        if (e == hipSuccess) e = hipHostMalloc(&hres, 2 * sizeof(double), hipHostMallocDefault);
+        if (e == hipSuccess) e = hipHostMalloc(&hres, qs::kHostDoubles * sizeof(double), hipHostMallocDefault);
         if (e != hipSuccess) {
             (void)hipGetLastError();
             if (scratch) (void)hipFree(scratch);
@@ -762,15 +749,13 @@ qs_status qs_calc_prob_of_outcome(qs_reg r, int qubit, int outcome, double* out)
     if (r->kind == QS_STATEVEC && qubit >= (r->prec == QS_C128 ? 3 : 4)) {
         const qs::Launch L = launch_of(r);
         double* partials = r->scratch;
-        double* dev_out = r->scratch + 4 * qs::kReduceBlocks;
         s = qs::profiled(r, QS_K_REDUCE, [&](int*) {
             return r->prec == QS_C128
-                       ? qs::launch_prob_half_sv<double>(L, r->amp, r->nbits, qubit, outcome, partials, dev_out)
-                       : qs::launch_prob_half_sv<float>(L, r->amp, r->nbits, qubit, outcome, partials, dev_out);
+                       ? qs::launch_prob_half_sv<double>(L, r->amp, r->nbits, qubit, outcome, partials, r->host_res)
+                       : qs::launch_prob_half_sv<float>(L, r->amp, r->nbits, qubit, outcome, partials, r->host_res);
         });
         if (s) return s;
-        QS_HIP(hipMemcpyAsync(r->host_res, dev_out, 2 * sizeof(double), hipMemcpyDeviceToHost, r->stream));
-        if ((s = sync_stream(r))) return s;
+            if ((s = sync_stream(r))) return s;
         *out = r->host_res[0];
         return QS_OK;
     }
@@ -842,115 +827,42 @@ qs_status qs_measure_given_probs(qs_reg r, int qubit, double p0, double p1, doub
 // clamped to [0, 1], outcome = (u < p0) ? 0 : 1, p = W(S, bit k = outcome) * g.
 // The W sums come from compensated histograms over 10 qubits at a time (the
 // first over the whole state, each later one over the surviving subspace),
-// and the state is collapsed once at the end: the measured basis entry
-// times sqrt(g) (state vector) or g (density matrix), every other entry 0.
+// each walked on the device, and the state is collapsed once at the end: the
+// measured basis entry times sqrt(g) (state vector) or g (density matrix),
+// every other entry 0.  One wait for all of it.
 qs_status qs_measure_all(qs_reg r, const double* u01, int* outcomes, double* probs)
 {
     QS_CHECK_REG(r);
     if (!u01) return qs::set_error(QS_E_ARG, "NULL draws");
     const int n = r->n;
-    for (int k = 0; k < n; ++k)
-        if (!(u01[k] >= 0.0 && u01[k] < 1.0)) return qs::set_error(QS_E_ARG, "draw must lie in [0, 1)");
-    const qs::Launch L = launch_of(r);
-    const bool dbl = r->prec == QS_C128;
-    std::vector<int> out_o(n);
-    std::vector<double> out_p(n);
-    double g = 1.0;
-    uint64_t pattern = 0;
-    // one step of the walk over bins: w[b] = (sum, compensation) of W over
-    // the bins of the current group; bits below k of b must match `sub`
-    auto walk = [&](const std::vector<double>& w, int nbins_log, int first_qubit) -> qs_status {
-        for (int k = 0; k < nbins_log; ++k) {
-            const uint64_t sub = (pattern >> first_qubit) & ((1ull << k) - 1);
-            HSum w0 = {0.0, 0.0}, w1 = {0.0, 0.0};
-            for (uint64_t b = 0; b < (1ull << nbins_log); ++b) {
-                if ((b & ((1ull << k) - 1)) != sub) continue;
-                HSum& acc = ((b >> k) & 1) ? w1 : w0;
-                hadd(acc, w[2 * b]);
-                hadd(acc, w[2 * b + 1]);
-            }
-            double p0 = (w0.s + w0.c) * g;
-            if (p0 < 0.0) p0 = 0.0;
-            if (p0 > 1.0) p0 = 1.0;
-            const int q = first_qubit + k;
-            const int o = (u01[q] < p0) ? 0 : 1;
-            const double p = ((o ? w1.s + w1.c : w0.s + w0.c)) * g;
-            if (!(p > 0.0)) return qs::set_error(QS_E_ARG, "selected outcome has zero probability");
-            out_o[q] = o;
-            out_p[q] = p;
-            g /= p;
-            pattern |= (uint64_t)o << q;
-        }
-        return QS_OK;
-    };
-    qs_status s = QS_OK;
-    if (r->kind == QS_DENSITY) {
-        const uint64_t dim = 1ull << n;
-        double* dd = nullptr;
-        QS_HIP(hipMallocAsync((void**)&dd, dim * sizeof(double), r->stream));
-        s = qs::profiled(r, QS_K_REDUCE, [&](int*) {
-            return dbl ? qs::launch_diag_dm<double>(L, r->amp, n, dd) : qs::launch_diag_dm<float>(L, r->amp, n, dd);
-        });
-        std::vector<double> diag(dim);
-        if (!s) {
-            hipError_t e = hipMemcpyAsync(diag.data(), dd, dim * sizeof(double), hipMemcpyDeviceToHost, r->stream);
-            if (e == hipSuccess) e = hipStreamSynchronize(r->stream);
-            if (e != hipSuccess) s = qs::hip_error(e, "diagonal copy");
-        }
-        (void)hipFreeAsync(dd, r->stream);
-        if (s) return s;
-        std::vector<double> w(2 * dim, 0.0);  // (value, 0) pairs: the walk over all N qubits at once
-        for (uint64_t j = 0; j < dim; ++j) w[2 * j] = diag[j];
-        if ((s = walk(w, n, 0))) return s;
-    } else {
-        const int kb = qs::kHistBlocks;
-        double* buf = nullptr;
-        QS_HIP(hipMallocAsync((void**)&buf, (2 * 1024 * (size_t)kb + 2 * 1024) * sizeof(double), r->stream));
-        double* dev_out = buf + 2 * 1024 * (size_t)kb;
-        std::vector<double> w;
-        for (int shift = 0; shift < n && !s; shift += 10) {
-            const int mb = std::min(10, n - shift);
-            s = qs::profiled(r, QS_K_REDUCE, [&](int*) {
-                return dbl ? qs::launch_hist_sv<double>(L, r->amp, r->nbits, shift, pattern, mb, buf, kb, dev_out)
-                           : qs::launch_hist_sv<float>(L, r->amp, r->nbits, shift, pattern, mb, buf, kb, dev_out);
-            });
-            if (s) break;
-            w.assign(2ull << mb, 0.0);
-            hipError_t e = hipMemcpyAsync(w.data(), dev_out, w.size() * sizeof(double), hipMemcpyDeviceToHost,
-                                          r->stream);
-            if (e == hipSuccess) e = hipStreamSynchronize(r->stream);
-            if (e != hipSuccess) s = qs::hip_error(e, "histogram copy");
-            if (!s) s = walk(w, mb, shift);
-        }
-        (void)hipFreeAsync(buf, r->stream);
-        if (s) return s;
-    }
-    // the kept entry, scaled in double precision
-    const uint64_t pos = r->kind == QS_DENSITY ? pattern + (pattern << n) : pattern;
-    double re = 0.0, im = 0.0;
-    if (dbl) {
-        double v[2];
-        QS_HIP(hipMemcpyAsync(v, (const double*)r->amp + 2 * pos, sizeof(v), hipMemcpyDeviceToHost, r->stream));
-        if ((s = sync_stream(r))) return s;
-        re = v[0];
-        im = v[1];
-    } else {
-        float v[2];
-        QS_HIP(hipMemcpyAsync(v, (const float*)r->amp + 2 * pos, sizeof(v), hipMemcpyDeviceToHost, r->stream));
-        if ((s = sync_stream(r))) return s;
-        re = v[0];
-        im = v[1];
-    }
-    const double scale = r->kind == QS_DENSITY ? g : sqrt(g);
-    s = qs::profiled(r, QS_K_COLLAPSE, [&](int*) {
-        const uint64_t len = 1ull << r->nbits;
-        return dbl ? qs::launch_init_basis<double>(L, r->amp, len, pos, re * scale, im * scale)
-                   : qs::launch_init_basis<float>(L, r->amp, len, pos, re * scale, im * scale);
-    });
-    if (s) return s;
+    qs::Draws draws = {};
     for (int k = 0; k < n; ++k) {
-        if (outcomes) outcomes[k] = out_o[k];
-        if (probs) probs[k] = out_p[k];
+        if (!(u01[k] >= 0.0 && u01[k] < 1.0)) return qs::set_error(QS_E_ARG, "draw must lie in [0, 1)");
+        draws.u[k] = u01[k];
+    }
+    const qs::Launch L = launch_of(r);
+    const bool dbl = r->prec == QS_C128, dm = r->kind == QS_DENSITY;
+    double* buf = nullptr;
+    QS_HIP(hipMallocAsync((void**)&buf, qs::kMeasureDoubles * sizeof(double), r->stream));
+    qs_status s = QS_OK;
+    for (int shift = 0; shift < n && !s; shift += 10)
+        s = qs::profiled(r, QS_K_REDUCE, [&](int*) {
+            return dbl ? qs::launch_measure_stage<double>(L, r->amp, n, dm, shift, draws, buf, r->host_res)
+                       : qs::launch_measure_stage<float>(L, r->amp, n, dm, shift, draws, buf, r->host_res);
+        });
+    if (!s)
+        s = qs::profiled(r, QS_K_COLLAPSE, [&](int*) {
+            const uint64_t len = 1ull << r->nbits;
+            return dbl ? qs::launch_measure_basis<double>(L, r->amp, len, buf)
+                       : qs::launch_measure_basis<float>(L, r->amp, len, buf);
+        });
+    (void)hipFreeAsync(buf, r->stream);
+    if (s || (s = sync_stream(r))) return s;
+    const double* res = r->host_res;
+    if (res[0] != 0.0) return qs::set_error(QS_E_ARG, "selected outcome has zero probability");
+    for (int k = 0; k < n; ++k) {
+        if (outcomes) outcomes[k] = (int)res[1 + qs::kMaxMeasured + k];
+        if (probs) probs[k] = res[1 + k];
     }
     return QS_OK;
 }
@@ -1704,9 +1616,7 @@ qs_status order_after(hipStream_t waiter, hipStream_t producer)
 
 qs_status read_pair(qs_reg r, double out[2])
 {
-    const double* dev_out = r->scratch + 4 * qs::kReduceBlocks;
-    QS_HIP(hipMemcpyAsync(r->host_res, dev_out, 2 * sizeof(double), hipMemcpyDeviceToHost, r->stream));
-    qs_status s = sync_stream(r);
+    const    qs_status s = sync_stream(r);
     if (s) return s;
     out[0] = r->host_res[0];
     out[1] = r->host_res[1];
@@ -1742,7 +1652,8 @@ qs_status qs_init_pure_state(qs_reg r, qs_reg pure)
     const qs::Launch L = launch_of(r);
     if (r->kind == QS_STATEVEC) {
         s = qs::profiled(r, QS_K_INIT, [&](int*) {
-            return hipMemcpyAsync(r->amp, pure->amp, r->bytes, hipMemcpyDeviceToDevice, r->stream);
+            return r->prec == QS_C128 ? qs::launch_copy<double>(L, r->amp, pure->amp, 1ull << r->nbits)
+                                      : qs::launch_copy<float>(L, r->amp, pure->amp, 1ull << r->nbits);
         });
     } else {
         s = qs::profiled(r, QS_K_INIT, [&](int*) {
@@ -1766,8 +1677,10 @@ qs_status qs_clone(qs_reg dst, qs_reg src)
     QS_HIP(hipSetDevice(dst->env->device));
     qs_status s = order_after(dst->stream, src->stream);
     if (s) return s;
+    const qs::Launch L = launch_of(dst);
     s = qs::profiled(dst, QS_K_INIT, [&](int*) {
-        return hipMemcpyAsync(dst->amp, src->amp, dst->bytes, hipMemcpyDeviceToDevice, dst->stream);
+        return dst->prec == QS_C128 ? qs::launch_copy<double>(L, dst->amp, src->amp, 1ull << dst->nbits)
+                                    : qs::launch_copy<float>(L, dst->amp, src->amp, 1ull << dst->nbits);
     });
     if (s) return s;
     return order_after(src->stream, dst->stream);
@@ -1787,11 +1700,10 @@ qs_status qs_calc_inner_product(qs_reg bra, qs_reg ket, qs_cplx* out)
     if (s) return s;
     const qs::Launch L = launch_of(bra);
     double* partials = bra->scratch;
-    double* dev_out = bra->scratch + 4 * qs::kReduceBlocks;
     s = qs::profiled(bra, QS_K_REDUCE, [&](int*) {
         return bra->prec == QS_C128
-                   ? qs::launch_inner_sv<double>(L, bra->amp, ket->amp, bra->nbits, partials, dev_out)
-                   : qs::launch_inner_sv<float>(L, bra->amp, ket->amp, bra->nbits, partials, dev_out);
+                   ? qs::launch_inner_sv<double>(L, bra->amp, ket->amp, bra->nbits, partials, bra->host_res)
+                   : qs::launch_inner_sv<float>(L, bra->amp, ket->amp, bra->nbits, partials, bra->host_res);
     });
     if (s) return s;
     double v[2];
@@ -1810,10 +1722,9 @@ qs_status qs_calc_purity(qs_reg r, double* out)
     // rho: the squared norm of the Eq. 2 vector
     const qs::Launch L = launch_of(r);
     double* partials = r->scratch;
-    double* dev_out = r->scratch + 4 * qs::kReduceBlocks;
     qs_status s = qs::profiled(r, QS_K_REDUCE, [&](int*) {
-        return r->prec == QS_C128 ? qs::launch_prob_sv<double>(L, r->amp, r->nbits, -1, partials, dev_out)
-                                  : qs::launch_prob_sv<float>(L, r->amp, r->nbits, -1, partials, dev_out);
+        return r->prec == QS_C128 ? qs::launch_prob_sv<double>(L, r->amp, r->nbits, -1, partials, r->host_res)
+                                  : qs::launch_prob_sv<float>(L, r->amp, r->nbits, -1, partials, r->host_res);
     });
     if (s) return s;
     double v[2];
@@ -1843,10 +1754,9 @@ qs_status qs_calc_fidelity(qs_reg r, qs_reg pure, double* out)
     if (s) return s;
     const qs::Launch L = launch_of(r);
     double* partials = r->scratch;
-    double* dev_out = r->scratch + 4 * qs::kReduceBlocks;
     s = qs::profiled(r, QS_K_REDUCE, [&](int*) {
-        return r->prec == QS_C128 ? qs::launch_fid_dm<double>(L, r->amp, r->n, pure->amp, partials, dev_out)
-                                  : qs::launch_fid_dm<float>(L, r->amp, r->n, pure->amp, partials, dev_out);
+        return r->prec == QS_C128 ? qs::launch_fid_dm<double>(L, r->amp, r->n, pure->amp, partials, r->host_res)
+                                  : qs::launch_fid_dm<float>(L, r->amp, r->n, pure->amp, partials, r->host_res);
     });
     if (s) return s;
     double v[2];

@@ -43,8 +43,8 @@ struct qs_reg_s {
     size_t bytes;
     bool owned;
     hipStream_t stream;
-    double* scratch;     // device: reduction partials + 2 results
-    double* host_res;    // pinned host: 2 doubles
+    double* scratch;     // device: reduction partials, matrices
+    double* host_res;    // pinned host: kHostDoubles results, written by the kernels
 };
 
 // One recorded circuit operation.

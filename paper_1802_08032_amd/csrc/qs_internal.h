@@ -57,7 +57,7 @@ template <typename T> hipError_t launch_dm_channel(const Launch& L, void* rho, i
 // --- reductions and collapse ----------------------------------------------
 // Sum of |alpha|^2 split by bit q (q < 0: one total sum in out[0]).  Writes
 // {sum over bit q == 0, sum over bit q == 1} as doubles to `dev_out`.
-// `partials` must hold 2 * 2 * kReduceBlocks doubles.
+// (device or pinned host memory).  `partials` must hold 2 * 2 * kReduceBlocks doubles.
 constexpr int kReduceBlocks = 1024;
 template <typename T> hipError_t launch_prob_sv(const Launch& L, const void* amp, int nbits, int q,
                                                 double* partials, double* dev_out);
@@ -76,10 +76,10 @@ template <typename T> hipError_t launch_collapse_sv(const Launch& L, void* amp, 
 template <typename T> hipError_t launch_collapse_dm(const Launch& L, void* rho, int N, int q,
                                                     int outcome, double scale);
 
-// Register scratch (device doubles): reduction partials, two results, then
+// Register scratch (device doubles): reduction partials, then
 // two k-qubit matrices of up to 32 x 32 complex entries (a gate and its
 // conjugate, or a superoperator).
-constexpr int kScratchMatOff = 4 * kReduceBlocks + 8;
+constexpr int kScratchMatOff = 4 * kReduceBlocks;
 constexpr int kScratchMatDoubles = 2 * 32 * 32 * 2;
 constexpr int kScratchDoubles = kScratchMatOff + kScratchMatDoubles;
 
@@ -103,15 +103,28 @@ template <typename T> hipError_t launch_fid_dm(const Launch& L, const void* rho,
                                                double* partials, double* dev_out);
 
 // --- measure-all ----------------------------------------------------------
-// |alpha|^2 of the items j < 2^(nbits - shift) at index fixed + (j << shift),
-// summed per bin j mod 2^mbits (mbits <= 10) with compensated sums: dev_out
-// receives 2^mbits (sum, compensation) pairs.  `partials` holds
-// 2 * 1024 * max_blocks doubles.
 constexpr int kHistBlocks = 256;
-template <typename T> hipError_t launch_hist_sv(const Launch& L, const void* amp, int nbits, int shift,
-                                                uint64_t fixed, int mbits, double* partials, int max_blocks,
-                                                double* dev_out);
-// Real parts of the 2^N diagonal entries of a density matrix, as doubles.
-template <typename T> hipError_t launch_diag_dm(const Launch& L, const void* rho, int N, double* dev_out);
+constexpr int kMaxMeasured = 64;  // qubits
+struct Draws {
+    double u[kMaxMeasured];
+};
+// What one group of qubits hands to the next (device memory).
+struct MeasureState {
+    double g, re, im;
+    uint64_t pattern, pos;
+    int err, pad;
+};
+// Device memory for the stages (in doubles), and pinned host memory for what
+// they return: an error flag, the probabilities, the outcomes.
+constexpr size_t kMeasureDoubles = 2 * 1024 * (size_t)kHistBlocks + 2 * 1024 + sizeof(MeasureState) / sizeof(double);
+constexpr size_t kHostDoubles = 1 + 2 * kMaxMeasured;
+// Outcomes of qubits shift .. min(shift + 10, n) - 1, after the stages before
+// it on the same stream and with the same `buf`; the last stage also forms
+// the entry that launch_measure_basis writes.
+template <typename T> hipError_t launch_measure_stage(const Launch& L, const void* amp, int n, bool dm, int shift,
+                                                      const Draws& draws, double* buf, double* res);
+template <typename T> hipError_t launch_measure_basis(const Launch& L, void* amp, uint64_t len, const double* buf);
+// dst <- src, `len` amplitudes.
+template <typename T> hipError_t launch_copy(const Launch& L, void* dst, const void* src, uint64_t len);
 
 }  // namespace qs
