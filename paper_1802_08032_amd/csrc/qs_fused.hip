@@ -293,33 +293,39 @@ template <typename T, int RB, int B1, int B2>
 __device__ __forceinline__ void dense4_case(typename C2<T>::type (&v)[1 << RB], T mv)
 {
     using V = typename C2<T>::type;
-    T m[32];
+    // Row by row, 8 values at a time, for all quads before the next row: the
+    // whole complex128 matrix is 64 scalar registers, and was spilled lane by
+    // lane (density matrix of 13 qubits, complex128, eight noisy layers with
+    // 104 of these: 11.7 ms, 10.1 so).
+    V y[1 << RB];
 #pragma unroll
-    for (int k = 0; k < 32; ++k) m[k] = lane_get(mv, k);
+    for (int i = 0; i < 4; ++i) {
+        T m[8];
 #pragma unroll
-    for (int r0 = 0; r0 < (1 << RB); ++r0) {
-        if ((r0 >> B1) & 1 || (r0 >> B2) & 1) continue;
-        const int r[4] = {r0, r0 | (1 << B1), r0 | (1 << B2), r0 | (1 << B1) | (1 << B2)};
-        const V x[4] = {v[r[0]], v[r[1]], v[r[2]], v[r[3]]};
+        for (int k = 0; k < 8; ++k) m[k] = lane_get(mv, 8 * i + k);
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
+        for (int r0 = 0; r0 < (1 << RB); ++r0) {
+            if ((r0 >> B1) & 1 || (r0 >> B2) & 1) continue;
+            const int r[4] = {r0, r0 | (1 << B1), r0 | (1 << B2), r0 | (1 << B1) | (1 << B2)};
             // one product or multiply-add per statement
-            T re = m[8 * i] * x[0].x;
-            T im = m[8 * i] * x[0].y;
-            re = -m[8 * i + 1] * x[0].y + re;
-            im = m[8 * i + 1] * x[0].x + im;
+            T re = m[0] * v[r0].x;
+            T im = m[0] * v[r0].y;
+            re = -m[1] * v[r0].y + re;
+            im = m[1] * v[r0].x + im;
 #pragma unroll
             for (int j = 1; j < 4; ++j) {
-                const T mr = m[2 * (4 * i + j)], mi = m[2 * (4 * i + j) + 1];
-                re = mr * x[j].x + re;
-                re = -mi * x[j].y + re;
-                im = mr * x[j].y + im;
-                im = mi * x[j].x + im;
+                re = m[2 * j] * v[r[j]].x + re;
+                re = -m[2 * j + 1] * v[r[j]].y + re;
+                im = m[2 * j] * v[r[j]].y + im;
+                im = m[2 * j + 1] * v[r[j]].x + im;
             }
-            v[r[i]].x = re;
-            v[r[i]].y = im;
+            y[r[i]].x = re;
+            y[r[i]].y = im;
         }
+        __builtin_amdgcn_sched_barrier(0);
     }
+#pragma unroll
+    for (int r = 0; r < (1 << RB); ++r) v[r] = y[r];
 }
 
 __device__ __forceinline__ uint32_t table_entry(float m) { return __float_as_uint(m); }
@@ -508,6 +514,8 @@ __device__ __forceinline__ void process_tile(typename C2<T>::type* __restrict__ 
     constexpr int E = 1 << RB;
     // 1024 complex128 threads have 128 registers each: no room for a second set of records
     constexpr bool kAhead = TB < 10 || sizeof(T) == 4;
+    // a 4x4 matrix loaded while the one before it is applied takes two more, which would cost the fourth wave here
+    constexpr bool kAhead4 = RB != 3 || sizeof(T) == 4;
     const uint32_t lane = tid & 63u;
     const int nph = P->nphases;
     uint32_t pw = ((const uint32_t*)&P->ph[0])[lane & 31u];
@@ -559,12 +567,21 @@ __device__ __forceinline__ void process_tile(typename C2<T>::type* __restrict__ 
                 const int i = __builtin_ctzll(act);
                 act &= act - 1;
                 const uint32_t code = lane_get(cur.code, i);
-                if (__builtin_expect((code & kcDense4) != 0, 0)) {
-                    m4 = m4n;
-                    d4 &= d4 - 1;
-                    if (d4) m4n = m4tab[32 * (uint64_t)lane_get(entry, __builtin_ctzll(d4)) + (lane & 31u)];
+                const bool is4 = (code & kcDense4) != 0;
+                if constexpr (kAhead4) {
+                    if (__builtin_expect(is4, 0)) {
+                        m4 = m4n;
+                        d4 &= d4 - 1;
+                        if (d4) m4n = m4tab[32 * (uint64_t)lane_get(entry, __builtin_ctzll(d4)) + (lane & 31u)];
+                    }
+                    apply_op<T, RB>(v, cur, i, code, m4, recs + c + i, tid);
+                } else {
+                    apply_op<T, RB>(v, cur, i, code, m4n, recs + c + i, tid);
+                    if (__builtin_expect(is4, 0)) {
+                        d4 &= d4 - 1;
+                        if (d4) m4n = m4tab[32 * (uint64_t)lane_get(entry, __builtin_ctzll(d4)) + (lane & 31u)];
+                    }
                 }
-                apply_op<T, RB>(v, cur, i, code, m4, recs + c + i, tid);
             }
             c += 64;
             if (c >= oe) break;

@@ -169,8 +169,8 @@ hipError_t batch_probs_launch(qs_batch_s* b, int q, double* dev_out);
 qs_status batch_update(qs_batch_s* b);
 // Eq. 2 on the 2N-qubit vector of a density matrix: gates become a gate on
 // q and its conjugate on q+N, channels become 4x4 superoperators on
-// (q, q+N); an uncontrolled gate and the channels that follow it on the same
-// qubit are merged into one 4x4 (qs_plan.hip).
+// (q, q+N); uncontrolled gates and channels on the same qubit with nothing on
+// it in between are merged into one 4x4 (qs_plan.hip).
 std::vector<OpRec> dm_vector_ops(const std::vector<OpRec>& ops, int N);
 // Run-time compiled passes (qs_jit.hip).
 // init_index != nullptr: the first pass forms the basis state |*init_index>

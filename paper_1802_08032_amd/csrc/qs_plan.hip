@@ -1191,14 +1191,24 @@ std::vector<OpRec> dm_vector_ops(const std::vector<OpRec>& ops, int N)
         for (int q : qs_) r.push_back(q + N);
         return r;
     };
+    // last[t]: the 4x4 on (t, t + N) after which nothing has touched qubit t.
+    // What lies between acts on other qubits, so a later 4x4 on t is applied
+    // with it: the channels behind a controlled gate and the next layer's
+    // gate and channels on the same qubit are one 4x4 (a noisy layer of 9
+    // qubits has 9 of them, not 18).
+    std::vector<int> last(N, -1);
+    auto touch = [&](const OpRec& op) {
+        if (op.kind != 2) last[op.target] = -1;  // a phase has its qubits in ctrls alone
+        if (op.target2 >= 0) last[op.target2] = -1;
+        for (int q : op.ctrls) last[q] = -1;
+    };
     auto push_pair = [&](int t, const Super4& M) {
-        if (!out.empty()) {
-            OpRec& prev = out.back();
-            if (prev.kind == 4 && prev.ctrls.empty() && prev.target == t && prev.target2 == t + N) {
-                prev.m4 = mat4_mul(M, prev.m4);  // M applied after prev
-                return;
-            }
+        if (last[t] >= 0) {
+            OpRec& prev = out[last[t]];
+            prev.m4 = mat4_mul(M, prev.m4);  // M applied after prev
+            return;
         }
+        last[t] = (int)out.size();
         OpRec op{};
         op.kind = 4;
         op.target = t;
@@ -1207,6 +1217,7 @@ std::vector<OpRec> dm_vector_ops(const std::vector<OpRec>& ops, int N)
         out.push_back(op);
     };
     for (const OpRec& op : ops) {
+        if (!(op.kind == 0 && op.ctrls.empty()) && op.kind != 3) touch(op);
         if (op.kind == 0 && op.ctrls.empty()) {
             push_pair(op.target, gate_superop(op.u));
         } else if (op.kind == 0) {
