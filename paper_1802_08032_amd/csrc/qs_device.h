@@ -75,28 +75,23 @@ inline int grid_for(uint64_t items, int items_per_thread)
     return (int)blocks;
 }
 
-// Insert the bits listed in `b` (ascending final positions) into i; the
-// inserted bits take the values of b.ones.
-__device__ __forceinline__ uint64_t expand(uint64_t i, const BitInsert& b)
-{
-    for (int k = 0; k < b.count; ++k) {
-        const int p = b.pos[k];
-        const uint64_t lo = i & ((1ull << p) - 1ull);
-        i = ((i >> p) << (p + 1)) | lo;
-    }
-    return i | b.ones;
-}
-
-// expand() without the ones.  The inserted bits split no bit of i, so the
-// images of disjoint parts of an index add up: a kernel deposits the thread's
-// part once and the uniform parts with scalar instructions.
+// Insert zeros at the positions of b.at into i.  The inserted bits split no
+// bit of i, so the images of disjoint parts of an index add up: a kernel
+// deposits the thread's part once and the uniform parts with scalar
+// instructions.
 __device__ __forceinline__ uint64_t deposit(uint64_t i, const BitInsert& b)
 {
-    for (int k = 0; k < b.count; ++k) {
-        const int p = b.pos[k];
-        i = ((i >> p) << (p + 1)) | (i & ((1ull << p) - 1ull));
+    for (uint64_t at = b.at; at; at &= at - 1) {
+        const uint64_t high = i & ~((at & -at) - 1);
+        i += high;  // doubles what lies at or above the position
     }
     return i;
+}
+
+// The same with b.ones in the inserted bits.
+__device__ __forceinline__ uint64_t expand(uint64_t i, const BitInsert& b)
+{
+    return deposit(i, b) | b.ones;
 }
 
 // Where the items of a step sit after deposit().  Item j of a step is base +

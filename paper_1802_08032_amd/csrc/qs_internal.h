@@ -10,12 +10,13 @@
 
 namespace qs {
 
-// Up to 64 bit positions to insert into a compact loop index, ascending.
-// After insertion the bits in `ones` are set (controls), the rest are 0.
+// Bits to insert into a compact loop index, at the positions set in `at`.
+// After insertion the bits in `ones` are set (controls), the rest are 0.  Two
+// words: as a list of positions the kernels read them one after the other
+// through the scalar cache before they could form an address, which the
+// smallest registers saw.
 struct BitInsert {
-    int count;
-    int pos[63];
-    uint64_t ones;
+    uint64_t at, ones;
 };
 
 // 2x2 complex matrix, row-major, real/imag interleaved.
