@@ -1071,8 +1071,8 @@ __global__ __launch_bounds__(kBlock) void k_group_gate(typename C2<T>::type* __r
 // the register, and a lane gets the members of the other lanes of its group by
 // cross-lane reads.  Loads and stores stay whole lines; with one group per
 // thread each load of a wave touched 64 lines (k = 3 on qubits 0, 1, 2 of 25
-// in complex128: 1,535 us against 190 on high qubits).  `ins` inserts a 0 at
-// the targets of at least a line and a 1 at the high controls.
+// in complex128: 1,535 us against 190 on high qubits; 192 so).  `ins` inserts a
+// 0 at the targets of at least a line and a 1 at the high controls.
 template <typename T, int K, int L, int P>
 __global__ __launch_bounds__(kBlock) void k_group_lane(typename C2<T>::type* __restrict__ amp, uint64_t nitems,
                                                        BitInsert ins, GroupBits<K> gb, uint64_t lowmask,
@@ -1177,7 +1177,8 @@ __global__ __launch_bounds__(kBlock) void k_group_lane(typename C2<T>::type* __r
 //
 // One thread per group held 2^k amplitudes and waited for the matrix row by
 // row: k = 5 on 25 qubits in complex128 took 620 us on high qubits and 1,414
-// us on qubits 0..4; memory alone needs about 180 us, the multiply-adds 110.
+// us on qubits 0..4, so 207 and 217; memory alone needs about 180 us, the
+// multiply-adds 110.
 typedef double Acc64 __attribute__((ext_vector_type(4)));
 typedef float Acc32 __attribute__((ext_vector_type(4)));
 template <typename T> struct MfmaAcc;
