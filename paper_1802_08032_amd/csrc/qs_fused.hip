@@ -824,8 +824,9 @@ FOp encode_op(const OpRec& op, const PassPlan& P, const Layout& L)
 // Diagonal factors deferred by the lowering (see lower_passes): the true
 // state is gsc times prod_q exp(i phi[q] x_q) over the qubits with has[q],
 // times the stored state.  Which qubits carry a factor, and whether gsc was
-// touched, depends only on the op structure, not on matrix values, so a
-// circuit with new parameters lowers to the same number of ops.
+// touched, depends only on the op structure, with one exception: a gate off
+// from unitary by more than 1e-14 (core_form -1) defers nothing, so a controlled
+// gate behind it needs no phase multiplied in first and its phase has an op less.
 struct Defer {
     double phi[64] = {};
     bool has[64] = {};
@@ -1646,10 +1647,12 @@ qs_status batch_build(qs_batch_s* b, const std::vector<qs_reg>& regs,
 
 qs_status batch_update(qs_batch_s* b)
 {
-    // lower every register's plan again with the circuits' current values:
-    // the structure (and so the slots of its ops) is unchanged; the kernel
-    // data (matrices, core coefficients, deferred phases) and the ends of the
-    // phases' op ranges follow the parameters
+    // lower every register's plan again with the circuits' current values: the
+    // passes and the number of ops are unchanged; the kernel data (matrices,
+    // core coefficients, deferred phases) and the phases' op ranges follow the
+    // parameters.  Both ends of a range move: two gates of different phases that
+    // trade forms (see Defer) leave the number of ops as it is and the phases
+    // between them one slot off.
     const size_t rsz = b->prec == QS_C128 ? sizeof(FRec<double>) : sizeof(FRec<float>);
     FPass* passes = (FPass*)(b->host_plan.data() + b->off_passes);
     for (size_t i = 0; i < b->regs.size(); ++i) {
@@ -1665,9 +1668,11 @@ qs_status batch_update(qs_batch_s* b)
         const std::vector<char> recs = rec_bytes(hp, hops, b->prec);
         memcpy(b->host_ops.data() + b->reg_op_begin[i] * rsz, recs.data(), hops.size() * rsz);
         for (size_t p = 0; p < hp.size(); ++p)
-            for (int ph = 0; ph < hp[p].nphases; ++ph)
-                passes[b->reg_pass_begin[i] + p].ph[ph].op_end =
-                    (uint32_t)b->reg_op_begin[i] + hp[p].ph[ph].op_end;
+            for (int ph = 0; ph < hp[p].nphases; ++ph) {
+                FPhase& F = passes[b->reg_pass_begin[i] + p].ph[ph];
+                F.op_begin = (uint32_t)b->reg_op_begin[i] + hp[p].ph[ph].op_begin;
+                F.op_end = (uint32_t)b->reg_op_begin[i] + hp[p].ph[ph].op_end;
+            }
         std::copy(m4.begin(), m4.end(), b->host_m4.begin() + b->reg_m4_begin[i]);
     }
     // from pageable memory the copies have left the host tables when the
