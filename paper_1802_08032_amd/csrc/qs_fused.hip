@@ -93,7 +93,7 @@ struct alignas(16) FRec {
 //   kNotM, sub rb      NOT with any register and thread-bit controls
 //   kPhase, sub        phase m[0] + i m[1]: sub 0 no register bit, 1 + b where bit b is 1,
 //                      6 + pair where both are 1, 16 any rmask; thread-bit controls in tmask
-//   kSign, sub         the phase -1, subs as kPhase
+//   kSign, sub         the phase of an angle of pi or -pi: a sign, subs as kPhase up to 15
 //   kDense4, sub pair  4x4 on register bits, matrix in the 4x4 table
 //   kOther, sub rb     dense 2x2 with any controls; sub 8 + rb: a diagonal one;
 //                      sub 16: nothing (a gate whose effect is deferred)
@@ -105,8 +105,16 @@ enum : int {
 };
 // Class bits of the device code.
 enum : uint32_t {
-    kcCore = 1, kcNot = 2, kcPhase = 4, kcSign = 8, kcRare = 16, kcNotM = 32, kcDense4 = 64, kcOther = 128, kcLane = 256
+    kcCore = 1, kcNot = 2, kcPhase = 4, kcSign = 8, kcRare = 16, kcNotM = 32, kcDense4 = 64, kcOther = 128, kcLane = 256,
+    kcBack = 512  // its signs are of -pi, not pi
 };
+// sin of the double next to pi: what exp(i pi) and exp(-i pi) have beside -1.
+// That is a whole unit in the last place of complex128, and the same way for
+// every CZ of a circuit: left out, 16 layers with a CZ ladder on 12 qubits are
+// off by 5.4e-15 instead of 2.4e-15, 400 CZs by 1.4e-14 instead of 1.8e-15.
+// A sign of complex128 therefore brings its turn, i k sin pi for k half turns;
+// complex64 does not see it.
+constexpr double kSinPi = 1.2246467991473532e-16;
 
 constexpr uint32_t kPhAny = 1u << 15, kPhAll = 1u << 16;
 
@@ -250,14 +258,18 @@ __device__ __forceinline__ void phase_case(typename C2<T>::type (&v)[1 << RB], T
         }
 }
 
+// Exchange the signs that `s` has set in the registers whose index has every
+// bit of MASK set and, in complex128, multiply them by 1 - i r (r^2 far below
+// an ulp).
 template <typename T, int RB, uint32_t MASK>
-__device__ __forceinline__ void sign_case(typename C2<T>::type (&v)[1 << RB], uint32_t s)
+__device__ __forceinline__ void sign_case(typename C2<T>::type (&v)[1 << RB], uint32_t s, T r)
 {
 #pragma unroll
-    for (int r = 0; r < (1 << RB); ++r)
-        if (((uint32_t)r & MASK) == MASK) {
-            v[r].x = flip_sign(v[r].x, s);
-            v[r].y = flip_sign(v[r].y, s);
+    for (int k = 0; k < (1 << RB); ++k)
+        if (((uint32_t)k & MASK) == MASK) {
+            const T x = flip_sign(v[k].x, s), y = flip_sign(v[k].y, s);
+            v[k].x = sizeof(T) == 8 ? fma(r, y, x) : x;
+            v[k].y = sizeof(T) == 8 ? fma(-r, x, y) : y;
         }
 }
 
@@ -391,16 +403,19 @@ __device__ __forceinline__ void apply_op(typename C2<T>::type (&v)[1 << RB], con
     }
     QS_IF(code, kcSign) {
         const uint32_t tmask = code >> 16;
-        const uint32_t s = (tid & tmask) == tmask ? 0x80000000u : 0u;
+        const bool sel = (tid & tmask) == tmask;
+        const uint32_t s = sel ? 0x80000000u : 0u;
+        const T r = (T)(!sel ? 0.0 : (code & kcBack) ? -kSinPi : kSinPi);
         QS_IF(multi, 31u << 15) {
-#define QS_P(B) if constexpr (RB > B) { QS_IF(multi, (1u << 15) << B) sign_case<T, RB, 1u << B>(v, s); }
+#define QS_P(B) if constexpr (RB > B) { QS_IF(multi, (1u << 15) << B) sign_case<T, RB, 1u << B>(v, s, r); }
             QS_P(0) QS_P(1) QS_P(2) QS_P(3) QS_P(4)
 #undef QS_P
         }
         QS_IF(multi, 1023u << 20) {
 #define QS_P(P)                                                                                        \
     if constexpr (RB > kPairB2[P]) {                                                                   \
-        QS_IF(multi, (1u << 20) << P) sign_case<T, RB, (1u << kPairB1[P]) | (1u << kPairB2[P])>(v, s); \
+        QS_IF(multi, (1u << 20) << P)                                                                  \
+            sign_case<T, RB, (1u << kPairB1[P]) | (1u << kPairB2[P])>(v, s, r);                        \
     }
             QS_P(0) QS_P(1) QS_P(2) QS_P(3) QS_P(4) QS_P(5) QS_P(6) QS_P(7) QS_P(8) QS_P(9)
 #undef QS_P
@@ -551,12 +566,15 @@ __device__ __forceinline__ void process_tile(typename C2<T>::type* __restrict__ 
             act ^= lanes;
             if (lanes) {
                 uint32_t s = 0;
+                int turns = 0;  // complex128
                 while (lanes) {
-                    const uint32_t tmask = lane_get(cur.code, __builtin_ctzll(lanes)) >> 16;
+                    const uint32_t code = lane_get(cur.code, __builtin_ctzll(lanes)), tmask = code >> 16;
                     lanes &= lanes - 1;
-                    s ^= (tid & tmask) == tmask ? 0x80000000u : 0u;
+                    const bool sel = (tid & tmask) == tmask;
+                    s ^= sel ? 0x80000000u : 0u;
+                    turns += !sel ? 0 : (code & kcBack) ? -1 : 1;
                 }
-                sign_case<T, RB, 0>(v, s);
+                sign_case<T, RB, 0>(v, s, (T)(kSinPi * turns));
             }
             // the next 4x4 matrix, one value per lane, loaded ahead
             uint64_t d4 = act & __ballot((cur.code & kcDense4) != 0);
@@ -771,8 +789,7 @@ FOp phase_fop(uint32_t rmask, uint32_t tmask, uint64_t gmask, Cx f)
     FOp o;
     memset(&o, 0, sizeof(o));
     const int sub = phase_sub(rmask);
-    // e^(i pi) in double is (-1, 1.2e-16): a sign to within half a unit in the last place
-    const bool sign = f.real() == -1.0 && fabs(f.imag()) < 1.5e-16 && sub < 16;
+    const bool sign = f.real() == -1.0 && fabs(fabs(f.imag()) - kSinPi) < 1e-18 && sub < 16;
     o.kind = (sign ? kSign : kPhase) + sub;
     o.rmask = rmask;
     o.tmask = tmask;
@@ -1226,7 +1243,9 @@ namespace {
 // on other register bits, cores and phases keep their order.  Ops with
 // thread-bit or outside controls, 4x4s and controlled dense gates stand alone.
 // Signs on thread and outside bits alone (sub 0) commute with everything
-// inside a lane and come first.
+// inside a lane and come first.  In complex128 a sign rounds (its turn), but no
+// less where it stands than where it was; the signs of a record are of pi or
+// all of -pi, and none is there twice.
 template <typename T>
 uint32_t bundle(const FOp* ops, uint32_t count, FRec<T>* out)
 {
@@ -1235,6 +1254,7 @@ uint32_t bundle(const FOp* ops, uint32_t count, FRec<T>* out)
     auto put = [&](int at, const FOp& f, int count_m) {
         for (int k = 0; k < count_m; ++k) out[n - 1].m[at + k] = (T)f.m[k];
     };
+    auto back = [](const FOp& f) { return f.m[1] < 0.0 ? (uint32_t)kcBack : 0u; };
     auto fresh = [&](bool joinable) {
         memset(&out[n], 0, sizeof(out[n]));
         ++n;
@@ -1246,7 +1266,7 @@ uint32_t bundle(const FOp* ops, uint32_t count, FRec<T>* out)
         const FOp& f = ops[k];
         if (f.kind != kSign) continue;
         fresh(false);
-        out[n - 1].code = kcLane | f.tmask << 16;
+        out[n - 1].code = kcLane | back(f) | f.tmask << 16;
         out[n - 1].gmask = f.gmask;
     }
     open = false;
@@ -1285,10 +1305,12 @@ uint32_t bundle(const FOp* ops, uint32_t count, FRec<T>* out)
             put(10, f, 2);
             phase = true;
         } else if (plain && cls == kSign) {
-            if (!open) fresh(true);
+            const uint32_t bit = (1u << 15) << (sub - 1);
+            const bool other = sign_bits && (out[n - 1].code & kcBack) != back(f);
+            if (!open || (sizeof(T) == 8 && (other || (out[n - 1].multi & bit)))) fresh(true);
             FRec<T>& r = out[n - 1];
-            r.code |= kcSign;
-            r.multi ^= (1u << 15) << (sub - 1);  // the same sign twice is none
+            r.code |= kcSign | back(f);
+            r.multi ^= bit;  // in complex64 the same sign twice is none
             sign_bits |= f.rmask;
         } else {
             fresh(false);
@@ -1310,7 +1332,7 @@ uint32_t bundle(const FOp* ops, uint32_t count, FRec<T>* out)
                 put(10, f, 2);
                 break;
             case kSign:
-                r.code |= kcSign;
+                r.code |= kcSign | back(f);
                 r.multi |= (1u << 15) << (sub - 1);
                 break;
             case kDense4:
