@@ -92,6 +92,10 @@ constexpr int kScratchDoubles = kScratchMatOff + kScratchMatDoubles;
 template <typename T> hipError_t launch_group_gate(const Launch& L, void* amp, int nbits, const int* targets,
                                                    int k, const int* ctrls, int nc, const std::complex<double>* m,
                                                    T* dev_m);
+// rho <- U rho U^dagger, U = m on two targets (4 x 4, as above): U on the rows
+// and conj(U) on the columns.
+template <typename T> hipError_t launch_dm_two(const Launch& L, void* rho, int N, const int* targets,
+                                               const std::complex<double>* m);
 // Every amplitude set to (re, im).  Write-only.
 template <typename T> hipError_t launch_init_fill(const Launch& L, void* amp, uint64_t len, double re, double im);
 // rho = |psi><psi| in the Eq. 2 layout; psi holds 2^N amplitudes.

@@ -1274,6 +1274,98 @@ __global__ __launch_bounds__(kBlock, 2) void k_group_mfma(typename C2<T>::type* 
     }
 }
 
+// U on two qubits of a density matrix: U on the row bits, then conj(U) on the
+// column bits, in one pass.  Lanes and members as in k_group_mfma: q are the row
+// bits and s the column bits, so the rows are a product of the matrix cores with
+// U on the diagonal blocks (the zeros add nothing), and the columns one within
+// the lane.  As one 16 x 16 product conj(U) (x) U every entry was rounded once
+// more and the sums were four times as long: error of a random U on 7 qubits
+// 1.67e-16 in complex128 and 8.55e-8 in complex64, 1.28e-16 and 7.81e-8 so (two
+// passes: 1.39e-16 and 8.37e-8).  Both row bits select lanes, so a load covers
+// whole lines wherever the targets lie, and is non-temporal.  Bound by HBM: 13
+// qubits 370 to 393 us in complex128 (5.5 to 5.8 TB/s), 186 to 189 in complex64;
+// the 16 x 16 product took 386 to 418 and 202 to 215.
+template <typename T>
+__global__ __launch_bounds__(kBlock, 2) void k_dm_two(typename C2<T>::type* __restrict__ rho, uint64_t ngroups,
+                                                      BitInsert ins, GroupBits<4> gb, MatK<T, 2> u)
+{
+    using V = typename C2<T>::type;
+    using Acc = typename MfmaAcc<T>::type;
+    const int lane = threadIdx.x & 63, g = lane & 15, q = lane >> 4;
+    T ur[4], ui[4];
+    const int row = sizeof(T) == 8 ? g : 4 * (g & 3) + (g >> 2);
+    const T er = u.m[2 * (4 * (row & 3) + q)], ei = u.m[2 * (4 * (row & 3) + q) + 1];
+#pragma unroll
+    for (int s = 0; s < 4; ++s) {
+        ur[s] = row >> 2 == s ? er : T(0);
+        ui[s] = row >> 2 == s ? ei : T(0);
+    }
+    uint64_t off[4];
+#pragma unroll
+    for (int s = 0; s < 4; ++s) off[s] = group_off<4>(gb, 4 * s);
+    const bool on = (uint64_t)g < ngroups;  // a register of fewer than 16 groups is one set
+    const uint64_t le = deposit(on ? g : 0, ins) + ((q & 1) ? gb.tbit[0] : 0) + ((q & 2) ? gb.tbit[1] : 0);
+    const uint64_t nsets = (ngroups + 15) / 16, nw = (uint64_t)gridDim.x * (kBlock / 64);
+    uint64_t set = (uint64_t)blockIdx.x * (kBlock / 64) + (uint64_t)__builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    if (set >= nsets) return;
+    uint64_t e = le + deposit(set * 16, ins);
+    V x[4];
+#pragma unroll
+    for (int s = 0; s < 4; ++s) x[s] = ldnt(rho + e + off[s]);
+    for (;;) {
+        // the next set's entries, in flight during the products
+        const uint64_t next = set + nw;
+        uint64_t ne = e;
+        V nx[4];
+#pragma unroll
+        for (int s = 0; s < 4; ++s) nx[s] = x[s];
+        if (next < nsets) {
+            ne = le + deposit(next * 16, ins);
+#pragma unroll
+            for (int s = 0; s < 4; ++s) nx[s] = ldnt(rho + ne + off[s]);
+        }
+        Acc re = {T(0), T(0), T(0), T(0)}, im = re, re2 = re, im2 = re;
+#pragma unroll
+        for (int s = 0; s < 4; ++s) {
+            re = mfma(ur[s], x[s].x, re);
+            im = mfma(ur[s], x[s].y, im);
+            re2 = mfma(ui[s], x[s].y, re2);
+            im2 = mfma(ui[s], x[s].x, im2);
+        }
+#pragma unroll
+        for (int s = 0; s < 4; ++s) {
+            x[s].x = re[s] - re2[s];
+            x[s].y = im[s] + im2[s];
+        }
+        V y[4];
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+            // products with the real and with the imaginary parts of conj(U)
+            const T* w = u.m + 8 * c;
+            T yx = w[0] * x[0].x, yy = w[0] * x[0].y, zx = w[1] * x[0].y, zy = w[1] * x[0].x;
+#pragma unroll
+            for (int s = 1; s < 4; ++s) {
+                yx = w[2 * s] * x[s].x + yx;
+                yy = w[2 * s] * x[s].y + yy;
+                zx = w[2 * s + 1] * x[s].y + zx;
+                zy = w[2 * s + 1] * x[s].x + zy;
+            }
+            y[c].x = yx + zx;
+            y[c].y = yy - zy;
+        }
+        __builtin_amdgcn_sched_barrier(0);  // the four stores of a set together
+        if (on) {
+#pragma unroll
+            for (int c = 0; c < 4; ++c) stnt(rho + e + off[c], y[c]);
+        }
+        if (next >= nsets) return;
+        set = next;
+        e = ne;
+#pragma unroll
+        for (int s = 0; s < 4; ++s) x[s] = nx[s];
+    }
+}
+
 // ---------------------------------------------------------------------------
 // Every amplitude set to (re, im).  Write-only.
 template <typename T, int U>
@@ -1908,6 +2000,10 @@ static hipError_t group_small(const Launch& L, void* amp, int nbits, const int* 
     return hipGetLastError();
 }
 
+// Two blocks per CU: as fast as more in complex128, faster in complex64 (k = 5
+// on 25 qubits 118 us; with four 150).
+constexpr uint64_t kMfmaGrid = 256 * 2;
+
 template <typename T, int K>
 static hipError_t group_mfma(const Launch& L, void* amp, int nbits, const int* targets, const int* ctrls, int nc,
                              const std::complex<double>* m, T* dev_m)
@@ -1938,16 +2034,30 @@ static hipError_t group_mfma(const Launch& L, void* amp, int nbits, const int* t
     const BitInsert ins = make_insert(pos, np, ones);
     const uint64_t ngroups = 1ull << (nbits - np);
     const uint64_t blocks = (ngroups + 63) / 64;  // four waves of 16 groups
-    // two blocks per CU: as fast as more in complex128, faster in complex64
-    // (k = 5 on 25 qubits 118 us; with four 150)
-    const uint64_t most = 256 * 2;
-    const dim3 grid((unsigned)std::min(blocks, most));
+    const dim3 grid((unsigned)std::min(blocks, kMfmaGrid));
     if (st[0] < kLineBits<T>)
         hipLaunchKernelGGL((k_group_mfma<T, K, false>), grid, dim3(kBlock), 0, L.stream, (V*)amp, ngroups, ins, gb, lowmask,
                            dev_m);
     else
         hipLaunchKernelGGL((k_group_mfma<T, K, true>), grid, dim3(kBlock), 0, L.stream, (V*)amp, ngroups, ins, gb, lowmask,
                            dev_m);
+    return hipGetLastError();
+}
+
+template <typename T>
+hipError_t launch_dm_two(const Launch& L, void* rho, int N, const int* targets, const std::complex<double>* m)
+{
+    using V = typename C2<T>::type;
+    int st[2];
+    MatK<T, 2> u;
+    sort_targets<T>(targets, 2, m, st, u.m);
+    const int pos[4] = {st[0], st[1], st[0] + N, st[1] + N};
+    GroupBits<4> gb;
+    for (int j = 0; j < 4; ++j) gb.tbit[j] = 1ull << pos[j];
+    const BitInsert ins = make_insert(pos, 4, 0);
+    const uint64_t ngroups = 1ull << (2 * N - 4);
+    const dim3 grid((unsigned)std::min<uint64_t>((ngroups + 63) / 64, kMfmaGrid));
+    hipLaunchKernelGGL(k_dm_two<T>, grid, dim3(kBlock), 0, L.stream, (V*)rho, ngroups, ins, gb, u);
     return hipGetLastError();
 }
 
@@ -2051,6 +2161,7 @@ hipError_t launch_fid_dm(const Launch& L, const void* rho, int N, const void* ps
     template hipError_t launch_prob_dm<T>(const Launch&, const void*, int, int, double*, double*);     \
     template hipError_t launch_collapse_sv<T>(const Launch&, void*, int, int, int, double);            \
     template hipError_t launch_collapse_dm<T>(const Launch&, void*, int, int, int, double); \
+    template hipError_t launch_dm_two<T>(const Launch&, void*, int, const int*, const std::complex<double>*); \
     template hipError_t launch_group_gate<T>(const Launch&, void*, int, const int*, int, const int*, int, \
                                              const std::complex<double>*, T*);                         \
     template hipError_t launch_init_fill<T>(const Launch&, void*, uint64_t, double, double);           \
