@@ -26,6 +26,7 @@
 #include <algorithm>
 #include <complex>
 #include <memory>
+#include <numeric>
 #include <vector>
 
 #include "qs_device.h"
@@ -40,7 +41,7 @@ constexpr int kRBMax = 5;
 
 // One register layout of a pass, 32 words: every wave loads it as one word
 // per lane and reads the words back with v_readlane.
-struct FPhase {
+struct alignas(16) FPhase {
     uint32_t wthr[kTBMax], wreg[kRBMax];  // LDS images of the layout being left
     uint32_t rthr[kTBMax], rreg[kRBMax];  // LDS images of the layout entered
     uint32_t op_begin, op_end;
@@ -53,6 +54,7 @@ struct FPass {
     uint64_t ld_thr[kTBMax], ld_reg[kRBMax];  // HBM offsets of the load layout
     uint64_t st_thr[kTBMax], st_reg[kRBMax];  // HBM offsets of the store layout
     BitInsert outside;                        // inserts zeros at the tile's qubits
+    uint32_t first_op[kPhMax + 1];            // of each phase among the FOps, and the end of the last
     FPhase ph[kPhMax + 1];                    // the phases, then (final_transpose) the store layout
 };
 
@@ -85,6 +87,15 @@ struct alignas(16) FRec {
     T m[12];
 };
 
+// Device form of one FOp, for passes that run op by op.
+template <typename T>
+struct alignas(16) FOne {
+    uint32_t kind, rmask, tmask, aux;
+    uint64_t gmask;
+    uint32_t cx, pad;
+    T m[8];
+};
+
 // Op kinds: class << 5 | sub.  Register-bit pairs (b1 < b2) are numbered in
 // lexical order.
 //   kCoreA, sub rb     unit-diagonal core, amplitudes in place: (a, b) <- (a + k b, b - conj(k) a)
@@ -101,7 +112,10 @@ struct alignas(16) FRec {
 // both bits of rmask are 1.
 enum : int {
     kCoreA = 0, kCoreB = 32, kNot = 64, kNotM = 96, kPhase = 128, kSign = 160, kDense4 = 192, kOther = 224,
-    kDiag = kOther + 8, kNop = kOther + 16
+    kDiag = kOther + 8, kNop = kOther + 16,
+    // of FOne, where NOTs with one register control are kNotM and phases and signs kPhase
+    kOneDense = 256,  // + rb, + 5 with register controls, + 10 with thread-bit controls
+    kOneDiag = 288    // + rb
 };
 // Class bits of the device code.
 enum : uint32_t {
@@ -197,14 +211,17 @@ template <typename T, int RB, int RBIT>
 __device__ __forceinline__ void diag_case(typename C2<T>::type (&v)[1 << RB], const T (&mm)[8], uint32_t rmask,
                                           bool sel)
 {
-    using V = typename C2<T>::type;
     const T d0r = sel ? mm[0] : T(1), d0i = sel ? mm[1] : T(0), d1r = sel ? mm[6] : T(1), d1i = sel ? mm[7] : T(0);
 #pragma unroll
     for (int r0 = 0; r0 < (1 << RB); ++r0) {
         if (r0 & (1 << RBIT)) continue;
         if (((uint32_t)r0 & rmask) != rmask) continue;
-        v[r0] = cmul<T, V>(d0r, d0i, v[r0]);
-        v[r0 | (1 << RBIT)] = cmul<T, V>(d1r, d1i, v[r0 | (1 << RBIT)]);
+        const int r1 = r0 | (1 << RBIT);
+        const T ax = v[r0].x, ay = v[r0].y, bx = v[r1].x, by = v[r1].y;
+        v[r0].x = fma(d0r, ax, -(d0i * ay));
+        v[r0].y = fma(d0r, ay, d0i * ax);
+        v[r1].x = fma(d1r, bx, -(d1i * by));
+        v[r1].y = fma(d1r, by, d1i * bx);
     }
 }
 
@@ -212,16 +229,26 @@ __device__ __forceinline__ void diag_case(typename C2<T>::type (&v)[1 << RB], co
 template <typename T, int RB, int RBIT, int C>
 __device__ __forceinline__ void not_case(typename C2<T>::type (&v)[1 << RB])
 {
+    using V = typename C2<T>::type;
 #pragma unroll
     for (int r0 = 0; r0 < (1 << RB); ++r0) {
         if (r0 & (1 << RBIT)) continue;
         if (C < 5 && !((r0 >> C) & 1)) continue;
         const int r1 = r0 | (1 << RBIT);
-        const T ax = v[r0].x, ay = v[r0].y, bx = v[r1].x, by = v[r1].y;
-        v[r0].x = bx;
-        v[r0].y = by;
-        v[r1].x = ax;
-        v[r1].y = ay;
+        // float pairs move as one (component by component twice the moves: 200
+        // NOTs on 26 qubits 1.77 ms, 1.60 so); double pairs cost k_fused 12
+        // registers and a wave that way
+        if constexpr (sizeof(T) == 4) {
+            const V t = v[r0];
+            v[r0] = v[r1];
+            v[r1] = t;
+        } else {
+            const T ax = v[r0].x, ay = v[r0].y, bx = v[r1].x, by = v[r1].y;
+            v[r0].x = bx;
+            v[r0].y = by;
+            v[r1].x = ax;
+            v[r1].y = ay;
+        }
     }
 }
 
@@ -482,23 +509,23 @@ __device__ __forceinline__ void lds_barrier()
     else asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
 }
 
-// Write the tile in the layout being left, read it in the one entered; lane
-// e < 32 of `pw` holds word e of the FPhase.
-template <typename T, int TB, int RB>
+// Write the tile in the layout being left, read it in the one entered; word(e)
+// is word e of the FPhase.
+template <typename T, int TB, int RB, typename W>
 __device__ __forceinline__ void relayout(typename C2<T>::type (&v)[1 << RB],
-                                         typename C2<T>::type* lds, uint32_t pw, uint32_t tid)
+                                         typename C2<T>::type* lds, W word, uint32_t tid)
 {
     uint32_t tw = 0, tr = 0, wreg[RB], rreg[RB];
 #pragma unroll
     for (int b = 0; b < TB; ++b) {
         const uint32_t on = 0u - ((tid >> b) & 1u);
-        tw ^= on & lane_get(pw, b);
-        tr ^= on & lane_get(pw, kTBMax + kRBMax + b);
+        tw ^= on & word(b);
+        tr ^= on & word(kTBMax + kRBMax + b);
     }
 #pragma unroll
     for (int b = 0; b < RB; ++b) {
-        wreg[b] = lane_get(pw, kTBMax + b);
-        rreg[b] = lane_get(pw, 2 * kTBMax + kRBMax + b);
+        wreg[b] = word(kTBMax + b);
+        rreg[b] = word(2 * kTBMax + kRBMax + b);
     }
 #pragma unroll
     for (int r = 0; r < (1 << RB); ++r) lds[tw ^ span<RB, uint32_t>((uint32_t)r, wreg)] = v[r];
@@ -555,7 +582,7 @@ __device__ __forceinline__ void process_tile(typename C2<T>::type* __restrict__ 
     for (int ph = 0; ph < nlay; ++ph) {
         // the next phase's words and records, in flight during this one's ops
         const uint32_t npw = ((const uint32_t*)&P->ph[ph + 1 < nlay ? ph + 1 : ph])[lane & 31u];
-        if (ph > 0) relayout<T, TB, RB>(v, lds, pw, tid);
+        if (ph > 0) relayout<T, TB, RB>(v, lds, [&](int e) { return lane_get(pw, e); }, tid);
         const uint32_t nob = lane_get(npw, 30), noe = lane_get(npw, 31);
         OpLanes<T, RB> nxt;
         if constexpr (kAhead) nxt = load_ops<T, RB>(recs, nob, noe, lane);
@@ -615,6 +642,151 @@ __device__ __forceinline__ void process_tile(typename C2<T>::type* __restrict__ 
     for (int r = 0; r < E; ++r) amp[base + st_t + span_sum<RB, uint64_t>((uint32_t)r, P->st_reg)] = v[r];
 }
 
+// One FOp by one switch.  REG, LANE: register-bit and thread-bit controls.
+template <typename T, int RB, int RBIT, bool REG, bool LANE>
+__device__ __forceinline__ void one_dense(typename C2<T>::type (&v)[1 << RB], const FOne<T>& op, bool sel)
+{
+    using V = typename C2<T>::type;
+    T m[8];
+#pragma unroll
+    for (int k = 0; k < 8; ++k) m[k] = op.m[k];
+#pragma unroll
+    for (int k = 0; k < 8; ++k) {
+        if (LANE) m[k] = sel ? m[k] : (k == 0 || k == 6) ? T(1) : T(0);
+        // products with scalar registers are slower in complex64 (200 dense gates on 26 qubits 3.43 ms, 2.84 so)
+        else if (sizeof(T) == 4) asm("" : "+v"(m[k]));
+    }
+#pragma unroll
+    for (int r0 = 0; r0 < (1 << RB); ++r0) {
+        if (r0 & (1 << RBIT)) continue;
+        if (REG && ((uint32_t)r0 & op.rmask) != op.rmask) continue;  // uniform over the wave
+        apply2<T, V>(m, v[r0], v[r0 | (1 << RBIT)]);
+    }
+}
+
+// 4x4 on every register quad, the whole matrix in scalar registers.
+template <typename T, int RB, int B1, int B2>
+__device__ __forceinline__ void one_dense4(typename C2<T>::type (&v)[1 << RB], const T* __restrict__ m)
+{
+    using V = typename C2<T>::type;
+#pragma unroll
+    for (int r0 = 0; r0 < (1 << RB); ++r0) {
+        if ((r0 >> B1) & 1 || (r0 >> B2) & 1) continue;
+        const int r[4] = {r0, r0 | (1 << B1), r0 | (1 << B2), r0 | (1 << B1) | (1 << B2)};
+        const V x[4] = {v[r[0]], v[r[1]], v[r[2]], v[r[3]]};
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            // one product or multiply-add per statement
+            T re = m[8 * i] * x[0].x;
+            T im = m[8 * i] * x[0].y;
+            re = -m[8 * i + 1] * x[0].y + re;
+            im = m[8 * i + 1] * x[0].x + im;
+#pragma unroll
+            for (int j = 1; j < 4; ++j) {
+                const T mr = m[2 * (4 * i + j)], mi = m[2 * (4 * i + j) + 1];
+                re = mr * x[j].x + re;
+                re = -mi * x[j].y + re;
+                im = mr * x[j].y + im;
+                im = mi * x[j].x + im;
+            }
+            v[r[i]].x = re;
+            v[r[i]].y = im;
+        }
+    }
+}
+
+template <typename T, int RB>
+__device__ __forceinline__ void apply_one(typename C2<T>::type (&v)[1 << RB], const FOne<T>& op, uint32_t tid,
+                                          const T* __restrict__ m4tab)
+{
+    const uint32_t rmask = op.rmask;
+    const bool sel = (tid & op.tmask) == op.tmask;
+    switch (op.kind) {
+#define QS_O(B)                                                                                           \
+    case kCoreA + B: if constexpr (RB > B) core_case<T, RB, B, false>(v, op.m[0], op.m[1]); break;        \
+    case kCoreB + B: if constexpr (RB > B) core_case<T, RB, B, true>(v, op.m[0], op.m[1]); break;         \
+    case kNot + B: if constexpr (RB > B) not_case<T, RB, B, 5>(v); break;                                 \
+    case kNotM + B: if constexpr (RB > B) notm_case<T, RB, B>(v, rmask, sel); break;                      \
+    case kOneDense + B: if constexpr (RB > B) one_dense<T, RB, B, false, false>(v, op, sel); break; \
+    case kOneDense + 5 + B: if constexpr (RB > B) one_dense<T, RB, B, true, false>(v, op, sel); break; \
+    case kOneDense + 10 + B: if constexpr (RB > B) one_dense<T, RB, B, false, true>(v, op, sel); break; \
+    case kOneDense + 15 + B: if constexpr (RB > B) one_dense<T, RB, B, true, true>(v, op, sel); break; \
+    case kOneDiag + B: if constexpr (RB > B) diag_case<T, RB, B>(v, op.m, rmask, sel); break;
+        QS_O(0) QS_O(1) QS_O(2) QS_O(3) QS_O(4)
+#undef QS_O
+#define QS_O(P)                                                                                           \
+    case kDense4 + P:                                                                                     \
+        if constexpr (RB > kPairB2[P]) one_dense4<T, RB, kPairB1[P], kPairB2[P]>(v, m4tab + 32 * op.aux); \
+        break;
+        QS_O(0) QS_O(1) QS_O(2) QS_O(3) QS_O(4) QS_O(5) QS_O(6) QS_O(7) QS_O(8) QS_O(9)
+#undef QS_O
+    case kPhase: phase_case<T, RB, 0>(v, sel ? op.m[0] : T(1), sel ? op.m[1] : T(0), rmask); break;
+    default: break;
+    }
+    if (op.cx) phase_case<T, RB, 0>(v, op.m[0], op.m[1], rmask | (1u << (op.cx - 1)));
+}
+
+// One tile of a pass whose time goes into 4x4s or full 2x2s (op_gain): an op at
+// a time, its record and matrix read through the scalar cache, whose latency
+// other waves hide.  The records of process_tile save that latency and pay in
+// issue slots: a complex128 4x4 gets its 32 values with 64 v_readlanes, a
+// quarter of its multiply-adds' time.  200 two-qubit gates on 26 qubits in
+// 12-qubit tiles: 19.3 ms by records, 14.7 so in complex128, 10.9 and 8.5 in
+// complex64; 200 one-qubit gates 3.6 and 4.9, 2.3 and 2.6.
+template <typename T, int TB, int RB>
+__device__ __forceinline__ void process_tile_ops(typename C2<T>::type* __restrict__ amp, const FPass* __restrict__ P,
+                                                 const FOne<T>* __restrict__ ops, const T* __restrict__ m4tab,
+                                                 uint64_t tile, typename C2<T>::type* lds, uint32_t tid,
+                                                 bool zero_init = false)
+{
+    using V = typename C2<T>::type;
+    const int nph = P->nphases, nlay = nph + P->final_transpose;
+    const uint64_t ld_t = span_sum<TB, uint64_t>(tid, P->ld_thr), st_t = span_sum<TB, uint64_t>(tid, P->st_thr);
+    const uint64_t base = expand(tile, P->outside);
+    V v[1 << RB];
+    if (zero_init) {  // the tile of |0..0>: nothing to read
+#pragma unroll
+        for (int r = 0; r < (1 << RB); ++r) {
+            v[r].x = base + ld_t + span_sum<RB, uint64_t>((uint32_t)r, P->ld_reg) == 0 ? T(1) : T(0);
+            v[r].y = T(0);
+        }
+    } else {
+#pragma unroll
+        for (int r = 0; r < (1 << RB); ++r) v[r] = amp[base + ld_t + span_sum<RB, uint64_t>((uint32_t)r, P->ld_reg)];
+    }
+    for (int ph = 0; ph < nlay; ++ph) {
+        if (ph > 0) {
+            uint4 F[8];
+#pragma unroll
+            for (int k = 0; k < 8; ++k) F[k] = ((const uint4*)&P->ph[ph])[k];
+            const auto word = [&](int e) {
+                const uint4 w = F[e / 4];
+                return e & 2 ? (e & 1 ? w.w : w.z) : (e & 1 ? w.y : w.x);
+            };
+            relayout<T, TB, RB>(v, lds, word, tid);
+        }
+        if (ph == nph) break;
+        for (uint32_t o = P->first_op[ph]; o < P->first_op[ph + 1]; ++o) {
+            const FOne<T>& op = ops[o];
+            if ((base & op.gmask) != op.gmask) continue;  // same for the whole tile
+            apply_one<T, RB>(v, op, tid, m4tab);
+        }
+    }
+#pragma unroll
+    for (int r = 0; r < (1 << RB); ++r) amp[base + st_t + span_sum<RB, uint64_t>((uint32_t)r, P->st_reg)] = v[r];
+}
+
+template <typename T, int TB, int RB>
+__global__ __launch_bounds__(1 << TB) void k_fused_ops(typename C2<T>::type* __restrict__ amp,
+                                                       const FPass* __restrict__ P,
+                                                       const FOne<T>* __restrict__ ops, const T* __restrict__ m4tab,
+                                                       uint64_t ntiles)
+{
+    __shared__ typename C2<T>::type lds[1 << (TB + RB)];
+    for (uint64_t tile = blockIdx.x; tile < ntiles; tile += gridDim.x)
+        process_tile_ops<T, TB, RB>(amp, P, ops, m4tab, tile, lds, threadIdx.x);
+}
+
 template <typename T, int TB, int RB>
 __global__ __launch_bounds__(1 << TB) void k_fused(typename C2<T>::type* __restrict__ amp,
                                                    const FPass* __restrict__ P,
@@ -647,11 +819,11 @@ struct BatchItem {
     uint32_t reg, pass, tile0, tile1;
 };
 
-template <typename T, int TB, int RB>
+template <typename T, int TB, int RB, bool BYOP>
 __global__ __launch_bounds__(1 << TB) void k_batch(const BatchReg* __restrict__ regs,
                                                    const BatchItem* __restrict__ items, int nitems,
                                                    const FPass* __restrict__ passes,
-                                                   const FRec<T>* __restrict__ recs, const T* __restrict__ m4tab,
+                                                   const void* __restrict__ ops, const T* __restrict__ m4tab,
                                                    int init)
 {
     using V = typename C2<T>::type;
@@ -663,7 +835,8 @@ __global__ __launch_bounds__(1 << TB) void k_batch(const BatchReg* __restrict__ 
         const FPass* P = passes + R.pass0 + it.pass;
         const bool zi = init && it.pass == 0;
         for (uint32_t tile = it.tile0; tile < it.tile1; ++tile)
-            process_tile<T, TB, RB>((V*)R.amp, P, recs, m4tab, tile, lds, tid, zi);
+            if constexpr (BYOP) process_tile_ops<T, TB, RB>((V*)R.amp, P, (const FOne<T>*)ops, m4tab, tile, lds, tid, zi);
+            else process_tile<T, TB, RB>((V*)R.amp, P, (const FRec<T>*)ops, m4tab, tile, lds, tid, zi);
     }
 }
 
@@ -881,6 +1054,34 @@ CoreForm core_form(const Cx (&u)[2][2])
     return {3, k, u[0][1], u[1][0]};
 }
 
+// What an op gains op by op over the records, where the chip is full.  Measured
+// on 26 qubits with 200 ops of a kind, in units of 3 us (1.5 in complex64): a
+// 4x4 8, a 2x2 with controls or not as a core 1, a core -2 (-1), a phase -3
+// (-2).  Complex64 with 8 amplitudes a thread: such a 2x2 2, a NOT with controls
+// and a diagonal 2x2 1, a phase -1; with 32: a 4x4 2, a 2x2 nothing.  Signs, of
+// which several share a record, -6, but a batch's choice is not to depend on
+// angles.
+int op_gain(const OpRec& op, bool dbl, int RB)
+{
+    const bool narrow = !dbl && RB == 3, wide = !dbl && RB == 5;
+    if (op.kind == 4) return wide ? 2 : 8;
+    if (op.kind == 1) return narrow && !op.ctrls.empty();
+    if (op.kind == 2) return op.ctrls.size() < 2 ? 0 : dbl ? -3 : narrow ? -1 : -2;
+    Cx u[2][2];
+    for (int i = 0; i < 4; ++i) u[i / 2][i % 2] = Cx(op.u[2 * i], op.u[2 * i + 1]);
+    const int form = core_form(u).form;
+    if (op.ctrls.empty() && form >= 0) return form < 2 ? 0 : dbl ? -2 : -1;
+    return wide ? 0 : (narrow ? 2 : 1) - (form == 0);
+}
+
+bool gains_by_op(const std::vector<OpRec>& ops, const std::vector<int>& which, int prec, const FusedConfig& c)
+{
+    if (c.TB == 9 && c.RB == 5) return false;  // 14-qubit tiles: 12.2 ms either way for 200 4x4s on 26 qubits
+    int gain = 0;
+    for (int k : which) gain += op_gain(ops[k], prec == QS_C128, c.RB);
+    return gain > 0;
+}
+
 // Device form of a planned pass list, appended to hp / hops / m4 (op
 // indices in the phases are positions in hops; 4x4 ops index m4 in blocks
 // of 32 values).  The ops are lowered on the way: an uncontrolled dense
@@ -916,7 +1117,7 @@ void serialize(const std::vector<PassPlan>& plan, const std::vector<OpRec>& ops,
             const Layout& L = P.phases[ph].lay;
             const Layout& prev = ph ? P.phases[ph - 1].lay : L;
             fill_phase(Fp, prev, L, K);
-            Fp.op_begin = (uint32_t)hops.size();
+            Fp.op_begin = F.first_op[ph] = (uint32_t)hops.size();
             auto reg_bit = [&](int q) {
                 for (int b = 0; b < RB; ++b)
                     if (L.reg[b] == local[q]) return b;
@@ -1079,7 +1280,7 @@ void serialize(const std::vector<PassPlan>& plan, const std::vector<OpRec>& ops,
                 d.gsc = 1.0;
                 d.gsc_used = false;
             }
-            Fp.op_end = (uint32_t)hops.size();
+            Fp.op_end = F.first_op[ph + 1] = (uint32_t)hops.size();
         }
         const Layout& last = P.phases.back().lay;
         F.final_transpose = (last.reg == P.store.reg && last.thr == P.store.thr) ? 0 : 1;
@@ -1110,6 +1311,30 @@ hipError_t launch_cfg(hipStream_t s, void* amp, const FPass* P, const void* recs
     hipLaunchKernelGGL((k_fused<T, TB, RB>), dim3((unsigned)grid), dim3(1 << TB), 0, s, (V*)amp, P,
                        (const FRec<T>*)recs, (const T*)m4, ntiles);
     return hipGetLastError();
+}
+
+template <typename T, int TB, int RB>
+hipError_t launch_ops_cfg(hipStream_t s, void* amp, const FPass* P, const void* ops, const void* m4, uint64_t ntiles)
+{
+    const uint64_t grid = std::min<uint64_t>(ntiles, 256 * 16);
+    hipLaunchKernelGGL((k_fused_ops<T, TB, RB>), dim3((unsigned)grid), dim3(1 << TB), 0, s,
+                       (typename C2<T>::type*)amp, P, (const FOne<T>*)ops, (const T*)m4, ntiles);
+    return hipGetLastError();
+}
+
+template <typename T>
+hipError_t launch_ops_pass(hipStream_t s, const FusedConfig& c, void* amp, const FPass* P, const void* ops,
+                           const void* m4, uint64_t ntiles)
+{
+#define QS_SHAPE(tb, rb) \
+    if (c.TB == tb && c.RB == rb) return launch_ops_cfg<T, tb, rb>(s, amp, P, ops, m4, ntiles);
+    QS_SHAPE(6, 3) QS_SHAPE(7, 3) QS_SHAPE(8, 3) QS_SHAPE(8, 4) QS_SHAPE(9, 3)
+    QS_SHAPE(9, 4) QS_SHAPE(10, 3)
+    if constexpr (sizeof(T) == 4) {
+        QS_SHAPE(8, 5) QS_SHAPE(10, 4)
+    }
+#undef QS_SHAPE
+    return hipErrorInvalidValue;
 }
 
 template <typename T>
@@ -1174,12 +1399,22 @@ static FusedConfig batch_config(int prec, int k, int n)
 // and then laid out for `c`, whose wider phases hold one or more planned
 // phases each: the order of the ops, and so every rounding, is that of the
 // default shape.
-static std::vector<PassPlan> batch_plan(const std::vector<OpRec>& ops, int n, int prec, const FusedConfig& c)
+//
+// A register whose circuit gains op by op (op_gain) keeps the default shape,
+// and `c` becomes that: 256 registers of 10 qubits are 256 waves of the wider
+// one, a quarter of the SIMDs, and 100 two-qubit gates on each took 189 us there,
+// 133 so.  The choice is the register's own, so that its results do not depend
+// on the batch.
+static std::vector<PassPlan> batch_plan(const std::vector<OpRec>& ops, int n, int prec, FusedConfig& c, bool& by_op)
 {
     const int K = c.TB + c.RB;
     const FusedConfig d = default_fused_config(prec, K, K);
     const int contig = std::min(4, d.TB);
     std::vector<PassPlan> plan = plan_passes(ops, n, d.TB, d.RB, kPhMax, 1 << 12, contig);
+    std::vector<int> all(ops.size());
+    std::iota(all.begin(), all.end(), 0);
+    by_op = gains_by_op(ops, all, prec, d);
+    if (by_op) c = d;
     if (d.RB == c.RB) return plan;
     for (PassPlan& P : plan) {
         std::vector<PhasePlan> wide;
@@ -1371,6 +1606,40 @@ std::vector<char> rec_bytes(std::vector<FPass>& hp, const std::vector<FOp>& hops
     return prec == QS_C128 ? rec_bytes_t<double>(hp, hops) : rec_bytes_t<float>(hp, hops);
 }
 
+template <typename T>
+std::vector<char> one_bytes_t(const std::vector<FOp>& hops)
+{
+    std::vector<char> out(hops.size() * sizeof(FOne<T>), 0);
+    FOne<T>* o = (FOne<T>*)out.data();
+    for (size_t k = 0; k < hops.size(); ++k, ++o) {
+        const FOp& f = hops[k];
+        const int cls = f.kind & 0xe0;
+        o->kind = (uint32_t)f.kind;
+        o->rmask = f.rmask;
+        o->tmask = f.tmask;
+        o->gmask = f.gmask;
+        o->aux = f.aux;
+        for (int i = 0; i < 8; ++i) o->m[i] = (T)f.m[i];
+        if (cls == kNot) {
+            const uint32_t bit = 1u << f.rb;
+            if (f.cx) o->cx = f.rb + 1;
+            o->rmask = f.rmask & ~bit;
+            o->kind = (o->rmask ? kNotM : kNot) + f.rb;
+        } else if (cls == kPhase || cls == kSign) {
+            o->kind = kPhase;
+        } else if (cls == kOther && f.kind != kNop) {
+            const int b = f.kind & 7;
+            o->kind = f.kind & 8 ? kOneDiag + b : kOneDense + b + (f.rmask ? 5 : 0) + (f.tmask ? 10 : 0);
+        }
+    }
+    return out;
+}
+
+std::vector<char> one_bytes(const std::vector<FOp>& hops, int prec)
+{
+    return prec == QS_C128 ? one_bytes_t<double>(hops) : one_bytes_t<float>(hops);
+}
+
 }  // namespace
 
 // The passes of one circuit for one register shape and tile, as uploaded.
@@ -1378,11 +1647,14 @@ struct FusedPlan {
     int nbits, kind, prec, TB, RB, max_phases;
     size_t nops;
     uint64_t version;
-    size_t npasses, off_recs, off_m4;
-    std::vector<char> host;  // FPass[], op records, 4x4 table
+    size_t npasses, off_recs, off_ops, off_m4;
+    std::vector<char> host;  // FPass[], op records, FOnes, 4x4 table
+    std::vector<bool> by_op;  // passes run by k_fused_ops
 };
 
 namespace {
+
+
 
 // The circuit's plan for this register and tile: the one it keeps, or a new
 // one, which it keeps from then on.  Planning takes 0.3 ms or more for a few
@@ -1408,8 +1680,16 @@ std::shared_ptr<const FusedPlan> fused_plan(qs_reg r, qs_circuit_s* c, const Fus
     std::vector<FOp> hops;
     std::vector<double> m4;
     serialize(plan, ops, cfg.TB, cfg.RB, r->prec, hp, hops, m4);
-    const std::vector<char> m4b = m4_bytes(m4, r->prec), recs = rec_bytes(hp, hops, r->prec);
     std::shared_ptr<FusedPlan> p = std::make_shared<FusedPlan>();
+    std::vector<char> ones;
+    // op by op needs four waves for each SIMD to hide its latency: 200 two-qubit
+    // gates in 12-qubit tiles took the same time either way on 20 qubits in
+    // complex128 (one wave) and 21 in complex64, 1361 us by records and 1147 op by
+    // op on 22, and 827 and 746
+    const bool full = (1ull << (r->nbits - cfg.RB)) >= 256 * 4 * 4 * 64;
+    for (const PassPlan& P : plan) p->by_op.push_back(full && gains_by_op(ops, P.ops, r->prec, cfg));
+    if (std::find(p->by_op.begin(), p->by_op.end(), true) != p->by_op.end()) ones = one_bytes(hops, r->prec);
+    const std::vector<char> m4b = m4_bytes(m4, r->prec), recs = rec_bytes(hp, hops, r->prec);
     p->nbits = r->nbits;
     p->kind = r->kind;
     p->prec = r->prec;
@@ -1421,10 +1701,12 @@ std::shared_ptr<const FusedPlan> fused_plan(qs_reg r, qs_circuit_s* c, const Fus
     p->npasses = hp.size();
     const size_t pbytes = hp.size() * sizeof(FPass);
     p->off_recs = (pbytes + 15) & ~(size_t)15;
-    p->off_m4 = (p->off_recs + recs.size() + 255) & ~(size_t)255;
+    p->off_ops = (p->off_recs + recs.size() + 15) & ~(size_t)15;
+    p->off_m4 = (p->off_ops + ones.size() + 255) & ~(size_t)255;
     p->host.resize(p->off_m4 + m4b.size());
     memcpy(p->host.data(), hp.data(), pbytes);
     memcpy(p->host.data() + p->off_recs, recs.data(), recs.size());
+    if (!ones.empty()) memcpy(p->host.data() + p->off_ops, ones.data(), ones.size());
     memcpy(p->host.data() + p->off_m4, m4b.data(), m4b.size());
     c->fused = p;
     return p;
@@ -1458,11 +1740,15 @@ qs_status run_fused_sv(qs_reg r, qs_circuit_s* c, FusedConfig cfg, int* passes_o
     }
     const FPass* dP = (const FPass*)dbuf;
     const void* dO = (const char*)dbuf + plan->off_recs;
+    const void* dS = (const char*)dbuf + plan->off_ops;
     const void* dM = (const char*)dbuf + plan->off_m4;
     const uint64_t ntiles = 1ull << (nbits - cfg.TB - cfg.RB);
     qs_status st = QS_OK;
     for (size_t p = 0; p < plan->npasses && st == QS_OK; ++p) {
         st = profiled(r, QS_K_FUSED, [&](int*) {
+            if (plan->by_op[p])
+                return r->prec == QS_C128 ? launch_ops_pass<double>(r->stream, cfg, r->amp, dP + p, dS, dM, ntiles)
+                                          : launch_ops_pass<float>(r->stream, cfg, r->amp, dP + p, dS, dM, ntiles);
             return r->prec == QS_C128 ? launch_fused_pass<double>(r->stream, cfg, r->amp, dP + p, dO, dM, ntiles)
                                       : launch_fused_pass<float>(r->stream, cfg, r->amp, dP + p, dO, dM, ntiles);
         });
@@ -1480,52 +1766,54 @@ qs_status run_fused_sv(qs_reg r, qs_circuit_s* c, FusedConfig cfg, int* passes_o
 
 namespace {
 
-template <typename T, int TB, int RB>
+template <typename T, int TB, int RB, bool BYOP>
 hipError_t batch_launch_t(qs_batch_s* b, const qs_batch_s::Launch& L, int init)
 {
     const char* base = (const char*)b->dbuf;
     const BatchItem* items = (const BatchItem*)(base + b->off_order);
-    hipLaunchKernelGGL((k_batch<T, TB, RB>), dim3(std::min(L.count, L.grid)), dim3(1 << TB), 0, b->stream,
+    hipLaunchKernelGGL((k_batch<T, TB, RB, BYOP>), dim3(std::min(L.count, L.grid)), dim3(1 << TB), 0, b->stream,
                        (const BatchReg*)(base + b->off_regs), items + L.off, L.count,
-                       (const FPass*)(base + b->off_passes), (const FRec<T>*)(base + b->off_ops),
+                       (const FPass*)(base + b->off_passes), (const void*)(base + (BYOP ? b->off_ones : b->off_ops)),
                        (const T*)(base + b->off_m4), init);
     return hipGetLastError();
 }
+
+// The shapes of batch_plan: the batch's, and the default ones of circuits that
+// gain op by op.
+#define QS_BATCH_SHAPES(X)                                                        \
+    X(6, 3, false) X(6, 4, false) X(7, 4, false) X(8, 4, false) X(9, 4, false)    \
+    X(6, 3, true) X(7, 3, true) X(8, 3, true) X(8, 4, true)                       \
+    if constexpr (sizeof(T) == 4) { X(8, 5, false) X(9, 5, false) X(8, 5, true) }               \
+    else { X(9, 4, true) }
 
 template <typename T>
 hipError_t batch_launch_p(qs_batch_s* b, int init)
 {
     for (const qs_batch_s::Launch& L : b->launches) {
         hipError_t e = hipErrorInvalidValue;
-#define QS_B(tb, rb) \
-    if (L.TB == tb && L.RB == rb) e = batch_launch_t<T, tb, rb>(b, L, init);
-        QS_B(6, 3) QS_B(6, 4) QS_B(7, 4) QS_B(8, 4) QS_B(9, 4)
-        if constexpr (sizeof(T) == 4) {
-            QS_B(8, 5) QS_B(9, 5)
-        }
+#define QS_B(tb, rb, byop) \
+    if (L.TB == tb && L.RB == rb && L.by_op == byop) e = batch_launch_t<T, tb, rb, byop>(b, L, init);
+        QS_BATCH_SHAPES(QS_B)
 #undef QS_B
         if (e != hipSuccess) return e;
     }
     return hipSuccess;
 }
 
-template <typename T, int TB, int RB>
+template <typename T, int TB, int RB, bool BYOP>
 int batch_occupancy()
 {
     int nb = 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, k_batch<T, TB, RB>, 1 << TB, 0) != hipSuccess) nb = 1;
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, k_batch<T, TB, RB, BYOP>, 1 << TB, 0) != hipSuccess) nb = 1;
     return nb < 1 ? 1 : nb;
 }
 
 template <typename T>
-int batch_occupancy_p(int TB, int RB)
+int batch_occupancy_p(int TB, int RB, bool by_op)
 {
-#define QS_O(tb, rb) \
-    if (TB == tb && RB == rb) return batch_occupancy<T, tb, rb>();
-    QS_O(6, 3) QS_O(6, 4) QS_O(7, 4) QS_O(8, 4) QS_O(9, 4)
-    if constexpr (sizeof(T) == 4) {
-        QS_O(8, 5) QS_O(9, 5)
-    }
+#define QS_O(tb, rb, byop) \
+    if (TB == tb && RB == rb && by_op == byop) return batch_occupancy<T, tb, rb, byop>();
+    QS_BATCH_SHAPES(QS_O)
 #undef QS_O
     return 1;
 }
@@ -1535,6 +1823,7 @@ int batch_occupancy_p(int TB, int RB)
 struct BatchPlans {
     std::vector<std::vector<PassPlan>> plans;  // per register
     std::vector<bool> placeholder;             // an empty circuit's identity pass
+    std::vector<bool> by_op;
 };
 
 void batch_plans_free(BatchPlans* p) { delete p; }
@@ -1575,10 +1864,12 @@ qs_status batch_build(qs_batch_s* b, const std::vector<qs_reg>& regs,
             ops = &none;
         }
         // a register narrower than the batch tile is one tile of its own width
-        const FusedConfig rc = regs[i]->n >= cfg.TB + cfg.RB ? cfg : batch_config(b->prec, regs[i]->n, regs[i]->n);
+        FusedConfig rc = regs[i]->n >= cfg.TB + cfg.RB ? cfg : batch_config(b->prec, regs[i]->n, regs[i]->n);
+        bool by_op;
+        std::vector<PassPlan> plan = batch_plan(*ops, regs[i]->n, b->prec, rc, by_op);
         b->reg_TB[i] = rc.TB;
         b->reg_RB[i] = rc.RB;
-        std::vector<PassPlan> plan = batch_plan(*ops, regs[i]->n, b->prec, rc);
+        bp->by_op.push_back(by_op);
         per_item[i] = 1ull << (regs[i]->n - (rc.TB + rc.RB));  // tile count, for now
         hr[i].amp = regs[i]->amp;
         hr[i].n = regs[i]->n;
@@ -1604,10 +1895,15 @@ qs_status batch_build(qs_batch_s* b, const std::vector<qs_reg>& regs,
     uint64_t total_tiles = 0;
     for (uint64_t t : per_item) total_tiles += t;
     const uint64_t per = std::max<uint64_t>(1, std::min<uint64_t>(16, total_tiles / 16384));
-    for (uint64_t& t : per_item) t = std::min(t, per);
+    // op by op about 8 items per CU: tiles of a register one after the other find
+    // its ops in the scalar cache (32 registers of 20 qubits in complex64, 100
+    // controlled gates on each: 1.55 ms with one tile an item, 0.97 with five)
+    const uint64_t per_ops = std::min<uint64_t>(16, (total_tiles + 2047) / 2048);
+    for (size_t i = 0; i < regs.size(); ++i) per_item[i] = std::min(per_item[i], bp->by_op[i] ? per_ops : per);
     if (hp.empty()) hp.push_back(FPass{});
     b->circ_ops.assign(circs.begin(), circs.end());
     b->host_ops = rec_bytes(hp, hops, b->prec);
+    if (std::find(bp->by_op.begin(), bp->by_op.end(), true) != bp->by_op.end()) b->host_ones = one_bytes(hops, b->prec);
     b->reg_pass_begin.assign(regs.size(), 0);
     for (size_t i = 0; i < regs.size(); ++i) b->reg_pass_begin[i] = hr[i].pass0;
     b->host_m4 = m4;
@@ -1618,25 +1914,29 @@ qs_status batch_build(qs_batch_s* b, const std::vector<qs_reg>& regs,
     std::stable_sort(byn.begin(), byn.end(), [&](uint32_t a, uint32_t c) { return hr[a].n > hr[c].n; });
     std::vector<BatchItem> items;
     b->launches.clear();
-    std::vector<std::pair<int, int>> shapes;  // distinct tile shapes, batch shape first
-    shapes.push_back({cfg.TB, cfg.RB});
+    struct Kernel {
+        int TB, RB;
+        bool by_op;
+        bool operator==(const Kernel& o) const { return TB == o.TB && RB == o.RB && by_op == o.by_op; }
+    };
+    auto kernel_of = [&](size_t i) { return Kernel{b->reg_TB[i], b->reg_RB[i], bp->by_op[i]}; };
+    std::vector<Kernel> kernels{{cfg.TB, cfg.RB, false}};  // distinct ones, the batch shape's first
     for (size_t i = 0; i < regs.size(); ++i)
-        if (std::find(shapes.begin(), shapes.end(), std::make_pair(b->reg_TB[i], b->reg_RB[i])) == shapes.end())
-            shapes.push_back({b->reg_TB[i], b->reg_RB[i]});
+        if (std::find(kernels.begin(), kernels.end(), kernel_of(i)) == kernels.end()) kernels.push_back(kernel_of(i));
     for (int p = 0; p < maxpasses; ++p) {
-        for (const auto& sh : shapes) {
+        for (const Kernel& k : kernels) {
             const int off = (int)items.size();
             for (uint32_t i : byn) {
-                if (p >= hr[i].npasses || b->reg_TB[i] != sh.first || b->reg_RB[i] != sh.second) continue;
-                const uint64_t ntiles = 1ull << (hr[i].n - (sh.first + sh.second)), per = per_item[i];
+                if (p >= hr[i].npasses || !(kernel_of(i) == k)) continue;
+                const uint64_t ntiles = 1ull << (hr[i].n - (k.TB + k.RB)), per = per_item[i];
                 for (uint64_t t0 = 0; t0 < ntiles; t0 += per)
                     items.push_back(BatchItem{i, (uint32_t)p, (uint32_t)t0, (uint32_t)std::min(ntiles, t0 + per)});
             }
             const int count = (int)items.size() - off;
             if (count == 0) continue;
-            const int per_cu = b->prec == QS_C128 ? batch_occupancy_p<double>(sh.first, sh.second)
-                                                  : batch_occupancy_p<float>(sh.first, sh.second);
-            b->launches.push_back({sh.first, sh.second, off, count, (int)(256L * per_cu)});
+            const int per_cu = b->prec == QS_C128 ? batch_occupancy_p<double>(k.TB, k.RB, k.by_op)
+                                                  : batch_occupancy_p<float>(k.TB, k.RB, k.by_op);
+            b->launches.push_back({k.TB, k.RB, k.by_op, off, count, (int)(256L * per_cu)});
         }
     }
     b->nitems = (int)items.size();
@@ -1645,7 +1945,8 @@ qs_status batch_build(qs_batch_s* b, const std::vector<qs_reg>& regs,
     b->off_order = align(hr.size() * sizeof(BatchReg));
     b->off_passes = align(b->off_order + items.size() * sizeof(BatchItem));
     b->off_ops = align(b->off_passes + hp.size() * sizeof(FPass));
-    b->off_m4 = align(b->off_ops + b->host_ops.size());
+    b->off_ones = align(b->off_ops + b->host_ops.size());
+    b->off_m4 = align(b->off_ones + b->host_ones.size());
     b->off_pieces = align(b->off_m4 + m4b.size());
     b->npieces = (int)pieces.size();
     const size_t total = align(b->off_pieces + pieces.size() * sizeof(ProbItem));
@@ -1656,6 +1957,7 @@ qs_status batch_build(qs_batch_s* b, const std::vector<qs_reg>& regs,
     memcpy(host.data() + b->off_order, items.data(), items.size() * sizeof(BatchItem));
     memcpy(host.data() + b->off_passes, hp.data(), hp.size() * sizeof(FPass));
     memcpy(host.data() + b->off_ops, b->host_ops.data(), b->host_ops.size());
+    if (!b->host_ones.empty()) memcpy(host.data() + b->off_ones, b->host_ones.data(), b->host_ones.size());
     memcpy(host.data() + b->off_m4, m4b.data(), m4b.size());
     // stream-ordered allocation and upload: creating a batch does not wait
     // for work on other streams (a plain free or a synchronous copy would)
@@ -1679,6 +1981,7 @@ qs_status batch_update(qs_batch_s* b)
     // trade forms (see Defer) leave the number of ops as it is and the phases
     // between them one slot off.
     const size_t rsz = b->prec == QS_C128 ? sizeof(FRec<double>) : sizeof(FRec<float>);
+    const size_t osz = b->prec == QS_C128 ? sizeof(FOne<double>) : sizeof(FOne<float>);
     FPass* passes = (FPass*)(b->host_plan.data() + b->off_passes);
     for (size_t i = 0; i < b->regs.size(); ++i) {
         if (b->plans->placeholder[i]) continue;
@@ -1692,12 +1995,19 @@ qs_status batch_update(qs_batch_s* b)
             if ((f.kind & 0xe0) == kDense4) f.aux += (uint32_t)(b->reg_m4_begin[i] / 32);
         const std::vector<char> recs = rec_bytes(hp, hops, b->prec);
         memcpy(b->host_ops.data() + b->reg_op_begin[i] * rsz, recs.data(), hops.size() * rsz);
-        for (size_t p = 0; p < hp.size(); ++p)
+        if (b->plans->by_op[i]) {
+            const std::vector<char> ones = one_bytes(hops, b->prec);
+            memcpy(b->host_ones.data() + b->reg_op_begin[i] * osz, ones.data(), ones.size());
+        }
+        const uint32_t first = (uint32_t)b->reg_op_begin[i];
+        for (size_t p = 0; p < hp.size(); ++p) {
+            FPass& P = passes[b->reg_pass_begin[i] + p];
             for (int ph = 0; ph < hp[p].nphases; ++ph) {
-                FPhase& F = passes[b->reg_pass_begin[i] + p].ph[ph];
-                F.op_begin = (uint32_t)b->reg_op_begin[i] + hp[p].ph[ph].op_begin;
-                F.op_end = (uint32_t)b->reg_op_begin[i] + hp[p].ph[ph].op_end;
+                P.ph[ph].op_begin = first + hp[p].ph[ph].op_begin;
+                P.ph[ph].op_end = first + hp[p].ph[ph].op_end;
             }
+            for (int ph = 0; ph <= hp[p].nphases; ++ph) P.first_op[ph] = first + hp[p].first_op[ph];
+        }
         std::copy(m4.begin(), m4.end(), b->host_m4.begin() + b->reg_m4_begin[i]);
     }
     // from pageable memory the copies have left the host tables when the
@@ -1706,6 +2016,11 @@ qs_status batch_update(qs_batch_s* b)
     hipError_t e = hipMemcpyAsync((char*)b->dbuf + b->off_ops, b->host_ops.data(), b->host_ops.size(),
                                   hipMemcpyHostToDevice, b->stream);
     if (e != hipSuccess) return hip_error(e, "batch parameter upload");
+    if (!b->host_ones.empty()) {
+        e = hipMemcpyAsync((char*)b->dbuf + b->off_ones, b->host_ones.data(), b->host_ones.size(),
+                           hipMemcpyHostToDevice, b->stream);
+        if (e != hipSuccess) return hip_error(e, "batch parameter upload");
+    }
     e = hipMemcpyAsync((char*)b->dbuf + b->off_passes, passes, (size_t)b->passes_total * sizeof(FPass),
                        hipMemcpyHostToDevice, b->stream);
     if (e != hipSuccess) return hip_error(e, "batch parameter upload");

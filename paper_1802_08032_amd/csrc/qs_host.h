@@ -92,15 +92,17 @@ struct qs_batch_s {
     std::vector<qs_reg> regs;
     std::vector<hipStream_t> reg_streams;  // distinct streams of the registers
     hipEvent_t ev_in, ev_out;
-    // BatchReg[] + BatchItem[] + FPass[] + op records + 4x4 table + ProbItem[] + probability partials
+    // BatchReg[] + BatchItem[] + FPass[] + op records + ops one by one + 4x4 table + ProbItem[] + probability partials
     void* dbuf = nullptr;
-    size_t off_regs, off_order, off_passes, off_ops, off_m4, off_pieces, off_partials;
+    size_t off_regs, off_order, off_passes, off_ops, off_ones, off_m4, off_pieces, off_partials;
     int nitems = 0, npieces = 0;
-    // launches in order: pass level by pass level, one per tile shape that
-    // has items at that level (registers narrower than the batch tile are
-    // one tile of their own width)
+    // launches in order: pass level by pass level, one per tile shape (and way
+    // of running ops) that has items at that level (registers narrower than the
+    // batch tile are one tile of their own width)
     struct Launch {
-        int TB, RB, off, count, grid;
+        int TB, RB;
+        bool by_op;
+        int off, count, grid;
     };
     std::vector<Launch> launches;
     std::vector<int> reg_TB, reg_RB;  // tile shape of each register
@@ -114,7 +116,7 @@ struct qs_batch_s {
     std::vector<const std::vector<OpRec>*> circ_ops;
     qs::BatchPlans* plans = nullptr;
     std::vector<size_t> reg_op_begin, reg_op_count, reg_m4_begin, reg_m4_count, reg_pass_begin;
-    std::vector<char> host_ops;
+    std::vector<char> host_ops, host_ones;
     std::vector<double> host_m4;
     // host sources of the asynchronous uploads on the batch stream (kept
     // until the batch is destroyed)
