@@ -1014,9 +1014,9 @@ FOp encode_op(const OpRec& op, const PassPlan& P, const Layout& L)
 // Diagonal factors deferred by the lowering (see lower_passes): the true
 // state is gsc times prod_q exp(i phi[q] x_q) over the qubits with has[q],
 // times the stored state.  Which qubits carry a factor, and whether gsc was
-// touched, depends only on the op structure, with one exception: a gate off
-// from unitary by more than 1e-14 (core_form -1) defers nothing, so a controlled
-// gate behind it needs no phase multiplied in first and its phase has an op less.
+// touched, depends only on the op structure, not on matrix values, so a
+// circuit with new parameters lowers to the same number of ops in every phase: a
+// gate off from unitary (core_form -1) defers a phase of 0.
 struct Defer {
     double phi[64] = {};
     bool has[64] = {};
@@ -1234,19 +1234,17 @@ void serialize(const std::vector<PassPlan>& plan, const std::vector<OpRec>& ops,
                         }
                     f.kind = kOther + b;
                     d.phi[t] = 0.0;
-                    d.has[t] = false;
-                    hops.push_back(f);
-                    continue;
+                } else {
+                    const int kind_of[4] = {kNop, kNot + 6 * b + 5, kCoreA + b, kCoreB + b};
+                    f.kind = kind_of[cf.form];
+                    for (int k = 0; k < 8; ++k) f.m[k] = 0.0;
+                    f.m[0] = cf.k.real();
+                    f.m[1] = cf.k.imag();
+                    d.gsc *= cf.d0;
+                    d.phi[t] = std::arg(cf.d1 / cf.d0);
                 }
-                const int kind_of[4] = {kNop, kNot + 6 * b + 5, kCoreA + b, kCoreB + b};
-                f.kind = kind_of[cf.form];
-                for (int k = 0; k < 8; ++k) f.m[k] = 0.0;
-                f.m[0] = cf.k.real();
-                f.m[1] = cf.k.imag();
                 hops.push_back(f);
-                d.gsc *= cf.d0;
                 d.gsc_used = true;
-                d.phi[t] = std::arg(cf.d1 / cf.d0);
                 d.has[t] = true;
                 if (++d.shrink >= max_shrink(prec)) {  // a fixed point in the op structure
                     hops.push_back(phase_fop(0, 0, 0, d.gsc));
@@ -1975,11 +1973,9 @@ qs_status batch_build(qs_batch_s* b, const std::vector<qs_reg>& regs,
 qs_status batch_update(qs_batch_s* b)
 {
     // lower every register's plan again with the circuits' current values: the
-    // passes and the number of ops are unchanged; the kernel data (matrices,
-    // core coefficients, deferred phases) and the phases' op ranges follow the
-    // parameters.  Both ends of a range move: two gates of different phases that
-    // trade forms (see Defer) leave the number of ops as it is and the phases
-    // between them one slot off.
+    // structure (and so the slots of its ops) is unchanged; the kernel data
+    // (matrices, core coefficients, deferred phases) and the phases' ranges of
+    // records follow the parameters
     const size_t rsz = b->prec == QS_C128 ? sizeof(FRec<double>) : sizeof(FRec<float>);
     const size_t osz = b->prec == QS_C128 ? sizeof(FOne<double>) : sizeof(FOne<float>);
     FPass* passes = (FPass*)(b->host_plan.data() + b->off_passes);

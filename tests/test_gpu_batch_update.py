@@ -1,10 +1,8 @@
-"""Parameters of a captured batch: an update that changes the form of gates in
-different phases of a pass.
+"""Parameters of a captured batch: updates that change the form of gates.
 
 A gate that is unitary to 1e-10 but not to 1e-14 is applied as a full matrix
-instead of a core, and a controlled gate behind it on the same qubit then needs
-no phase multiplied in first: one op fewer in its phase.  Two gates that trade
-forms keep the op count of the circuit and move the phases between them.
+instead of a core.  What follows it has the same ops all the same: two such
+gates in different phases may trade forms, and any gate may change its own.
 
 Tolerance: a gate computed with unit round-off e adds at most about 4 e to the
 2-norm error of a normalised state, and a gate off by d from unitary changes
@@ -68,3 +66,28 @@ def test_gates_of_two_phases_trade_forms(q, env, oracle_lib, tile, extra, prec):
         b.close()
         circ.close()
         reg.close()
+
+
+@pytest.mark.parametrize('prec', ['C128', 'C64'])
+@pytest.mark.parametrize('tile', [9, 10, 12])
+def test_one_gate_changes_its_form(q, env, oracle_lib, tile, prec):
+    from workloads import Op, haar_unitary
+    rng = np.random.default_rng(100 + tile)
+    n = tile + 1
+    ops = [Op('u', target=t, u=haar_unitary(rng)) for t in range(n)]
+    ops += [Op('x', target=t, controls=(t - 1,)) for t in range(1, n)]
+    ops += [Op('u', target=t, controls=(t - 1, 0) if t > 1 else (t - 1,), u=haar_unitary(rng)) for t in range(1, n)]
+    reg = q.Register(env, n, q.STATEVEC, getattr(q, prec))
+    circ = q.Circuit(ops)
+    b = q.Batch([reg], [circ], tile)
+    b.capture(init_zero=True)
+    for k, off in ((n - 1, 1e-12), (0, 1e-11), (n - 1, 0.0), (n // 2, 1e-12), (0, 0.0)):
+        ops[k].u = haar_unitary(rng) + off * (rng.standard_normal((2, 2)) + 1j * rng.standard_normal((2, 2)))
+        circ.set_unitary(k, ops[k].u)
+        b.update()
+        b.replay()
+        err = float(np.max(np.abs(reg.get_amps() - oracle_lib.run_sv(n, ops))))
+        assert err <= 4 * EPS[prec] * len(ops) + 1e-13, (k, off, err)
+    b.close()
+    circ.close()
+    reg.close()
