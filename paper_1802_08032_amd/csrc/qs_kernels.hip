@@ -236,8 +236,7 @@ __global__ __launch_bounds__(kBlock) void k_not(typename C2<T>::type* __restrict
 }
 
 // Diagonal phase on the amplitudes whose `ins.ones` bits are all set,
-// except those that also have every bit of `skip` set (skip != 0; no bit of
-// it lies within a line), which are not touched.
+// except those that also have every bit of `skip` set (skip != 0).
 template <typename T, int U>
 __global__ __launch_bounds__(kBlock) void k_phase(typename C2<T>::type* __restrict__ amp,
                                                   uint64_t count, BitInsert ins, uint64_t lowmask,
@@ -248,26 +247,31 @@ __global__ __launch_bounds__(kBlock) void k_phase(typename C2<T>::type* __restri
     const StepItems<U> at(ps, kBlock, ins);
     const uint64_t et = deposit(threadIdx.x, ins);
     // bits within a line are the thread's own: its other values are written
-    // back unchanged so that every store is a full line
+    // back unchanged so that every store is a full line, and so are excepted
+    // ones; only where no bit of `skip` lies within a line are those not touched
     const bool ok = (et & lowmask) == lowmask;
-    const uint64_t none = skip ? 0 : ~0ull;  // with no skip bits nothing is left out
+    constexpr uint64_t kIn = (1ull << kLineBits<T>) - 1;
+    const uint64_t sin = skip & kIn, sline = skip & ~kIn;
+    const uint64_t none = skip && !sin ? 0 : ~0ull;              // all ones: no line is left out
+    const uint64_t kept = sin && (et & sin) == sin ? 0 : ~0ull;  // all ones: this thread's values all turn
     for (uint64_t s = blockIdx.x; step_base(s, ps) < count; s += gridDim.x) {
         const uint64_t c = step_base(s, ps);
         const uint64_t ec = deposit(c, ins) | ins.ones;
-        bool on[U];
+        bool on[U], hit[U];
         V v[U];
 #pragma unroll
         for (int j = 0; j < U; ++j) {
             const uint64_t e = et + (ec + at(j));
-            on[j] = step_item(c, j, ps) < count && (e & skip) != (skip | none);
+            on[j] = step_item(c, j, ps) < count && (e & sline) != (sline | none);
+            hit[j] = ok && (e & sline) != (sline | kept);
             v[j].x = v[j].y = T(0);
             if (on[j]) v[j] = ldnt(amp + e);
         }
 #pragma unroll
         for (int j = 0; j < U; ++j) {
             const V m = cmul<T, V>(fr, fi, v[j]);
-            v[j].x = ok ? m.x : v[j].x;
-            v[j].y = ok ? m.y : v[j].y;
+            v[j].x = hit[j] ? m.x : v[j].x;
+            v[j].y = hit[j] ? m.y : v[j].y;
         }
 #pragma unroll
         for (int j = 0; j < U; ++j)
@@ -275,8 +279,8 @@ __global__ __launch_bounds__(kBlock) void k_phase(typename C2<T>::type* __restri
     }
 }
 
-// Phase of a density matrix whose qubits lie within a line, rows and columns
-// in one pass: rows with all bits of `rmask` set gain (fr, fi), columns with
+// Phase of a density matrix on qubits some of which lie within a line, rows
+// and columns in one pass: rows with all bits of `rmask` set gain (fr, fi), columns with
 // all bits of `cmask` set its conjugate, entries with both nothing.  Two
 // passes of k_phase read and write most lines twice (CZ on qubits 0 and 1 of
 // 13: complex128 512 us, 365 so; complex64 455, 162).
@@ -1721,10 +1725,17 @@ template <typename T>
 hipError_t launch_dm_phase(const Launch& L, void* rho, int N, uint64_t rmask, double fre, double fim)
 {
     using V = typename C2<T>::type;
-    // qubits within a line: one pass over everything; the lines a pass for the
-    // rows and one for the columns would leave out are few
-    if (rmask & ((1ull << kLineBits<T>) - 1)) {
-        const uint64_t len = 1ull << (2 * N);
+    // qubits within a line: one pass over everything, while the lines that a
+    // pass for the rows and one for the columns would leave out are few, or the
+    // second launch costs more than the walk over them.  Two passes against
+    // one, 13 qubits, complex128 / complex64: qubits 0 and 1 401 us, 362 / 221,
+    // 161; 2 and 4 269, 214 / 140, 120; 0, 1 and 12 235, 253 / 118, 118; 2, 4
+    // and 5 161, 143 / 82, 106; 2 to 5 82, 128 / 72, 103; 11 qubits, 2 to 5
+    // 8.9, 12.5 (64 MiB) / 8.8, 7.0 (32 MiB).
+    const uint64_t len = 1ull << (2 * N);
+    const int inside = __builtin_popcountll(rmask & ((1ull << kLineBits<T>) - 1));
+    const int above = __builtin_popcountll(rmask >> kLineBits<T>);
+    if (inside && (above == 0 || (above == 1 && inside == 1) || len * 2 * sizeof(T) <= (32ull << 20))) {
         constexpr int U = kPer<double>;  // complex64 too: its 32 index tests per step cost more than the fewer steps save
         const bool big = wide(len, U);
         const StreamShape sh = stream_shape<T>(len, big ? U : kSmallPer, len);
