@@ -808,12 +808,12 @@ __global__ __launch_bounds__(kBlock) void k_collapse_dm(typename C2<T>::type* __
 // ---------------------------------------------------------------------------
 // Measure-all.  The items j < count of a subspace sit at index
 // pattern + (j << shift), with the outcomes so far in `st` (null: none yet);
-// item j falls in bin j mod 2^mbits (mbits <= 10).  Each block writes 2^mbits
-// Neumaier partials (sum, compensation) of |alpha|^2, or of a density
-// matrix's diagonal (DM: entry i at i (dim + 1)).  Steps are multiples
-// of 1024 items, so with the alternating step order the thread's j-th element
-// lies in bin ((j >> 1) & 3) * kBlock + tid (mod 2^mbits): four accumulators
-// per thread, folded through LDS.
+// item j falls in bin j mod 2^mbits; mbits is 10, or less and count = 2^mbits.
+// Each block writes 2^mbits Neumaier partials (sum, compensation) of
+// |alpha|^2, or of a density matrix's diagonal (DM: entry i at i (dim + 1)).
+// Steps are multiples of 1024 items, so with the alternating step order the
+// thread's j-th element lies in bin ((j >> 1) & 3) * kBlock + tid of 1024:
+// four bins per thread, no exchange between threads.
 template <typename T, int U, bool DM>
 __global__ __launch_bounds__(kBlock) void k_hist(const typename C2<T>::type* __restrict__ amp, uint64_t count,
                                                  int shift, uint64_t dim, const MeasureState* __restrict__ st,
@@ -822,7 +822,6 @@ __global__ __launch_bounds__(kBlock) void k_hist(const typename C2<T>::type* __r
     using V = typename C2<T>::type;
     const uint64_t fixed = st ? st->pattern : 0;
     static_assert((kBlock * U / 2) % 1024 == 0, "steps must be whole multiples of 1024 bins");
-    __shared__ double ls[4 * kBlock], lc[4 * kBlock];
     NSum acc[4] = {};
     const uint64_t ps = (uint64_t)kBlock * U;
     for (uint64_t s = blockIdx.x; step_base(s, ps) < count; s += gridDim.x) {
@@ -842,18 +841,14 @@ __global__ __launch_bounds__(kBlock) void k_hist(const typename C2<T>::type* __r
             nadd(acc[(j >> 1) & 3], step_item(c, j, ps) < count ? p : 0.0);
         }
     }
+    const int nb = 1 << mbits;
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
-        ls[k * kBlock + threadIdx.x] = acc[k].s;
-        lc[k * kBlock + threadIdx.x] = acc[k].c;
-    }
-    __syncthreads();
-    const int nb = 1 << mbits;
-    for (int b = threadIdx.x; b < nb; b += kBlock) {
-        NSum a = {0.0, 0.0};
-        for (int e = b; e < 4 * kBlock; e += nb) a = nmerge(a, NSum{ls[e], lc[e]});
-        partials[2 * ((uint64_t)blockIdx.x * nb + b)] = a.s;
-        partials[2 * ((uint64_t)blockIdx.x * nb + b) + 1] = a.c;
+        const int b = k * kBlock + threadIdx.x;
+        if (b < nb) {
+            partials[2 * ((uint64_t)blockIdx.x * nb + b)] = acc[k].s;
+            partials[2 * ((uint64_t)blockIdx.x * nb + b) + 1] = acc[k].c;
+        }
     }
 }
 
