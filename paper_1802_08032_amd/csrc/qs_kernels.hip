@@ -959,8 +959,9 @@ __global__ __launch_bounds__(kBlock) void k_measure_basis(typename C2<T>::type* 
     }
 }
 
-// dst <- src.  28 qubits complex128, 8.6 GB moved: 1.44 ms, 1.98 by the
-// runtime's copy; plain stores 1.54.
+// dst <- src, from 256 MiB on; smaller states take the runtime's copy.  28
+// qubits complex128, 8.6 GB moved: 1.44 ms, 1.98 by the runtime's copy; plain
+// stores 1.54.  256 MiB 95 us and 100; 128 MiB 46 and 37; 16 MiB 6.9 and 4.5.
 template <typename T, int U>
 __global__ __launch_bounds__(kBlock) void k_copy(typename C2<T>::type* __restrict__ dst,
                                                  const typename C2<T>::type* __restrict__ src, uint64_t len)
@@ -982,7 +983,6 @@ __global__ __launch_bounds__(kBlock) void k_copy(typename C2<T>::type* __restric
         }
     }
 }
-
 
 // ---------------------------------------------------------------------------
 // k-qubit groups.  Eq. 1 and the Eq. 2 identity hold for gates on several
@@ -1586,12 +1586,10 @@ template <typename T>
 hipError_t launch_copy(const Launch& L, void* dst, const void* src, uint64_t len)
 {
     using V = typename C2<T>::type;
+    if (len * 2 * sizeof(T) < (256ull << 20))
+        return hipMemcpyAsync(dst, src, len * 2 * sizeof(T), hipMemcpyDeviceToDevice, L.stream);
     const StreamShape sh = stream_shape<T>(len, kPer<T>, len);
-    if (wide(len, kPer<T>))
-        hipLaunchKernelGGL((k_copy<T, kPer<T>>), sh.grid, dim3(kBlock), sh.lds, L.stream, (V*)dst, (const V*)src, len);
-    else
-        hipLaunchKernelGGL((k_copy<T, kSmallPer>), dim3(grid_for(len, kSmallPer)), dim3(kBlock), 0, L.stream, (V*)dst,
-                           (const V*)src, len);
+    hipLaunchKernelGGL((k_copy<T, kPer<T>>), sh.grid, dim3(kBlock), sh.lds, L.stream, (V*)dst, (const V*)src, len);
     return hipGetLastError();
 }
 
