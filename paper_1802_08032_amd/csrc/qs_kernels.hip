@@ -1505,16 +1505,30 @@ inline bool wide(uint64_t items, int per) { return items >= (uint64_t)512 * kBlo
 // workgroups on a CU, and more of them in the grid let the dispatcher even
 // out the CUs.  complex128, 29 qubits: gate on qubit 17 5.4 TB/s with six
 // workgroups on a CU, 5.7 with four, 6.0 with two; T gate 5.3 to 5.9;
-// complex64, 30 qubits, CNOT 5.6 to 6.2.  Data within the cache wants the
-// waves instead (complex64, 128 MiB, gate on qubit 4: 43 us, 47 with two).
+// complex64, 30 qubits, CNOT 5.6 to 6.2.
+//
+// Of the passes that touch less, from 128 MiB on only those gain that walk
+// pairs or a strided part of the state (`mid`): complex128, gate on qubit 6 of
+// 23 and 24 51 and 100 us, 47 and 91 so; CNOT of 24 94 and 87; dephasing of
+// qubit 2 of 12 95 and 89; complex64, 25 qubits, gate on qubit 6 95 and 89; 24
+// qubits, CNOT 48.5, with four workgroups 46.4, with two 49.  The others want
+// the waves: complex64, 128 MiB, gate on qubit 4 43 us, 47 with two; complex128,
+// 24 qubits, gate on qubit 4 86 and 90, targets 0, 1, 2 91 and 106; phase on
+// qubit 5 of a 12-qubit density matrix 61 and 64; dephasing of qubit 5 of 13,
+// complex64, 100 and 140.
 struct StreamShape {
     dim3 grid;
     unsigned lds;
 };
 template <typename T>
-static StreamShape stream_shape(uint64_t items, int per, uint64_t amps, unsigned lds = 64 << 10)
+static StreamShape stream_shape(uint64_t items, int per, uint64_t amps, bool mid = false, unsigned lds = 64 << 10)
 {
-    if (amps * 2 * sizeof(T) < (512ull << 20)) return {dim3(grid_for(items, per)), 0};
+    const uint64_t bytes = amps * 2 * sizeof(T);
+    if (bytes < (512ull << 20)) {
+        if (!mid || bytes < (128ull << 20)) lds = 0;
+        else if (sizeof(T) == 4 && bytes < (256ull << 20)) lds = 40000;
+        return {dim3(grid_for(items, per)), lds};
+    }
     const uint64_t blocks = items / ((uint64_t)kBlock * per);
     return {dim3((unsigned)std::min<uint64_t>(blocks, 4 * kMaxGrid)), lds};
 }
@@ -1646,7 +1660,7 @@ hipError_t launch_gate(const Launch& L, void* amp, int nbits, int t, const int* 
     pos[np] = t;
     const BitInsert ins = make_insert(pos, np + 1, ones);
     const uint64_t npairs = 1ull << (nbits - 1 - np);
-    const StreamShape sh = stream_shape<T>(npairs, kPer<T> / 2, 2 * npairs);
+    const StreamShape sh = stream_shape<T>(npairs, kPer<T> / 2, 2 * npairs, true);
     if (wide(npairs, kPer<T> / 2))
         hipLaunchKernelGGL((k_gate_pair<T, kPer<T> / 2>), sh.grid, dim3(kBlock), sh.lds, L.stream,
                            (V*)amp, npairs, 1ull << t, ins, lowmask, u);
@@ -1682,7 +1696,7 @@ hipError_t launch_not(const Launch& L, void* amp, int nbits, int t, const int* c
     pos[np] = t;
     const BitInsert ins = make_insert(pos, np + 1, ones);
     const uint64_t npairs = 1ull << (nbits - 1 - np);
-    const StreamShape sh = stream_shape<T>(npairs, kPer<T> / 2, 2 * npairs);
+    const StreamShape sh = stream_shape<T>(npairs, kPer<T> / 2, 2 * npairs, true);
     if (wide(npairs, kPer<T> / 2))
         hipLaunchKernelGGL((k_not<T, kPer<T> / 2>), sh.grid, dim3(kBlock), sh.lds, L.stream,
                            (V*)amp, npairs, 1ull << t, ins, lowmask);
@@ -1704,7 +1718,7 @@ hipError_t launch_phase(const Launch& L, void* amp, int nbits, uint64_t mask, ui
         if ((mask >> q) & 1) pos[np++] = q;
     const BitInsert ins = make_insert(pos, np, mask & ~lowmask);
     const uint64_t count = 1ull << (nbits - np);
-    const StreamShape sh = stream_shape<T>(count, kPer<T>, count);
+    const StreamShape sh = stream_shape<T>(count, kPer<T>, count, !skip);
     if (wide(count, kPer<T>))
         hipLaunchKernelGGL((k_phase<T, kPer<T>>), sh.grid, dim3(kBlock), sh.lds, L.stream,
                            (V*)amp, count, ins, lowmask, skip, (T)fre, (T)fim);
@@ -1761,7 +1775,7 @@ hipError_t launch_dm_gate(const Launch& L, void* rho, int N, int t, const int* c
     constexpr int G = kPer<T> / 4, G2 = kPer<T> / 2;
     const bool big = wide(items, low ? G2 : G);
     const StreamShape sh = stream_shape<T>(items, !big ? kSmallPer : low ? G2 : G,
-                                             (nc ? 3ull : 4ull) << (2 * N - 2));
+                                             (nc ? 3ull : 4ull) << (2 * N - 2), sizeof(T) == 8);
 #define QS_DM(K) hipLaunchKernelGGL(K, sh.grid, dim3(kBlock), sh.lds, L.stream, (V*)rho, items, tb, cb, ins, rmask, rmask << N, u)
     if (low) {
         if (big) QS_DM((k_dm_gate_low<T, G2>));
@@ -1786,7 +1800,8 @@ static hipError_t dm_channel(const Launch& L, void* rho, int N, int t, double p0
     constexpr int G = kPer<T> / 4, G2 = kPer<T> / 2;
     const bool big = wide(items, low ? G2 : G);
     const StreamShape sh = stream_shape<T>(items, !big ? kSmallPer : low ? G2 : G,
-                                             (CH == QS_DEPHASING && !low ? 1ull : 2ull) << (2 * N - 1));
+                                             (CH == QS_DEPHASING && !low ? 1ull : 2ull) << (2 * N - 1),
+                                             sizeof(T) == 8);
 #define QS_CH(K) hipLaunchKernelGGL(K, sh.grid, dim3(kBlock), sh.lds, L.stream, (V*)rho, items, tb, cb, ins, p0, p1, f)
     if (low) {
         if (big) QS_CH((k_dm_channel_low<T, CH, G2>));
@@ -1948,7 +1963,7 @@ static hipError_t group_lane(const Launch& L0, void* amp, int nbits, const int* 
     for (int j = 0; j < np; ++j) ip[ni++] = pos[j];
     const uint64_t nitems = 1ull << (nbits - ni);
     const BitInsert ins = make_insert(ip, ni, ones);
-    const StreamShape sh = stream_shape<T>(nitems, P, nitems << (K - L), kGroupLds);
+    const StreamShape sh = stream_shape<T>(nitems, P, nitems << (K - L), false, kGroupLds);
     if (wide(nitems, P))
         hipLaunchKernelGGL((k_group_lane<T, K, L, P>), sh.grid, dim3(kBlock), sh.lds, L0.stream, (V*)amp,
                            nitems, ins, gb, lowmask, mk);
@@ -1994,7 +2009,7 @@ static hipError_t group_small(const Launch& L, void* amp, int nbits, const int* 
     const BitInsert ins = make_insert(pos, np, ones);
     const uint64_t ngroups = 1ull << (nbits - np);
     constexpr int P = std::max(1, (sizeof(T) == 8 ? 8 : 16) >> K);
-    const StreamShape sh = stream_shape<T>(ngroups, P, ngroups << K, kGroupLds);
+    const StreamShape sh = stream_shape<T>(ngroups, P, ngroups << K, false, kGroupLds);
     if (wide(ngroups, P))
         hipLaunchKernelGGL((k_group_gate<T, K, P>), sh.grid, dim3(kBlock), sh.lds, L.stream, (V*)amp,
                            ngroups, ins, gb, lowmask, mk);
