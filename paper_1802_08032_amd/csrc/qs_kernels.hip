@@ -1505,32 +1505,40 @@ inline bool wide(uint64_t items, int per) { return items >= (uint64_t)512 * kBlo
 // workgroups on a CU, and more of them in the grid let the dispatcher even
 // out the CUs.  complex128, 29 qubits: gate on qubit 17 5.4 TB/s with six
 // workgroups on a CU, 5.7 with four, 6.0 with two; T gate 5.3 to 5.9;
-// complex64, 30 qubits, CNOT 5.6 to 6.2.
+// complex64, 30 qubits, CNOT 5.6 to 6.2.  A pass that touches only the
+// amplitudes whose `ones` bits are set stays at 16 blocks per CU where one of
+// these is the address bit of 2 KB: blocks that take one step each, in the
+// order of their addresses, keep half the memory channels busy.  complex128,
+// 27 qubits, control 7, gate on qubit 14 473 us with the larger grid, 378 so,
+// targets 14 and 15 585 and 402; control 8 and 6 365 and 370, 3% slower so.
 //
 // Of the passes that touch less, from 128 MiB on only those gain that walk
 // pairs or a strided part of the state (`mid`): complex128, gate on qubit 6 of
 // 23 and 24 51 and 100 us, 47 and 91 so; CNOT of 24 94 and 87; dephasing of
-// qubit 2 of 12 95 and 89; complex64, 25 qubits, gate on qubit 6 95 and 89; 24
-// qubits, CNOT 48.5, with four workgroups 46.4, with two 49.  The others want
-// the waves: complex64, 128 MiB, gate on qubit 4 43 us, 47 with two; complex128,
-// 24 qubits, gate on qubit 4 86 and 90, targets 0, 1, 2 91 and 106; phase on
-// qubit 5 of a 12-qubit density matrix 61 and 64; dephasing of qubit 5 of 13,
-// complex64, 100 and 140.
+// qubit 2 of 12 95 and 89; targets 4 and 5 of 25, control 7, 162 and 144;
+// complex64, 25 qubits, gate on qubit 6 95 and 89; 24 qubits, CNOT 48.5, with
+// four workgroups 46.4, with two 49.  The others want the waves: complex64,
+// 128 MiB, gate on qubit 4 43 us, 47 with two; complex128, 24 qubits, gate on
+// qubit 4 86 and 90, targets 0, 1, 2 91 and 106; phase on qubit 5 of a 12-qubit
+// density matrix 61 and 64; dephasing of qubit 5 of 13, complex64, 100 and 140.
+// Four as well where `ones` holds the address bit of 4 KB: complex128, 25
+// qubits, phase on qubits 8 and 15 56 us, 70 with two.
 struct StreamShape {
     dim3 grid;
     unsigned lds;
 };
 template <typename T>
-static StreamShape stream_shape(uint64_t items, int per, uint64_t amps, bool mid = false, unsigned lds = 64 << 10)
+static StreamShape stream_shape(uint64_t items, int per, uint64_t amps, uint64_t ones = 0, bool mid = false,
+                                unsigned lds = 64u << 10)
 {
-    const uint64_t bytes = amps * 2 * sizeof(T);
+    const uint64_t bytes = amps * 2 * sizeof(T), fixed = ones * 2 * sizeof(T);
     if (bytes < (512ull << 20)) {
-        if (!mid || bytes < (128ull << 20)) lds = 0;
-        else if (sizeof(T) == 4 && bytes < (256ull << 20)) lds = 40000;
-        return {dim3(grid_for(items, per)), lds};
+        const bool few = mid && bytes >= (128ull << 20);
+        const bool four = (fixed & 4096) || (sizeof(T) == 4 && bytes < (256ull << 20));
+        return {dim3(grid_for(items, per)), !few ? 0u : four ? 40000u : 64u << 10};
     }
     const uint64_t blocks = items / ((uint64_t)kBlock * per);
-    return {dim3((unsigned)std::min<uint64_t>(blocks, 4 * kMaxGrid)), lds};
+    return {dim3((unsigned)std::min(blocks, fixed & 2048 ? kMaxGrid : 4 * kMaxGrid)), lds};
 }
 
 template <typename T>
@@ -1630,7 +1638,7 @@ hipError_t launch_gate(const Launch& L, void* amp, int nbits, int t, const int* 
         const uint64_t nchunks = 1ull << (nbits - 6 - nh);
         // one wave-row of 64 lanes per chunk, U chunks per wave per step
         const bool big = wide(nchunks * 64, kPer<T>);
-        const StreamShape sh = stream_shape<T>(nchunks * 64, big ? kPer<T> : kSmallPer, nchunks * 64);
+        const StreamShape sh = stream_shape<T>(nchunks * 64, big ? kPer<T> : kSmallPer, nchunks * 64, ones << 6);
         switch (t) {
 #define QS_LOW(TT) case TT:                                                                              \
     if (big)                                                                                             \
@@ -1660,7 +1668,7 @@ hipError_t launch_gate(const Launch& L, void* amp, int nbits, int t, const int* 
     pos[np] = t;
     const BitInsert ins = make_insert(pos, np + 1, ones);
     const uint64_t npairs = 1ull << (nbits - 1 - np);
-    const StreamShape sh = stream_shape<T>(npairs, kPer<T> / 2, 2 * npairs, true);
+    const StreamShape sh = stream_shape<T>(npairs, kPer<T> / 2, 2 * npairs, ones, true);
     if (wide(npairs, kPer<T> / 2))
         hipLaunchKernelGGL((k_gate_pair<T, kPer<T> / 2>), sh.grid, dim3(kBlock), sh.lds, L.stream,
                            (V*)amp, npairs, 1ull << t, ins, lowmask, u);
@@ -1696,7 +1704,7 @@ hipError_t launch_not(const Launch& L, void* amp, int nbits, int t, const int* c
     pos[np] = t;
     const BitInsert ins = make_insert(pos, np + 1, ones);
     const uint64_t npairs = 1ull << (nbits - 1 - np);
-    const StreamShape sh = stream_shape<T>(npairs, kPer<T> / 2, 2 * npairs, true);
+    const StreamShape sh = stream_shape<T>(npairs, kPer<T> / 2, 2 * npairs, ones, true);
     if (wide(npairs, kPer<T> / 2))
         hipLaunchKernelGGL((k_not<T, kPer<T> / 2>), sh.grid, dim3(kBlock), sh.lds, L.stream,
                            (V*)amp, npairs, 1ull << t, ins, lowmask);
@@ -1718,7 +1726,7 @@ hipError_t launch_phase(const Launch& L, void* amp, int nbits, uint64_t mask, ui
         if ((mask >> q) & 1) pos[np++] = q;
     const BitInsert ins = make_insert(pos, np, mask & ~lowmask);
     const uint64_t count = 1ull << (nbits - np);
-    const StreamShape sh = stream_shape<T>(count, kPer<T>, count, !skip);
+    const StreamShape sh = stream_shape<T>(count, kPer<T>, count, mask, !skip);
     if (wide(count, kPer<T>))
         hipLaunchKernelGGL((k_phase<T, kPer<T>>), sh.grid, dim3(kBlock), sh.lds, L.stream,
                            (V*)amp, count, ins, lowmask, skip, (T)fre, (T)fim);
@@ -1775,7 +1783,7 @@ hipError_t launch_dm_gate(const Launch& L, void* rho, int N, int t, const int* c
     constexpr int G = kPer<T> / 4, G2 = kPer<T> / 2;
     const bool big = wide(items, low ? G2 : G);
     const StreamShape sh = stream_shape<T>(items, !big ? kSmallPer : low ? G2 : G,
-                                             (nc ? 3ull : 4ull) << (2 * N - 2), sizeof(T) == 8);
+                                             (nc ? 3ull : 4ull) << (2 * N - 2), 0, sizeof(T) == 8);
 #define QS_DM(K) hipLaunchKernelGGL(K, sh.grid, dim3(kBlock), sh.lds, L.stream, (V*)rho, items, tb, cb, ins, rmask, rmask << N, u)
     if (low) {
         if (big) QS_DM((k_dm_gate_low<T, G2>));
@@ -1801,7 +1809,7 @@ static hipError_t dm_channel(const Launch& L, void* rho, int N, int t, double p0
     const bool big = wide(items, low ? G2 : G);
     const StreamShape sh = stream_shape<T>(items, !big ? kSmallPer : low ? G2 : G,
                                              (CH == QS_DEPHASING && !low ? 1ull : 2ull) << (2 * N - 1),
-                                             sizeof(T) == 8);
+                                             0, sizeof(T) == 8);
 #define QS_CH(K) hipLaunchKernelGGL(K, sh.grid, dim3(kBlock), sh.lds, L.stream, (V*)rho, items, tb, cb, ins, p0, p1, f)
     if (low) {
         if (big) QS_CH((k_dm_channel_low<T, CH, G2>));
@@ -1925,8 +1933,14 @@ hipError_t launch_collapse_dm(const Launch& L, void* rho, int N, int q, int outc
 
 // The group kernels keep half as much in flight per lane as the others, and
 // twice the workgroups on a CU: complex128, 25 qubits, targets 10 and 20:
-// 204 us with five, 214 with two; 0, 1, 2: 192 and 225.
-constexpr unsigned kGroupLds = 32000;
+// 204 us with five, 214 with two; 0, 1, 2: 192 and 225.  With the smaller grid
+// of a control at the address bit of 2 KB, all that fit (complex64, 27 qubits,
+// targets 4 and 5, control 8: 224 us, 242 with five).
+template <typename T>
+static unsigned group_lds(uint64_t ones)
+{
+    return (ones * 2 * sizeof(T)) & 2048 ? 0 : 32000;
+}
 
 // Sorts the targets, with the bits of the matrix index in the same order.
 template <typename T>
@@ -1963,7 +1977,8 @@ static hipError_t group_lane(const Launch& L0, void* amp, int nbits, const int* 
     for (int j = 0; j < np; ++j) ip[ni++] = pos[j];
     const uint64_t nitems = 1ull << (nbits - ni);
     const BitInsert ins = make_insert(ip, ni, ones);
-    const StreamShape sh = stream_shape<T>(nitems, P, nitems << (K - L), false, kGroupLds);
+    const StreamShape sh = stream_shape<T>(nitems, P, nitems << (K - L), ones, K == 2 && sizeof(T) == 8,
+                                           group_lds<T>(ones));
     if (wide(nitems, P))
         hipLaunchKernelGGL((k_group_lane<T, K, L, P>), sh.grid, dim3(kBlock), sh.lds, L0.stream, (V*)amp,
                            nitems, ins, gb, lowmask, mk);
@@ -2009,7 +2024,8 @@ static hipError_t group_small(const Launch& L, void* amp, int nbits, const int* 
     const BitInsert ins = make_insert(pos, np, ones);
     const uint64_t ngroups = 1ull << (nbits - np);
     constexpr int P = std::max(1, (sizeof(T) == 8 ? 8 : 16) >> K);
-    const StreamShape sh = stream_shape<T>(ngroups, P, ngroups << K, false, kGroupLds);
+    const StreamShape sh = stream_shape<T>(ngroups, P, ngroups << K, ones, K == 2 && sizeof(T) == 8,
+                                           group_lds<T>(ones));
     if (wide(ngroups, P))
         hipLaunchKernelGGL((k_group_gate<T, K, P>), sh.grid, dim3(kBlock), sh.lds, L.stream, (V*)amp,
                            ngroups, ins, gb, lowmask, mk);
