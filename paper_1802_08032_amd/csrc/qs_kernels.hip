@@ -318,9 +318,16 @@ __global__ __launch_bounds__(kBlock) void k_dm_phase(typename C2<T>::type* __res
     }
 }
 
-// `rline`, `cline`: the parts of rmask and cmask at or above a line; a lane
-// whose line holds no selected entry touches nothing, the others store whole
-// lines.
+template <typename T> constexpr int kHalfBits = kLineBits<T> - 1;
+
+// Density matrix, Eq. 2 fused into one pass.  A group is the four entries
+// (rho[r][c]) with row bit t = r and column bit t + N = c; the gate is
+// rho -> (R ? U : I) rho (C ? U^dagger : I), R and C: all bits of rmask, cmask
+// set.  Columns multiplied by U^dagger is conj(U) on the column qubit.
+// `rline`, `cline`: the parts of rmask and cmask at or above half a line; a
+// lane whose half holds no selected entry touches nothing, the others store
+// whole halves.  13 qubits, control 2 (the upper half of each line, complex128),
+// gate on qubit 12: 350 us by whole lines, 315 so; control 3 in complex64 177, 158.
 template <typename T, int G>
 __global__ __launch_bounds__(kBlock) void k_dm_gate(typename C2<T>::type* __restrict__ rho,
                                                     uint64_t ngroups, uint64_t tb, uint64_t cb,
@@ -331,7 +338,7 @@ __global__ __launch_bounds__(kBlock) void k_dm_gate(typename C2<T>::type* __rest
     T uc[8];
 #pragma unroll
     for (int k = 0; k < 8; ++k) uc[k] = (k & 1) ? -u.m[k] : u.m[k];
-    const uint64_t rline = rmask & ~((1ull << kLineBits<T>) - 1), cline = cmask & ~((1ull << kLineBits<T>) - 1);
+    const uint64_t rline = rmask & ~((1ull << kHalfBits<T>) - 1), cline = cmask & ~((1ull << kHalfBits<T>) - 1);
     const uint64_t ps = (uint64_t)kBlock * G;
     const StepItems<G> at(ps, kBlock, ins);
     const uint64_t et = deposit(threadIdx.x, ins);
@@ -389,7 +396,7 @@ __global__ __launch_bounds__(kBlock) void k_dm_gate_low(typename C2<T>::type* __
     T uc[8];
 #pragma unroll
     for (int k = 0; k < 8; ++k) uc[k] = (k & 1) ? -u.m[k] : u.m[k];
-    const uint64_t rline = rmask & ~((1ull << kLineBits<T>) - 1), cline = cmask & ~((1ull << kLineBits<T>) - 1);
+    const uint64_t rline = rmask & ~((1ull << kHalfBits<T>) - 1), cline = cmask & ~((1ull << kHalfBits<T>) - 1);
     const uint64_t ps = (uint64_t)kBlock * G;
     const StepItems<G> at(ps, kBlock, ins);
     const uint64_t et = deposit(threadIdx.x, ins);
