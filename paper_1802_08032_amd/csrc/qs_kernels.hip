@@ -1942,11 +1942,14 @@ hipError_t launch_collapse_dm(const Launch& L, void* rho, int N, int q, int outc
 // twice the workgroups on a CU: complex128, 25 qubits, targets 10 and 20:
 // 204 us with five, 214 with two; 0, 1, 2: 192 and 225.  With the smaller grid
 // of a control at the address bit of 2 KB, all that fit (complex64, 27 qubits,
-// targets 4 and 5, control 8: 224 us, 242 with five).
+// targets 4 and 5, control 8: 224 us, 242 with five).  From 2 GiB on two, but
+// where targets lie within a line: 28 qubits, complex64, targets 17, 25 and 27
+// 853 us with five, 737 with two, 18 and 19 767 and 700; 26 qubits 189 and 192,
+// 174 and 175; 0, 1 and 2 of 28 747 and 814.
 template <typename T>
-static unsigned group_lds(uint64_t ones)
+static unsigned group_lds(uint64_t ones, uint64_t amps = 0)
 {
-    return (ones * 2 * sizeof(T)) & 2048 ? 0 : 32000;
+    return (ones * 2 * sizeof(T)) & 2048 ? 0 : amps * 2 * sizeof(T) >= (2ull << 30) ? 64u << 10 : 32000;
 }
 
 // Sorts the targets, with the bits of the matrix index in the same order.
@@ -2032,7 +2035,7 @@ static hipError_t group_small(const Launch& L, void* amp, int nbits, const int* 
     const uint64_t ngroups = 1ull << (nbits - np);
     constexpr int P = std::max(1, (sizeof(T) == 8 ? 8 : 16) >> K);
     const StreamShape sh = stream_shape<T>(ngroups, P, ngroups << K, ones, K == 2 && sizeof(T) == 8,
-                                           group_lds<T>(ones));
+                                           group_lds<T>(ones, ngroups << K));
     if (wide(ngroups, P))
         hipLaunchKernelGGL((k_group_gate<T, K, P>), sh.grid, dim3(kBlock), sh.lds, L.stream, (V*)amp,
                            ngroups, ins, gb, lowmask, mk);
