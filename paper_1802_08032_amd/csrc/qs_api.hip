@@ -755,7 +755,7 @@ qs_status qs_calc_prob_of_outcome(qs_reg r, int qubit, int outcome, double* out)
                        : qs::launch_prob_half_sv<float>(L, r->amp, r->nbits, qubit, outcome, partials, r->host_res);
         });
         if (s) return s;
-            if ((s = sync_stream(r))) return s;
+        if ((s = sync_stream(r))) return s;
         *out = r->host_res[0];
         return QS_OK;
     }
@@ -1629,7 +1629,7 @@ qs_status order_after(hipStream_t waiter, hipStream_t producer)
 
 qs_status read_pair(qs_reg r, double out[2])
 {
-    const    qs_status s = sync_stream(r);
+    const qs_status s = sync_stream(r);
     if (s) return s;
     out[0] = r->host_res[0];
     out[1] = r->host_res[1];

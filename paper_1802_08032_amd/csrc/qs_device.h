@@ -62,8 +62,9 @@ __device__ __forceinline__ void stnt(V* p, V v)
     e.y = v.y;
     __builtin_nontemporal_store(e, (E*)p);
 }
-// 16 resident blocks of 4 waves per CU on 256 CUs: every grid-stride kernel
-// is capped here so that each CU holds a fixed share of the waves.
+// 16 resident blocks of 4 waves per CU on 256 CUs: grid-stride kernels are
+// capped here so that each CU holds a fixed share of the waves, but for the
+// streaming passes over 512 MiB and more.
 constexpr uint64_t kMaxGrid = 256 * 16;
 
 inline int grid_for(uint64_t items, int items_per_thread)

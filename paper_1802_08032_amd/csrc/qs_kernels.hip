@@ -5,8 +5,8 @@
 //
 // Layout: interleaved complex (double2 / float2), qubit q = bit q of the
 // index.  Every kernel loops over 64-bit indices with a grid capped at 16
-// blocks per CU; the streaming kernels take kPer amplitudes per thread per
-// step (see qs_device.h).
+// blocks per CU, or 64 for passes over 512 MiB and more (stream_shape); the
+// streaming kernels take kPer amplitudes per thread per step (see qs_device.h).
 #include <algorithm>
 #include <complex>
 #include <vector>
@@ -859,9 +859,9 @@ __global__ __launch_bounds__(kBlock) void k_hist(const typename C2<T>::type* __r
     }
 }
 
-// Fold the per-block partials of each bin; out[2b], out[2b+1] = (sum, compensation).
-// Folds the rows of partials, 16 bins of 16 slices of the rows per block: 256
-// rows of 1024 bins in 6 us, 67 by one thread per bin.
+// Folds the blocks' partials of each bin, 16 bins of 16 slices of the rows per
+// block; out[2b], out[2b+1] = (sum, compensation).  256 rows of 1024 bins in 6
+// us, 67 by one thread per bin.
 __global__ __launch_bounds__(kBlock) void k_hist_final(const double* __restrict__ partials, int nblocks,
                                                        int nb, double* __restrict__ out)
 {
@@ -1758,14 +1758,16 @@ hipError_t launch_dm_phase(const Launch& L, void* rho, int N, uint64_t rmask, do
     const int inside = __builtin_popcountll(rmask & ((1ull << kLineBits<T>) - 1));
     const int above = __builtin_popcountll(rmask >> kLineBits<T>);
     if (inside && (above == 0 || (above == 1 && inside == 1) || len * 2 * sizeof(T) <= (32ull << 20))) {
-        constexpr int U = kPer<double>;  // complex64 too: its 32 index tests per step cost more than the fewer steps save
+        // complex64 too: its 32 index tests per step cost more than the fewer steps save
+        constexpr int U = kPer<double>;
         const bool big = wide(len, U);
         const StreamShape sh = stream_shape<T>(len, big ? U : kSmallPer, len);
         if (big)
-            hipLaunchKernelGGL((k_dm_phase<T, U>), sh.grid, dim3(kBlock), sh.lds, L.stream, (V*)rho, len, rmask, rmask << N, (T)fre, (T)fim);
+            hipLaunchKernelGGL((k_dm_phase<T, U>), sh.grid, dim3(kBlock), sh.lds, L.stream, (V*)rho, len, rmask,
+                               rmask << N, (T)fre, (T)fim);
         else
-            hipLaunchKernelGGL((k_dm_phase<T, kSmallPer>), sh.grid, dim3(kBlock), 0, L.stream, (V*)rho, len, rmask, rmask << N, (T)fre,
-                               (T)fim);
+            hipLaunchKernelGGL((k_dm_phase<T, kSmallPer>), sh.grid, dim3(kBlock), 0, L.stream, (V*)rho, len, rmask,
+                               rmask << N, (T)fre, (T)fim);
         return hipGetLastError();
     }
     // rows with all bits set gain the phase, columns its conjugate; entries
@@ -1791,7 +1793,8 @@ hipError_t launch_dm_gate(const Launch& L, void* rho, int N, int t, const int* c
     const bool big = wide(items, low ? G2 : G);
     const StreamShape sh = stream_shape<T>(items, !big ? kSmallPer : low ? G2 : G,
                                              (nc ? 3ull : 4ull) << (2 * N - 2), 0, sizeof(T) == 8);
-#define QS_DM(K) hipLaunchKernelGGL(K, sh.grid, dim3(kBlock), sh.lds, L.stream, (V*)rho, items, tb, cb, ins, rmask, rmask << N, u)
+#define QS_DM(K)                                                                                              \
+    hipLaunchKernelGGL(K, sh.grid, dim3(kBlock), sh.lds, L.stream, (V*)rho, items, tb, cb, ins, rmask, rmask << N, u)
     if (low) {
         if (big) QS_DM((k_dm_gate_low<T, G2>));
         else QS_DM((k_dm_gate_low<T, kSmallPer>));
@@ -1846,8 +1849,8 @@ hipError_t launch_dm_channel(const Launch& L, void* rho, int N, int t, int chann
     }
 }
 
-// Up to this many items one block does the whole sum in one step of kAlonePer
-// items per thread, and there is one launch instead of two.  Beyond, many
+// Up to this many items one block does the whole sum, with kAlonePer loads per
+// thread in flight, and there is one launch instead of two.  Beyond, many
 // blocks and a fold are faster: 13 qubits complex64 3.3 us and 2.4 against
 // 9.1 by one block.
 constexpr int kAlonePer = 8;
@@ -2027,7 +2030,8 @@ static hipError_t group_small(const Launch& L, void* amp, int nbits, const int* 
         gb.tbit[j] = 1ull << st[j];
         nlow += st[j] < kLineBits<T>;
     }
-    // cross-lane reads need whole waves of items: 2^6 of them
+    // cross-lane reads need every lane of a group's 2^nlow active: the item
+    // count is a power of two of at least that
     switch (nlow) {
     case 1: return group_lane<T, K, 1>(L, amp, nbits, st, pos, np, ones, lowmask, gb, mk);
     case 2: return group_lane<T, K, 2>(L, amp, nbits, st, pos, np, ones, lowmask, gb, mk);
