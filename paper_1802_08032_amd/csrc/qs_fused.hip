@@ -1900,11 +1900,14 @@ qs_status batch_build(qs_batch_s* b, const std::vector<qs_reg>& regs,
     uint64_t total_tiles = 0;
     for (uint64_t t : per_item) total_tiles += t;
     const uint64_t per = std::max<uint64_t>(1, std::min<uint64_t>(16, total_tiles / 16384));
-    // op by op about 8 items per CU: tiles of a register one after the other find
+    // op by op about 8 waves for each SIMD: tiles of a register one after the other find
     // its ops in the scalar cache (32 registers of 20 qubits in complex64, 100
     // controlled gates on each: 1.55 ms with one tile an item, 0.97 with five)
-    const uint64_t per_ops = std::min<uint64_t>(16, (total_tiles + 2047) / 2048);
-    for (size_t i = 0; i < regs.size(); ++i) per_item[i] = std::min(per_item[i], bp->by_op[i] ? per_ops : per);
+    for (size_t i = 0; i < regs.size(); ++i) {
+        const uint64_t items = 8192 >> (b->reg_TB[i] > 6 ? b->reg_TB[i] - 6 : 0);
+        const uint64_t per_ops = std::min<uint64_t>(16, (total_tiles + items - 1) / items);
+        per_item[i] = std::min(per_item[i], bp->by_op[i] ? per_ops : per);
+    }
     if (hp.empty()) hp.push_back(FPass{});
     b->circ_ops.assign(circs.begin(), circs.end());
     b->host_ops = rec_bytes(hp, hops, b->prec);
